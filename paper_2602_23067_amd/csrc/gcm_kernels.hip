@@ -600,7 +600,7 @@ __device__ __forceinline__ u32x4 wave_xor_reduce(u32x4 a)
 
 // ---------------------------------------------------------------- fused tile kernel
 //
-// LDS layout (144 KiB, one workgroup per CU):
+// LDS layout of the passes with GHASH (148 KiB, one workgroup per CU):
 //   [0, 64 KiB)        byte-position GHASH table of H^64 for the current key,
 //                      entry-major: the product for byte value v at position
 //                      k sits at byte 256*v + 16*k, so position k lives in
@@ -608,55 +608,29 @@ __device__ __forceinline__ u32x4 wave_xor_reduce(u32x4 a)
 //   [64 KiB, 128 KiB)  AES T-tables: entry e of table t, copy c (c = 0..15)
 //                      at 0x10000 + 256*e + 64*t + 4*c.
 //   [128 KiB, 144 KiB) the key's lane fix-up window tables (slot layout).
+//   [144 KiB, 148 KiB) the message's round-2 words (see CtrBlock): 16 bytes
+//                      for each value of the low counter byte.
+// and of counter mode alone (132 KiB):
+//   [0, 128 KiB)       AES T-tables: entry e of table t, copy c (c = 0..31)
+//                      at 0x10000 * (t >> 1) + 256 * e + 128 * (t & 1) + 4 * c.
+//   [128 KiB, 132 KiB) the round-2 words.
 //
-// A wave64 ds_read_b32 takes two cycles when no two lanes of a half-wave
-// share a bank; random indices into one 1 KiB table cost about three times
-// that.  A ds_read_b128 serves 16 lanes per cycle, four banks each, so its
-// 16 lanes must fall in 16 different bank groups.  The GHASH lookups get that
-// from the schedule: in lookup j lane l reads position (j + l) & 15, with its
+// A wave64 ds_read_b32 takes two cycles, 32 lanes each, when no two lanes of a
+// half-wave share a bank; random indices into one 1 KiB table cost about three
+// times that.  With 32 copies lane l reads copy l & 31, a bank of its own
+// whatever its index.  Beside the GHASH table there is room for 16 copies:
+// lane l uses copy c = l & 15, and lane group g = (l >> 4) & 3 keeps its AES
+// state rotated left by 8g bits.  Because T_t = rotl(T_0, 8t), a rotated state
+// turns "table r, byte r" into "table (r+g)&3, byte (r+g)&3", so in every
+// lookup instruction the four lane groups read four different tables and every
+// lane again has a bank of its own; the price is a rotation of each round key
+// word.  One v_perm_b32 per lookup builds the address from the state byte and
+// the lane's table and copy.
+// A ds_read_b128 serves 16 lanes per cycle, four banks each, so its 16 lanes
+// must fall in 16 different bank groups.  The GHASH lookups get that from the
+// schedule: in lookup j lane l reads position (j + l) & 15, with its
 // accumulator held byte-rotated by l & 15 so that position is byte j of the
 // rotated value; 16 consecutive lanes then read 16 different positions.
-//  Here the bank of a T-table read depends only on
-// (t, c): lane l uses copy c = l & 15, and lane group g = (l >> 4) & 3 keeps
-// its AES state rotated left by 8g bits.  Because T_t = rotl(T_0, 8t), a
-// rotated state turns "table r, byte r" into "table (r+g)&3, byte (r+g)&3",
-// so in every lookup instruction the four lane groups read four different
-// tables and each bank serves exactly two lanes.  One v_perm_b32 per lookup
-// builds the address 0x10000 | byte << 8 | (64*table + 4*copy).
-
-constexpr uint32_t kTeBase = 0x10000u;
-
-struct LaneK {
-    uint32_t sel[4];          // v_perm selectors: byte u_r of the state word into bits 8..15
-    uint32_t off[4];          // 0x10000 | 64*u_r + 4*copy
-    uint32_t rot;             // alignbit shift for rotl by 8g
-    uint32_t fsel01, fsel23;  // last round: v_perm selectors of the S-box bytes
-};
-
-__device__ __forceinline__ LaneK lane_constants(int lane)
-{
-    LaneK k;
-    const uint32_t g = (uint32_t)(lane >> 4) & 3u, copy = (uint32_t)lane & 15u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t u = ((uint32_t)r + g) & 3u;
-        k.sel[r] = 0x0c020000u | ((4u + u) << 8);
-        k.off[r] = kTeBase | (u * 64u + copy * 4u);
-    }
-    {
-        const uint32_t u0 = g & 3u, u1 = (1u + g) & 3u, u2 = (2u + g) & 3u, u3 = (3u + g) & 3u;
-        // S(x) sits in byte (u+1)&3 of table u
-        k.fsel01 = ((u0 + 1u) & 3u) | ((4u + ((u1 + 1u) & 3u)) << 8) | 0x0c0c0000u;
-        k.fsel23 = 0x00000c0cu | (((u2 + 1u) & 3u) << 16) | ((4u + ((u3 + 1u) & 3u)) << 24);
-    }
-    k.rot = (32u - 8u * g) & 31u;
-    return k;
-}
-
-__device__ __forceinline__ uint32_t lds_word(const uint8_t *lds, uint32_t byte_addr)
-{
-    return *reinterpret_cast<const uint32_t *>(lds + byte_addr);
-}
 
 __device__ __forceinline__ uint32_t rotr_by(uint32_t x, uint32_t n) { return __builtin_amdgcn_alignbit(x, x, n); }
 
@@ -665,116 +639,80 @@ __device__ __forceinline__ uint32_t rotr_by(uint32_t x, uint32_t n) { return __b
 #define B2(x) (((x) >> 16) & 0xffu)
 #define B3(x) ((x) >> 24)
 
-// unrotated T_t[x] (uniform reads, used for the per-tile round-1 constants)
-__device__ __forceinline__ uint32_t te_u(const uint8_t *lds, uint32_t t, uint32_t x)
-{
-    return lds_word(lds, kTeBase + x * 256u + t * 64u);
-}
+// The T-tables in LDS as a lane sees them; ROT: 16 copies and a rotated state.
+template <bool ROT>
+struct Tables;
 
-#define LK(r, w) lds_word(lds, __builtin_amdgcn_perm((w), lk.off[r], lk.sel[r]))
+template <>
+struct Tables<false> {
+    const uint8_t *lds;
+    uint32_t lo, hi;  // 4 * copy, 0x10000 | 4 * copy
 
-struct AesCtx {
-    uint32_t u0, u1, u2, u3;  // round-1 columns with the 12 IV bytes folded in (unrotated, uniform)
-    uint32_t rk3;             // round key 0, column 3
-};
-
-// Rounds R0..NR of AES on a lane-rotated state (rounds R0..NR-1 with the
-// T-tables, the last with S-box bytes only).
-template <int R0, int NR>
-__device__ __forceinline__ u32x4 aes_rounds(uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3,
-                                            const CONST_AS uint32_t *rk, const uint8_t *lds, const LaneK &lk)
-{
-    // fully unrolled: the scheduler issues each round's lookups as soon as
-    // their addresses exist, across round boundaries
-#pragma unroll
-    for (int r = R0; r < NR; ++r) {
-        const uint32_t k0 = rotr_by(rk[4 * r + 0], lk.rot), k1 = rotr_by(rk[4 * r + 1], lk.rot);
-        const uint32_t k2 = rotr_by(rk[4 * r + 2], lk.rot), k3 = rotr_by(rk[4 * r + 3], lk.rot);
-        const uint32_t t0 = xor3(xor3(LK(0, s0), LK(1, s1), LK(2, s2)), LK(3, s3), k0);
-        const uint32_t t1 = xor3(xor3(LK(0, s1), LK(1, s2), LK(2, s3)), LK(3, s0), k1);
-        const uint32_t t2 = xor3(xor3(LK(0, s2), LK(1, s3), LK(2, s0)), LK(3, s1), k2);
-        const uint32_t t3 = xor3(xor3(LK(0, s3), LK(1, s0), LK(2, s1)), LK(3, s2), k3);
-        s0 = t0;
-        s1 = t1;
-        s2 = t2;
-        s3 = t3;
+    __device__ __forceinline__ Tables(const uint8_t *l, int lane) : lds(l)
+    {
+        lo = 4u * ((uint32_t)lane & 31u);
+        hi = 0x10000u | lo;
     }
-    // last round: the round tables hold S(x) in byte (u+1)&3; two v_perm
-    // pick the four S-box bytes into their unrotated positions, so the key
-    // is added unrotated and the result needs no rotation back
-    const uint32_t o0 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(LK(1, s1), LK(0, s0), lk.fsel01),
-                                                    __builtin_amdgcn_perm(LK(3, s3), LK(2, s2), lk.fsel23), rk[4 * NR + 0], 0x56);
-    const uint32_t o1 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(LK(1, s2), LK(0, s1), lk.fsel01),
-                                                    __builtin_amdgcn_perm(LK(3, s0), LK(2, s3), lk.fsel23), rk[4 * NR + 1], 0x56);
-    const uint32_t o2 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(LK(1, s3), LK(0, s2), lk.fsel01),
-                                                    __builtin_amdgcn_perm(LK(3, s1), LK(2, s0), lk.fsel23), rk[4 * NR + 2], 0x56);
-    const uint32_t o3 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_perm(LK(1, s0), LK(0, s3), lk.fsel01),
-                                                    __builtin_amdgcn_perm(LK(3, s2), LK(2, s1), lk.fsel23), rk[4 * NR + 3], 0x56);
-    return u32x4{o0, o1, o2, o3};
-}
-
-// Keystream block for counter value `ctr` (big-endian in bytes 12..15).
-// Only column 3 of the counter block varies, so round 1 needs four table
-// lookups instead of sixteen (counter-mode caching).
-template <int NR>
-__device__ __forceinline__ u32x4 aes_ctr(uint32_t ctr, const AesCtx &c, const CONST_AS uint32_t *rk,
-                                         const uint8_t *lds, const LaneK &lk)
-{
-    const uint32_t v = bswap32(ctr) ^ c.rk3;
-    const uint32_t w3 = rotr_by(v, lk.rot);  // rotl(v, 8g)
-    const uint32_t s0 = rotr_by(c.u0, lk.rot) ^ LK(3, w3);
-    const uint32_t s1 = rotr_by(c.u1, lk.rot) ^ LK(2, w3);
-    const uint32_t s2 = rotr_by(c.u2, lk.rot) ^ LK(1, w3);
-    const uint32_t s3 = rotr_by(c.u3, lk.rot) ^ LK(0, w3);
-    return aes_rounds<2, NR>(s0, s1, s2, s3, rk, lds, lk);
-}
-
-// Counter-mode caching through round 2.  With counter bytes 12..14 fixed,
-// round 1 leaves state columns 1..3 fixed and only column 0 depends on the
-// low counter byte; every round-2 output column then takes exactly one
-// table entry indexed by a byte of that column, XOR a word that depends only
-// on the upper 24 counter bits.  Ctr2 holds those four words (unrotated).
-struct Ctr2 {
-    uint32_t v0, v1, v2, v3;
+    // T_R[byte R of w]
+    template <int R>
+    __device__ __forceinline__ uint32_t look(uint32_t w) const
+    {
+        const uint32_t a = __builtin_amdgcn_perm(w, (R & 2) ? hi : lo, 0x0c020000u | ((4u + R) << 8));
+        return *reinterpret_cast<const uint32_t *>(lds + 128 * (R & 1) + a);
+    }
+    // T_t[x] itself
+    __device__ __forceinline__ uint32_t entry(int t, uint32_t x) const
+    {
+        return *reinterpret_cast<const uint32_t *>(lds + 0x10000 * (t >> 1) + 128 * (t & 1) + (x << 8 | lo));
+    }
+    __device__ __forceinline__ uint32_t rot(uint32_t x) const { return x; }
+    // the S-box bytes of rows 0, 1 (2, 3), unrotated: S(x) sits in byte (t + 1) & 3 of table t's entry
+    __device__ __forceinline__ uint32_t last01(uint32_t a, uint32_t b) const
+    {
+        return __builtin_amdgcn_perm(b, a, 0x0c0c0601u);
+    }
+    __device__ __forceinline__ uint32_t last23(uint32_t c, uint32_t d) const
+    {
+        return __builtin_amdgcn_perm(d, c, 0x04030c0cu);
+    }
 };
 
-// T_t[x] read through the scalar cache (uniform x): TE0 at word 0, TE1..TE3
-// from word kTe1Off of the table block
-__device__ __forceinline__ uint32_t te_s(const CONST_AS uint32_t *te, int t, uint32_t x)
-{
-    return t == 0 ? te[x] : te[kTe1Off + 256 * (t - 1) + x];
-}
+template <>
+struct Tables<true> {
+    const uint8_t *lds;
+    uint32_t sel[4];          // v_perm selectors: byte u_r of the state word into bits 8..15
+    uint32_t off[4];          // 0x10000 | 64*u_r + 4*copy
+    uint32_t sh;              // alignbit shift for rotl by 8g
+    uint32_t fsel01, fsel23;  // last round: v_perm selectors of the S-box bytes
 
-// the four round-2 words for upper counter bits `hi` (wave-uniform)
-__device__ __forceinline__ Ctr2 ctr_round2(uint32_t hi, const AesCtx &c, const CONST_AS uint32_t *rk,
-                                           const CONST_AS uint32_t *te)
-{
-    const uint32_t v = bswap32(hi << 8) ^ c.rk3;  // column 3 of the first state (byte 3 unused)
-    const uint32_t u1 = c.u1 ^ te_s(te, 2, B2(v));
-    const uint32_t u2 = c.u2 ^ te_s(te, 1, B1(v));
-    const uint32_t u3 = c.u3 ^ te_s(te, 0, B0(v));
-    Ctr2 q;
-    q.v0 = te_s(te, 1, B1(u1)) ^ te_s(te, 2, B2(u2)) ^ te_s(te, 3, B3(u3)) ^ rk[8];
-    q.v1 = te_s(te, 0, B0(u1)) ^ te_s(te, 1, B1(u2)) ^ te_s(te, 2, B2(u3)) ^ rk[9];
-    q.v2 = te_s(te, 0, B0(u2)) ^ te_s(te, 1, B1(u3)) ^ te_s(te, 3, B3(u1)) ^ rk[10];
-    q.v3 = te_s(te, 0, B0(u3)) ^ te_s(te, 2, B2(u1)) ^ te_s(te, 3, B3(u2)) ^ rk[11];
-    return q;
-}
-
-// Keystream block for `ctr` whose upper 24 bits match `q`: one lookup in
-// round 1 and four in round 2 instead of four and sixteen.
-template <int NR>
-__device__ __forceinline__ u32x4 aes_ctr2(uint32_t ctr, const Ctr2 &q, const AesCtx &c,
-                                          const CONST_AS uint32_t *rk, const uint8_t *lds, const LaneK &lk)
-{
-    const uint32_t w3 = rotr_by((ctr << 24) ^ c.rk3, lk.rot);  // byte 3: low counter byte ^ key
-    const uint32_t x0 = rotr_by(c.u0, lk.rot) ^ LK(3, w3);      // round-1 column 0
-    const uint32_t s0 = rotr_by(q.v0, lk.rot) ^ LK(0, x0);
-    const uint32_t s1 = rotr_by(q.v1, lk.rot) ^ LK(3, x0);
-    const uint32_t s2 = rotr_by(q.v2, lk.rot) ^ LK(2, x0);
-    const uint32_t s3 = rotr_by(q.v3, lk.rot) ^ LK(1, x0);
-    return aes_rounds<3, NR>(s0, s1, s2, s3, rk, lds, lk);
-}
+    __device__ __forceinline__ Tables(const uint8_t *l, int lane) : lds(l)
+    {
+        const uint32_t g = (uint32_t)(lane >> 4) & 3u, copy = (uint32_t)lane & 15u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t u = ((uint32_t)r + g) & 3u;
+            sel[r] = 0x0c020000u | ((4u + u) << 8);
+            off[r] = 0x10000u | (u * 64u + copy * 4u);
+        }
+        const uint32_t u0 = g & 3u, u1 = (1u + g) & 3u, u2 = (2u + g) & 3u, u3 = (3u + g) & 3u;
+        // S(x) sits in byte (u+1)&3 of table u
+        fsel01 = ((u0 + 1u) & 3u) | ((4u + ((u1 + 1u) & 3u)) << 8) | 0x0c0c0000u;
+        fsel23 = 0x00000c0cu | (((u2 + 1u) & 3u) << 16) | ((4u + ((u3 + 1u) & 3u)) << 24);
+        sh = (32u - 8u * g) & 31u;
+    }
+    template <int R>
+    __device__ __forceinline__ uint32_t look(uint32_t w) const
+    {
+        return *reinterpret_cast<const uint32_t *>(lds + __builtin_amdgcn_perm(w, off[R], sel[R]));
+    }
+    __device__ __forceinline__ uint32_t entry(int t, uint32_t x) const
+    {
+        return *reinterpret_cast<const uint32_t *>(lds + 0x10000 + 64 * t + (x << 8 | ((off[0] & 63u))));
+    }
+    __device__ __forceinline__ uint32_t rot(uint32_t x) const { return rotr_by(x, sh); }
+    __device__ __forceinline__ uint32_t last01(uint32_t a, uint32_t b) const { return __builtin_amdgcn_perm(b, a, fsel01); }
+    __device__ __forceinline__ uint32_t last23(uint32_t c, uint32_t d) const { return __builtin_amdgcn_perm(d, c, fsel23); }
+};
 
 // Per-lane constants of the GHASH lookup schedule (q = lane & 15):
 // pos[m] byte t = 16 * ((4m + t + q) & 15), the bank-group offset of lookup
@@ -812,36 +750,233 @@ __device__ __forceinline__ u32x4 rot_bytes_lane(u32x4 a, const GhK &g)
                  __builtin_amdgcn_alignbit(b.w, b.z, g.sh), __builtin_amdgcn_alignbit(b.x, b.w, g.sh)};
 }
 
-// a * H^64 + x with the entry-major byte-position table at LDS offset 0
-// (16 lookups of 16 bytes, conflict-free across each 16-lane group)
+// The Horner step a <- a * H^64 ^ x with the entry-major byte-position table at
+// LDS offset 0: 16 lookups of 16 bytes, conflict-free across each 16-lane
+// group, in four groups, so that they can be issued between the rounds of
+// another row's AES.
+struct GhashStep {
+    uint32_t w[4];
+    u32x4 acc, e[4];
+
+    __device__ __forceinline__ void start(u32x4 a, u32x4 x, const GhK &g)
+    {
+        const u32x4 r = rot_bytes_lane(a, g);
+        w[0] = r.x, w[1] = r.y, w[2] = r.z, w[3] = r.w;
+        acc = x;
+    }
+    template <int G>
+    __device__ __forceinline__ void issue(const uint8_t *__restrict__ lds, const GhK &g)
+    {
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            // address = 256 * (byte 4G + q of the rotated value) + 16 * position
+            const uint32_t at = __builtin_amdgcn_perm(w[G], g.pos[G], 0x0c0c0000u | ((4u + q) << 8) | q);
+            e[q] = *reinterpret_cast<const u32x4 *>(lds + at);
+        }
+    }
+    __device__ __forceinline__ void absorb() { acc = xor3v(xor3v(e[0], e[1], e[2]), e[3], acc); }
+};
+
 __device__ __forceinline__ u32x4 ghash_mul8(u32x4 a, u32x4 x, const uint8_t *__restrict__ lds, const GhK &g)
 {
-    const u32x4 r = rot_bytes_lane(a, g);
-    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-    u32x4 acc = x;
-    // two halves of eight lookups, so at most 32 result registers are live
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        u32x4 e[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int j = 8 * h + q;
-            // address = 256 * (byte j of r) + 16 * position
-            const uint32_t sel = 0x0c0c0000u | ((4u + (uint32_t)(j & 3)) << 8) | (uint32_t)(j & 3);
-            const uint32_t addr = __builtin_amdgcn_perm(w[j >> 2], g.pos[j >> 2], sel);
-            e[q] = *reinterpret_cast<const u32x4 *>(lds + addr);
-        }
-        acc = xor3v(xor3v(e[0], e[1], e[2]), xor3v(e[3], e[4], e[5]), xor3v(e[6], e[7], acc));
-    }
-    return acc;
+    GhashStep s, t;  // two groups in flight
+    s.start(a, x, g);
+    t.start(a, u32x4{0, 0, 0, 0}, g);
+    s.issue<0>(lds, g);
+    t.issue<1>(lds, g);
+    s.absorb();
+    s.issue<2>(lds, g);
+    t.absorb();
+    t.issue<3>(lds, g);
+    s.absorb();
+    t.absorb();
+    return s.acc ^ t.acc;
 }
 
-// zero-padded load of block `blk` of a buffer of `total` bytes
-__device__ __forceinline__ u32x4 load_block_partial(const uint8_t *p, uint64_t blk, uint64_t total)
+// Keeps the compiler's scheduler from moving anything across this point.
+#define STAGE_END __builtin_amdgcn_sched_barrier(0)
+
+// Rounds 3..NR of AES on the state columns after round 2.
+//
+// A round's sixteen lookups are issued by source column, and output column j
+// is formed as soon as its last lookup (source column 3) is back, its own four
+// lookups of the next round following at once, so that a wave always has
+// lookups in flight.  Left to itself the compiler issues three to eight and
+// waits for all of them, which left the LDS idle a third of the time in
+// counter mode.
+//
+// With GH the GHASH step of the row before runs between the rounds: a group of
+// its lookups after each of the first four rounds, absorbed a round later.
+template <int NR, bool GH, typename TAB>
+__device__ __forceinline__ u32x4 aes_rounds(u32x4 s, const CONST_AS uint32_t *rk, const TAB &tab, GhashStep &gs,
+                                            const GhK &gk)
+{
+    uint32_t v[4][4];  // v[j][i]: the lookup of output column j in source column i, state row (i - j) & 3
+#define ISSUE0(d, w) d[0][0] = tab.template look<0>(w), d[3][0] = tab.template look<1>(w), d[2][0] = tab.template look<2>(w), d[1][0] = tab.template look<3>(w)
+#define ISSUE1(d, w) d[1][1] = tab.template look<0>(w), d[0][1] = tab.template look<1>(w), d[3][1] = tab.template look<2>(w), d[2][1] = tab.template look<3>(w)
+#define ISSUE2(d, w) d[2][2] = tab.template look<0>(w), d[1][2] = tab.template look<1>(w), d[0][2] = tab.template look<2>(w), d[3][2] = tab.template look<3>(w)
+#define ISSUE3(d, w) d[0][3] = tab.template look<3>(w), d[1][3] = tab.template look<2>(w), d[2][3] = tab.template look<1>(w), d[3][3] = tab.template look<0>(w)
+    ISSUE0(v, s.x);
+    ISSUE1(v, s.y);
+    ISSUE2(v, s.z);
+    ISSUE3(v, s.w);
+    STAGE_END;
+#pragma unroll
+    for (int r = 3; r < NR; ++r) {
+        uint32_t n[4][4];
+        const uint32_t p0 = xor3(v[0][0], v[0][1], v[0][2]), p1 = xor3(v[1][0], v[1][1], v[1][2]);
+        const uint32_t p2 = xor3(v[2][0], v[2][1], v[2][2]), p3 = xor3(v[3][0], v[3][1], v[3][2]);
+        const uint32_t k0 = tab.rot(rk[4 * r + 0]), k1 = tab.rot(rk[4 * r + 1]);
+        const uint32_t k2 = tab.rot(rk[4 * r + 2]), k3 = tab.rot(rk[4 * r + 3]);
+        STAGE_END;
+        const uint32_t t0 = xor3(p0, v[0][3], k0);
+        ISSUE0(n, t0);
+        STAGE_END;
+        const uint32_t t1 = xor3(p1, v[1][3], k1);
+        ISSUE1(n, t1);
+        STAGE_END;
+        const uint32_t t2 = xor3(p2, v[2][3], k2);
+        ISSUE2(n, t2);
+        STAGE_END;
+        const uint32_t t3 = xor3(p3, v[3][3], k3);
+        ISSUE3(n, t3);
+        STAGE_END;
+        if (GH && r >= 4 && r <= 7)
+            gs.absorb();
+        if (GH && r == 3)
+            gs.template issue<0>(tab.lds, gk);
+        if (GH && r == 4)
+            gs.template issue<1>(tab.lds, gk);
+        if (GH && r == 5)
+            gs.template issue<2>(tab.lds, gk);
+        if (GH && r == 6)
+            gs.template issue<3>(tab.lds, gk);
+        if (GH && r <= 7)
+            STAGE_END;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                v[i][j] = n[i][j];
+    }
+    // last round: two v_perm pick a column's four S-box bytes into their
+    // unrotated places, so the key is added as it is
+    u32x4 o;
+#define LAST(j, k)                                                                                                     \
+    __builtin_amdgcn_bitop3_b32(tab.last01(v[j][j], v[j][((j) + 1) & 3]), tab.last23(v[j][((j) + 2) & 3], v[j][((j) + 3) & 3]), k, 0x56)
+    o.x = LAST(0, rk[4 * NR + 0]);
+    o.y = LAST(1, rk[4 * NR + 1]);
+    o.z = LAST(2, rk[4 * NR + 2]);
+    o.w = LAST(3, rk[4 * NR + 3]);
+#undef LAST
+    return o;
+}
+
+// T_t[x] read through the scalar cache (uniform x): TE0 at word 0, TE1..TE3
+// from word kTe1Off of the table block
+__device__ __forceinline__ uint32_t te_s(const CONST_AS uint32_t *te, int t, uint32_t x)
+{
+    return t == 0 ? te[x] : te[kTe1Off + 256 * (t - 1) + x];
+}
+
+// The counter block with its counter dword left out, after round 1: column i
+// of round 1 is u[i] XOR one table entry of a counter byte.  GCM's big-endian
+// counter is dword 3 (its low byte in state row 3), GCM-SIV's little-endian
+// counter dword 0 (low byte in row 0); both low bytes reach column 0 of round 1.
+template <bool SIV>
+struct CtrBlock {
+    uint32_t u0, u1, u2, u3;
+    uint32_t k;  // the counter dword's word of round key 0
+
+    __device__ __forceinline__ void init(uint32_t w1, uint32_t w2, uint32_t w3, const CONST_AS uint32_t *rk,
+                                         const CONST_AS uint32_t *te)
+    {
+        if (SIV) {  // w1..w3: dwords 1..3
+            const uint32_t s1 = w1 ^ rk[1], s2 = w2 ^ rk[2], s3 = w3 ^ rk[3];
+            u0 = te_s(te, 1, B1(s1)) ^ te_s(te, 2, B2(s2)) ^ te_s(te, 3, B3(s3)) ^ rk[4];
+            u1 = te_s(te, 0, B0(s1)) ^ te_s(te, 1, B1(s2)) ^ te_s(te, 2, B2(s3)) ^ rk[5];
+            u2 = te_s(te, 0, B0(s2)) ^ te_s(te, 1, B1(s3)) ^ te_s(te, 3, B3(s1)) ^ rk[6];
+            u3 = te_s(te, 0, B0(s3)) ^ te_s(te, 2, B2(s1)) ^ te_s(te, 3, B3(s2)) ^ rk[7];
+            k = rk[0];
+        } else {  // w1..w3: dwords 0..2
+            const uint32_t s0 = w1 ^ rk[0], s1 = w2 ^ rk[1], s2 = w3 ^ rk[2];
+            u0 = te_s(te, 0, B0(s0)) ^ te_s(te, 1, B1(s1)) ^ te_s(te, 2, B2(s2)) ^ rk[4];
+            u1 = te_s(te, 0, B0(s1)) ^ te_s(te, 1, B1(s2)) ^ te_s(te, 3, B3(s0)) ^ rk[5];
+            u2 = te_s(te, 0, B0(s2)) ^ te_s(te, 2, B2(s0)) ^ te_s(te, 3, B3(s1)) ^ rk[6];
+            u3 = te_s(te, 1, B1(s0)) ^ te_s(te, 2, B2(s1)) ^ te_s(te, 3, B3(s2)) ^ rk[7];
+            k = rk[3];
+        }
+    }
+
+    // Round-2 words of counters whose low byte is `low`: column 0 of round 1 is
+    // the only one that byte reaches, and it does not depend on the upper bits,
+    // so the four entries that round 2 reads of it are one 16-byte word a low
+    // byte and message.
+    template <typename TAB>
+    __device__ __forceinline__ u32x4 low_words(uint32_t low, const TAB &tab) const
+    {
+        const uint32_t x0 = u0 ^ (SIV ? tab.entry(0, (low ^ k) & 0xffu) : tab.entry(3, low ^ B3(k)));
+        return u32x4{tab.entry(0, B0(x0)), tab.entry(3, B3(x0)), tab.entry(2, B2(x0)), tab.entry(1, B1(x0))};
+    }
+
+    // the rest of the state after round 2, for upper counter bits `hi` (uniform)
+    __device__ __forceinline__ u32x4 high_words(uint32_t hi, const CONST_AS uint32_t *rk,
+                                                const CONST_AS uint32_t *te) const
+    {
+        const uint32_t v = SIV ? (hi << 8) ^ k : bswap32(hi << 8) ^ k;
+        const uint32_t a1 = u1 ^ (SIV ? te_s(te, 3, B3(v)) : te_s(te, 2, B2(v)));
+        const uint32_t a2 = u2 ^ (SIV ? te_s(te, 2, B2(v)) : te_s(te, 1, B1(v)));
+        const uint32_t a3 = u3 ^ (SIV ? te_s(te, 1, B1(v)) : te_s(te, 0, B0(v)));
+        return u32x4{te_s(te, 1, B1(a1)) ^ te_s(te, 2, B2(a2)) ^ te_s(te, 3, B3(a3)) ^ rk[8],
+                     te_s(te, 0, B0(a1)) ^ te_s(te, 1, B1(a2)) ^ te_s(te, 2, B2(a3)) ^ rk[9],
+                     te_s(te, 0, B0(a2)) ^ te_s(te, 1, B1(a3)) ^ te_s(te, 3, B3(a1)) ^ rk[10],
+                     te_s(te, 0, B0(a3)) ^ te_s(te, 2, B2(a1)) ^ te_s(te, 3, B3(a2)) ^ rk[11]};
+    }
+};
+
+// a * c_l for this lane's fixed multiplier c_l = H^(63 - lane), through its
+// 4-bit window table in LDS (entry (v, l) = (v * c_l) mod P at
+// win + 16 * (64 v + l)): a comb over the eight nibble positions of the
+// four words of a, 256-bit accumulate with word-aligned XORs, one fold at the
+// end.  32 conflict-free ds_read_b128 (16 consecutive lanes read 16
+// different bank groups) and about 300 VALU instructions.
+__device__ __forceinline__ u32x4 gf_mul_lanewin(u32x4 a, const uint8_t *__restrict__ wins, int lane)
+{
+    const uint32_t am[4] = {a.x, a.y, a.z, a.w};
+    const P128 pa = mem_to_poly(am);
+    const uint32_t aw[4] = {(uint32_t)pa.lo, (uint32_t)(pa.lo >> 32), (uint32_t)pa.hi, (uint32_t)(pa.hi >> 32)};
+    const uint8_t *win = wins + 16u * (uint32_t)lane;
+    uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int q = 7; q >= 0; --q) {
+#pragma unroll
+        for (int k = 7; k > 0; --k)
+            acc[k] = __builtin_amdgcn_alignbit(acc[k], acc[k - 1], 28);  // acc <<= 4
+        acc[0] <<= 4;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t v = (aw[w] >> (4 * q)) & 15u;
+            const u32x4 t = *reinterpret_cast<const u32x4 *>(win + 1024u * v);
+            acc[w] ^= t.x;
+            acc[w + 1] ^= t.y;
+            acc[w + 2] ^= t.z;
+            acc[w + 3] ^= t.w;
+        }
+    }
+    const P128 r = poly_reduce((uint64_t)acc[0] | ((uint64_t)acc[1] << 32), (uint64_t)acc[2] | ((uint64_t)acc[3] << 32),
+                               (uint64_t)acc[4] | ((uint64_t)acc[5] << 32), (uint64_t)acc[6] | ((uint64_t)acc[7] << 32));
+    return poly_to_mem(r);
+}
+
+// Zero-padded load of block `blk` of a buffer of `total` bytes.  (All buffers
+// are addressed in the global address space: a flat access anywhere in the row
+// loop counts as an LDS access too, and the compiler then drains the LDS queue
+// at every wait of the loop instead of waiting for the lookups it needs.)
+__device__ __forceinline__ u32x4 load_block_partial(const GLOBAL_AS uint8_t *p, uint64_t blk, uint64_t total)
 {
     const uint64_t off = blk * 16;
     if (off + 16 <= total)
-        return *reinterpret_cast<const u32x4 *>(p + off);
+        return *reinterpret_cast<const GLOBAL_AS u32x4 *>(p + off);
     uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
     for (uint64_t k = off; k < total; ++k) {
         const uint32_t b = (uint32_t)p[k] << (8 * ((k - off) & 3));
@@ -868,11 +1003,11 @@ __device__ __forceinline__ u32x4 mask_block(u32x4 v, uint64_t blk, uint64_t tota
     return u32x4{keep_bytes(v.x, nb), keep_bytes(v.y, nb - 4), keep_bytes(v.z, nb - 8), keep_bytes(v.w, nb - 12)};
 }
 
-__device__ __forceinline__ void store_block_partial(uint8_t *p, uint64_t blk, uint64_t total, u32x4 v)
+__device__ __forceinline__ void store_block_partial(GLOBAL_AS uint8_t *p, uint64_t blk, uint64_t total, u32x4 v)
 {
     const uint64_t off = blk * 16;
     if (off + 16 <= total) {
-        *reinterpret_cast<u32x4 *>(p + off) = v;
+        *reinterpret_cast<GLOBAL_AS u32x4 *>(p + off) = v;
         return;
     }
     for (uint64_t k = off; k < total; ++k) {
@@ -882,255 +1017,265 @@ __device__ __forceinline__ void store_block_partial(uint8_t *p, uint64_t blk, ui
     }
 }
 
-// LDS byte offset of the lane fix-up window table (after the GHASH table and
-// the T-tables)
-constexpr uint32_t kWinBase = 0x20000u;
+__device__ __forceinline__ u32x4 rev_block(u32x4 x) { return u32x4{bswap32(x.w), bswap32(x.z), bswap32(x.y), bswap32(x.x)}; }
 
-// a * c_l for this lane's fixed multiplier c_l = H^(63 - lane), through its
-// 4-bit window table in LDS (entry (v, l) = (v * c_l) mod P at
-// kWinBase + 16 * (64 v + l)): a comb over the eight nibble positions of the
-// four words of a, 256-bit accumulate with word-aligned XORs, one fold at the
-// end.  32 conflict-free ds_read_b128 (16 consecutive lanes read 16
-// different bank groups) and about 300 VALU instructions.
-__device__ __forceinline__ u32x4 gf_mul_lanewin(u32x4 a, const uint8_t *__restrict__ lds, int lane)
+// What a tile kernel does: GCM; counter mode only; GCM-SIV's POLYVAL alone
+// (encrypt, first pass), its counter mode alone (second pass, once the tag is
+// known), and its counter mode with the POLYVAL of the output (decrypt-verify).
+constexpr int kGcm = 0, kCtr = 1, kSivHash = 2, kSivCtr = 3, kSivDec = 4;
+
+template <int KIND>
+struct Kind {
+    static constexpr bool gh = KIND == kGcm || KIND == kSivHash || KIND == kSivDec;
+    static constexpr bool aes = KIND != kSivHash;
+    static constexpr bool siv = KIND == kSivHash || KIND == kSivCtr || KIND == kSivDec;
+    using tables = Tables<gh>;
+    // LDS bytes: fix-up windows (GHASH passes), round-2 words, total
+    static constexpr uint32_t windows = 0x20000u, round2 = gh ? 0x24000u : 0x20000u;
+    static constexpr uint32_t lds = round2 + 0x1000u;
+};
+
+// the message's counter block; c1: the counter value of data block 0, cj0: of J0
+template <int KIND>
+__device__ __forceinline__ void message_counter(const CONST_AS MsgDesc *dp, const CONST_AS uint32_t *te,
+                                                CtrBlock<Kind<KIND>::siv> &c, uint32_t &c1, uint32_t &cj0)
 {
-    const uint32_t am[4] = {a.x, a.y, a.z, a.w};
-    const P128 pa = mem_to_poly(am);
-    const uint32_t aw[4] = {(uint32_t)pa.lo, (uint32_t)(pa.lo >> 32), (uint32_t)pa.hi, (uint32_t)(pa.hi >> 32)};
-    const uint8_t *win = lds + kWinBase + 16u * (uint32_t)lane;
-    uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int q = 7; q >= 0; --q) {
-#pragma unroll
-        for (int k = 7; k > 0; --k)
-            acc[k] = __builtin_amdgcn_alignbit(acc[k], acc[k - 1], 28);  // acc <<= 4
-        acc[0] <<= 4;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const uint32_t v = (aw[w] >> (4 * q)) & 15u;
-            const u32x4 t = *reinterpret_cast<const u32x4 *>(win + 1024u * v);
-            acc[w] ^= t.x;
-            acc[w + 1] ^= t.y;
-            acc[w + 2] ^= t.z;
-            acc[w + 3] ^= t.w;
-        }
+    const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
+    const uint64_t jaddr = dp->j0;
+    const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
+    if (Kind<KIND>::siv) {  // the counter block is the tag with its top bit set
+        c.init(jw[1], jw[2], jw[3], rk, te);
+        c1 = cj0 = jw[0];
+    } else if (jaddr) {  // J0 computed on the device from an IV that is not 96 bits
+        c.init(jw[0], jw[1], jw[2], rk, te);
+        cj0 = bswap32(jw[3]);
+        c1 = cj0 + 1u + dp->ctr_off;
+    } else {  // J0 = IV || 0^31 || 1
+        c.init(dp->iv[0], dp->iv[1], dp->iv[2], rk, te);
+        cj0 = 1u;
+        c1 = 2u + dp->ctr_off;
     }
-    const P128 r = poly_reduce((uint64_t)acc[0] | ((uint64_t)acc[1] << 32), (uint64_t)acc[2] | ((uint64_t)acc[3] << 32),
-                               (uint64_t)acc[4] | ((uint64_t)acc[5] << 32), (uint64_t)acc[6] | ((uint64_t)acc[7] << 32));
-    return poly_to_mem(r);
 }
 
-// One wave processes wave tile t of message d: rows of 64 consecutive
-// blocks, lane l on block 64*r + l, so every load/store instruction moves one
-// contiguous KiB.  a_l = sum_r X_(64r+l) * (H^64)^(R-1-r) by Horner; then
-// p_t = sum_l a_l * H^(63-l) is formed by exponent-bit fix-ups and an XOR
-// across the wave.  With GH false the tile is counter mode only (no GHASH,
-// no partial).  AADROWS adds a GHASH-only pass over rows of whole AAD blocks,
-// J0DEV reads J0 from device memory (IVs other than 96 bits) instead of
-// forming IV || 0^31 || 1.  A streamed segment's counters start d.ctr_off
-// blocks after J0 + 1 in every variant.  Both options cost the main loop its
-// batching of LDS reads (a run-time counter base, or the extra loop, leaves
-// it fewer registers), so each is compiled only into kernel variants of its
-// own.
-template <int NR, bool GH, bool AADROWS, bool J0DEV>
-__device__ void wave_tile(const MsgDesc &d, uint64_t t, const uint8_t *__restrict__ lds, const LaneK &lk,
-                          const GhK &gk, const uint32_t *__restrict__ te0g, u32x4 *__restrict__ partials)
+// One wave processes wave tile t of a message: rows of 64 consecutive blocks,
+// lane l on block 64 r + l, so every load and store moves one contiguous KiB.
+// Rows [fa, fb) hold 64 whole data blocks and rows [aa, ab) 64 whole AAD
+// blocks; the others (zero padding, partial blocks, the length block) load and
+// store lane by lane.  The wave of tile 0 runs one row ahead of its tile for
+// E_K(J0), the keystream block of J0's own counter value, and leaves it after
+// the message's partials for the combine.  A streamed segment's
+// counters start ctr_off blocks after J0 + 1.
+// a_l = sum_r X_(64r+l) * (H^64)^(R-1-r) by Horner on lane l, then the tile's
+// value is sum_l a_l * H^(63-l).  GCM-SIV hashes byte-reversed blocks.
+template <int NR, int KIND>
+__device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t, const uint8_t *__restrict__ lds,
+                                          const typename Kind<KIND>::tables &tab, const GhK &gk,
+                                          const CONST_AS uint32_t *te, u32x4 *__restrict__ partials)
 {
+    constexpr bool GH = Kind<KIND>::gh, SIV = Kind<KIND>::siv, AES = Kind<KIND>::aes;
     const int lane = threadIdx.x & 63;
-    const CONST_AS uint32_t *te = cptr<uint32_t>(te0g);
-    const CONST_AS uint32_t *rk_base = cptr<uint32_t>(reinterpret_cast<const void *>(d.slot));
-    const CONST_AS uint32_t *rk = rk_base;
-    // J0 = IV || 0^31 || 1, or a J0 computed from a longer or shorter IV;
-    // E_K(J0) uses J0's own counter value cj0, data block j (of a streamed
-    // segment that follows d.ctr_off earlier blocks) counter value c1 + j
-    uint32_t iv0 = d.iv[0], iv1 = d.iv[1], iv2 = d.iv[2], cj0 = 1u;
-    if (J0DEV) {
-        const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(d.j0));
-        iv0 = jw[0];
-        iv1 = jw[1];
-        iv2 = jw[2];
-        cj0 = bswap32(jw[3]);
-    }
-    const uint32_t c1 = cj0 + 1u + d.ctr_off;
-    AesCtx c;
-    {
-        const uint32_t s0 = iv0 ^ rk[0], s1 = iv1 ^ rk[1], s2 = iv2 ^ rk[2];
-        c.u0 = uniform(te_u(lds, 0, B0(s0)) ^ te_u(lds, 1, B1(s1)) ^ te_u(lds, 2, B2(s2)) ^ rk[4]);
-        c.u1 = uniform(te_u(lds, 0, B0(s1)) ^ te_u(lds, 1, B1(s2)) ^ te_u(lds, 3, B3(s0)) ^ rk[5]);
-        c.u2 = uniform(te_u(lds, 0, B0(s2)) ^ te_u(lds, 2, B2(s0)) ^ te_u(lds, 3, B3(s1)) ^ rk[6]);
-        c.u3 = uniform(te_u(lds, 1, B1(s0)) ^ te_u(lds, 2, B2(s1)) ^ te_u(lds, 3, B3(s2)) ^ rk[7]);
-        c.rk3 = rk[3];
-    }
+    const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
+    CtrBlock<SIV> c;
+    uint32_t c1 = 0, cj0 = 0;
+    if (AES)
+        message_counter<KIND>(dp, te, c, c1, cj0);
 
-    if (GH && t == 0) {
-        // E_K(J0) is the keystream block of counter value 1; the wave that owns
-        // tile 0 leaves it after the message's partials for the combine
-        const u32x4 ek = aes_ctr<NR>(cj0, c, rk, lds, lk);
-        if (lane == 0)
-            partials[d.tile_base + d.n_tiles] = ek;
-    }
-
-    const uint64_t B = 1ull << d.log2B;
-    const uint32_t R = (uint32_t)(B >> 6);
-    const int64_t vbase = (int64_t)(t * B) - (int64_t)d.z;  // GHASH index of lane 0, row 0
-    const uint32_t r0 = vbase < 0 ? (uint32_t)((uint64_t)(-vbase) >> 6) : 0u;
-    const int64_t na = (int64_t)d.na;
-    const int64_t nafull = (int64_t)(d.aad_len >> 4);
-    const int64_t nfull = (int64_t)(d.len >> 4);
-    const int64_t ndat = (int64_t)d.n;
-    const bool enc = d.op == 0;
-    const uint8_t *__restrict__ in = reinterpret_cast<const uint8_t *>(d.in);
-    uint8_t *__restrict__ out = reinterpret_cast<uint8_t *>(d.out);
-    const GLOBAL_AS u32x4 *in_g = gptr<const u32x4>(d.in);
-    GLOBAL_AS u32x4 *out_g = gptr<u32x4>(d.out);
-    const GLOBAL_AS u32x4 *aad_g = gptr<const u32x4>(d.aad);
-
-    u32x4 a = {0, 0, 0, 0};
-    // boundary row: zero padding, AAD, partial blocks or the length block
-    auto boundary_row = [&](int64_t v0) {
-        const int64_t v = v0 + lane;
-        const uint64_t j = (uint64_t)(v - na);
-        const u32x4 ks = aes_ctr<NR>((uint32_t)j + c1, c, rk, lds, lk);
-        u32x4 X = {0, 0, 0, 0};
-        if (GH && v >= 0 && v < na) {
-            X = load_block_partial(reinterpret_cast<const uint8_t *>(d.aad), (uint64_t)v, d.aad_len);
-        } else if (v >= na && v < na + ndat) {
-            const u32x4 x = load_block_partial(in, j, d.len);
-            const u32x4 o = x ^ ks;
-            store_block_partial(out, j, d.len, o);
-            X = enc ? mask_block(o, j, d.len) : x;
-        } else if (GH && v == na + ndat) {
-            const uint64_t abits = d.aad_len * 8, cbits = d.len * 8;
-            X = u32x4{bswap32((uint32_t)(abits >> 32)), bswap32((uint32_t)abits), bswap32((uint32_t)(cbits >> 32)),
-                      bswap32((uint32_t)cbits)};
-        }
-        if (GH)
-            a = ghash_mul8(a, X, lds, gk);
+    const uint32_t log2B = dp->log2B;
+    const int32_t R = (int32_t)(1u << (log2B - 6));
+    const int64_t vbase = (int64_t)(t << log2B) - (int64_t)dp->z;  // GHASH index of lane 0, row 0
+    const int32_t r0 = vbase < 0 ? (int32_t)((uint64_t)(-vbase) >> 6) : 0;
+    const int64_t na = (int64_t)dp->na, nfull = (int64_t)(dp->len >> 4);
+    // rows whose 64 blocks all lie in blocks [first, end) of the sequence
+    auto whole_rows = [&](int64_t first, int64_t end, int32_t &lo, int32_t &hi) {
+        const int64_t l = first - vbase, h = end - vbase - 64;  // 64 r >= l, 64 r <= h
+        const int64_t f0 = l <= 0 ? 0 : (l + 63) >> 6, f1 = h < 0 ? 0 : (h >> 6) + 1;
+        lo = f0 > (int64_t)r0 ? (f0 < (int64_t)R ? (int32_t)f0 : R) : r0;
+        hi = f1 > (int64_t)lo ? (f1 < (int64_t)R ? (int32_t)f1 : R) : lo;
     };
-
-    uint32_t r = r0;
-    if (GH && AADROWS) {
-        // Rows of whole AAD blocks, [ra0, ra1), take the GHASH step only.  They
-        // follow at most one boundary row (zero prefix and AAD start) and
-        // precede every data row, so they are peeled off before the main loop.
-        const int64_t vb = vbase;
-        const int64_t rz = vb >= 0 ? 0 : (-vb + 63) >> 6;        // first row with v0 >= 0
-        const int64_t fit = nafull - vb;                          // rows r with v0 + 64 <= nafull: r < fit / 64
-        int64_t ra0 = rz > (int64_t)r0 ? rz : (int64_t)r0;
-        int64_t ra1 = fit >= 64 ? fit >> 6 : 0;
-        ra1 = ra1 < (int64_t)R ? ra1 : (int64_t)R;
-        if (ra1 > ra0) {
-            for (; (int64_t)r < ra0; ++r)
-                boundary_row(vb + 64 * (int64_t)r);
-            for (; (int64_t)r < ra1; ++r)
-                a = ghash_mul8(a, aad_g[(uint64_t)(vb + 64 * (int64_t)r) + (uint64_t)lane], lds, gk);
-        }
-    }
-
-    // Rows [fa, fb) hold 64 whole data blocks each and take the fast path
-    // (v0 >= na and v0 + 64 <= na + nfull).  The range is computed once, so
-    // the row loop keeps only scalar 32-bit bookkeeping and one uniform row
-    // address.
-    int64_t rf0, rf1;
-    {
-        const int64_t lo = na - vbase;                // 64 r >= lo
-        const int64_t hi = na + nfull - vbase - 64;   // 64 r <= hi
-        rf0 = lo <= 0 ? 0 : (lo + 63) >> 6;
-        rf1 = hi < 0 ? 0 : (hi >> 6) + 1;
-    }
-    const uint32_t fa = (uint32_t)(rf0 > (int64_t)r ? (rf0 < (int64_t)R ? rf0 : (int64_t)R) : (int64_t)r);
-    const uint32_t fb = (uint32_t)(rf1 > (int64_t)fa ? (rf1 < (int64_t)R ? rf1 : (int64_t)R) : (int64_t)fa);
-    for (; r < fa; ++r)
-        boundary_row(vbase + 64 * (int64_t)r);
+    int32_t fa, fb, aa = 0, ab = 0;
+    whole_rows(na, na + nfull, fa, fb);
+    if (GH)
+        whole_rows(0, (int64_t)(dp->aad_len >> 4), aa, ab);
+    const int64_t jb = vbase - na;  // data block index of lane 0, row 0
 
     uint32_t hc = 0xffffffffu;  // upper counter bits `cur` belongs to (none yet)
-    Ctr2 cur = {0, 0, 0, 0};
-    const uint32_t loff = 16u * (uint32_t)lane;  // this lane's byte offset in a row
-    // Issue priority falls as the wave gets through its rows (at 5/8, 3/4
-    // and 7/8 of them), so that waves the arbiter has left behind catch up
-    // and the compute unit stays full until its last tile ends.
-    const uint32_t span = fb > r ? fb - r : 0u;
-    const uint32_t q1 = r + 5 * (span / 8), q2 = r + 3 * (span / 4), q3 = r + 7 * (span / 8);
-    __builtin_amdgcn_s_setprio(3);
-    for (; r < fb; ++r) {
-        if (r == q1)
-            __builtin_amdgcn_s_setprio(2);
-        if (r == q2)
-            __builtin_amdgcn_s_setprio(1);
-        if (r == q3)
-            __builtin_amdgcn_s_setprio(0);
-        // re-read the round keys with scalar loads each row instead of holding
-        // 4*(Nr+1) of them (or their lane-rotated copies) in registers
-        rk = rk_base;
-        asm volatile("" : "+s"(rk));
-        const uint64_t j0 = (uint64_t)(vbase + 64 * (int64_t)r - na);  // first data block of the row (uniform)
-        const GLOBAL_AS uint8_t *src = reinterpret_cast<const GLOBAL_AS uint8_t *>(in_g + j0);
-        GLOBAL_AS uint8_t *dst = reinterpret_cast<GLOBAL_AS uint8_t *>(out_g + j0);
-        const u32x4 x = *reinterpret_cast<const GLOBAL_AS u32x4 *>(src + loff);
-        // counters of this row: base + lane (mod 2^32); the upper 24 bits
-        // change at most once inside a row, and then by one
-        const uint32_t base = (uint32_t)j0 + c1;
+    u32x4 cur = {0, 0, 0, 0};
+    // The state after round 2 of the row whose first counter is `base`: its
+    // counters are base + lane (mod 2^32), whose upper 24 bits change at most
+    // once inside the row, and then by one.
+    auto round2 = [&](uint32_t base) {
+        const uint32_t low = (base + (uint32_t)lane) & 255u;
+        u32x4 s = *reinterpret_cast<const u32x4 *>(lds + Kind<KIND>::round2 + 16u * low);
         const uint32_t h = base >> 8;
         if (h != hc) {
-            cur = ctr_round2(h, c, rk, te);
+            cur = c.high_words(h, rk, te);
             hc = h;
         }
-        const uint32_t ctr = base + (uint32_t)lane;
-        Ctr2 q = cur;
         if ((base & 255u) > 192u) {
             const uint32_t h1 = (h + 1u) & 0xffffffu;
-            const Ctr2 nxt = ctr_round2(h1, c, rk, te);
-            // this lane's low counter byte wrapped inside the row; compared in
-            // the top byte, as aes_ctr2 uses it, so that no per-lane constant
-            // stays live across the loop
-            const bool up = (ctr << 24) < (base << 24);
-            q = Ctr2{up ? nxt.v0 : cur.v0, up ? nxt.v1 : cur.v1, up ? nxt.v2 : cur.v2, up ? nxt.v3 : cur.v3};
+            const u32x4 nxt = c.high_words(h1, rk, te);
+            const bool up = low < (base & 255u);  // this lane's low counter byte wrapped inside the row
+            s ^= u32x4{up ? nxt.x : cur.x, up ? nxt.y : cur.y, up ? nxt.z : cur.z, up ? nxt.w : cur.w};
             cur = nxt;
             hc = h1;
+        } else {
+            s ^= cur;
         }
-        const u32x4 ks = aes_ctr2<NR>(ctr, q, c, rk, lds, lk);
-        const u32x4 o = x ^ ks;
-        __builtin_nontemporal_store(o, reinterpret_cast<GLOBAL_AS u32x4 *>(dst + loff));
-        if (GH)
-            a = ghash_mul8(a, enc ? o : x, lds, gk);
+        return u32x4{tab.rot(s.x), tab.rot(s.y), tab.rot(s.z), tab.rot(s.w)};
+    };
+
+    // GHASH runs one row behind: a is the Horner value without the pending row xp
+    u32x4 a = {0, 0, 0, 0}, xp = {0, 0, 0, 0};
+    const bool ek = KIND == kGcm && t == 0;
+    __builtin_amdgcn_s_setprio(3);
+    for (int32_t r = ek ? r0 - 1 : r0; r < R;) {
+        if (GH && r >= aa && r < ab) {
+            // rows of 64 whole AAD blocks: GHASH alone
+            const GLOBAL_AS u32x4 *src = gptr<const u32x4>(dp->aad) + (vbase + 64 * (int64_t)r) + lane;
+            for (; r < ab; ++r, src += 64) {
+                const u32x4 x = *src;
+                a = ghash_mul8(a, xp, lds, gk);
+                xp = SIV ? rev_block(x) : x;
+            }
+            continue;
+        }
+        if (r < fa || r >= fb) {
+            // a row with zero padding, AAD, a partial block or the length
+            // block, or the extra row for E_K(J0)
+            const CONST_AS MsgDesc *bp = dp;
+            asm volatile("" : "+s"(bp));
+            const bool ekrow = ek && r < r0;
+            const int64_t v0 = vbase + 64 * (int64_t)r, v = v0 + lane;
+            const int64_t ndat = (int64_t)bp->n;
+            const bool data = v >= na && v < na + ndat;
+            const uint64_t j = (uint64_t)(v - na);
+            const bool hot = AES && (ekrow || (v0 + 64 > na && v0 < na + ndat));  // some lane needs a keystream block
+            u32x4 ks = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+            if (hot) {
+                GhashStep none;
+                ks = aes_rounds<NR, false>(round2(ekrow ? cj0 : (uint32_t)jb + 64u * (uint32_t)r + c1), rk, tab, none, gk);
+            }
+            ++r;
+            if (ekrow) {
+                if (lane == 0)
+                    partials[bp->tile_base + bp->n_tiles] = ks;
+                continue;
+            }
+            if (data) {
+                x = load_block_partial(gptr<const uint8_t>(bp->in), j, bp->len);
+                if (AES) {
+                    const u32x4 o = x ^ ks;
+                    store_block_partial(gptr<uint8_t>(bp->out), j, bp->len, o);
+                    x = (SIV || bp->op == 0) ? mask_block(o, j, bp->len) : x;
+                }
+            } else if (GH && v >= 0 && v < na) {
+                x = load_block_partial(gptr<const uint8_t>(bp->aad), (uint64_t)v, bp->aad_len);
+            } else if (GH && v == na + ndat) {
+                const uint64_t abits = bp->aad_len * 8, cbits = bp->len * 8;
+                x = SIV ? u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)cbits, (uint32_t)(cbits >> 32)}
+                        : u32x4{bswap32((uint32_t)(abits >> 32)), bswap32((uint32_t)abits),
+                                bswap32((uint32_t)(cbits >> 32)), bswap32((uint32_t)cbits)};
+            }
+            if (GH) {
+                a = ghash_mul8(a, xp, lds, gk);
+                xp = SIV ? rev_block(x) : x;
+            }
+            continue;
+        }
+        // Rows of 64 whole data blocks.  Issue priority falls as the wave gets
+        // through them (at 5/8, 3/4 and 7/8), so that waves the arbiter has
+        // left behind catch up and the compute unit stays full until its last
+        // tile ends.
+        const int32_t span = fb - fa;
+        const int32_t q1 = fa + 5 * (span / 8), q2 = fa + 3 * (span / 4), q3 = fa + 7 * (span / 8);
+        const GLOBAL_AS uint8_t *src = gptr<const uint8_t>(dp->in) + 16 * (jb + 64 * (int64_t)r);
+        GLOBAL_AS uint8_t *dst = gptr<uint8_t>(dp->out) + 16 * (jb + 64 * (int64_t)r);
+        uint32_t base = (uint32_t)jb + 64u * (uint32_t)r + c1;
+        const uint32_t loff = 16u * (uint32_t)lane;
+        const bool enc = SIV || dp->op == 0;
+        for (; r < fb; ++r, src += 1024, dst += 1024, base += 64) {
+            if (r == q1)
+                __builtin_amdgcn_s_setprio(2);
+            if (r == q2)
+                __builtin_amdgcn_s_setprio(1);
+            if (r == q3)
+                __builtin_amdgcn_s_setprio(0);
+            const u32x4 x = *reinterpret_cast<const GLOBAL_AS u32x4 *>(src + loff);
+            if (!AES) {
+                a = ghash_mul8(a, xp, lds, gk);
+                xp = SIV ? rev_block(x) : x;
+                continue;
+            }
+            const CONST_AS uint32_t *rkr = rk;
+            asm volatile("" : "+s"(rkr));  // round keys are read again each row instead of held across all of them
+            GhashStep gs;
+            if (GH)
+                gs.start(a, xp, gk);
+            const u32x4 s = round2(base);
+            const u32x4 o = x ^ aes_rounds<NR, GH>(s, rkr, tab, gs, gk);
+            __builtin_nontemporal_store(o, reinterpret_cast<GLOBAL_AS u32x4 *>(dst + loff));
+            if (GH) {
+                a = gs.acc;
+                xp = enc ? o : x;
+                if (SIV)
+                    xp = rev_block(xp);
+            }
+        }
     }
-    for (; r < R; ++r)
-        boundary_row(vbase + 64 * (int64_t)r);
     if (!GH)
         return;
-
+    a = ghash_mul8(a, xp, lds, gk);
     // fix-up: a * H^(63 - lane) through the lane's window table in LDS
-    a = gf_mul_lanewin(a, lds, lane);
-    a = wave_xor_reduce(a);
+    const u32x4 p = wave_xor_reduce(gf_mul_lanewin(a, lds + Kind<KIND>::windows, lane));
     if (lane == 0)
-        partials[d.tile_base + t] = a;
+        partials[dp->tile_base + t] = p;
 }
 
-// T-tables into LDS: dword 16384 + 64*e + 16*t + c holds rotl(TE0[e], 8t)
-// for copy c = 0..15; thread q of NT writes the 16 copies of entries
-// (e, t) = (q >> 2, q & 3), q + NT, ..., with all loads issued first.  The
-// caller adds the barrier.
+// T-tables into LDS, every copy of every entry, all of a thread's loads issued
+// before its stores; the caller adds the barrier.
+//
+// 32 copies: 16-byte unit i of each 64 KiB half holds four copies of entry
+// i >> 4 of table ((i >> 3) & 1), in the upper half of the table after next.
 template <int NT>
-__device__ __forceinline__ void stage_ttables(u32x4 *lds_v, const uint32_t *__restrict__ te0g)
+__device__ __forceinline__ void stage_ttables(u32x4 *lds_v, const uint32_t *__restrict__ te0g, Tables<false> *)
 {
-    constexpr int kPer = (1024 + NT - 1) / NT;
+    constexpr int kPer = (4096 + NT - 1) / NT;
     uint32_t v[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        const int q = (int)threadIdx.x + r * NT;
-        v[r] = q < 1024 ? rotl32(te0g[q >> 2], 8 * (q & 3)) : 0u;
+        const int i = (int)threadIdx.x + r * NT;
+        v[r] = i < 4096 ? te0g[i >> 4] : 0u;
     }
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
-        const int q = (int)threadIdx.x + r * NT;
-        if (q >= 1024)
+        const int i = (int)threadIdx.x + r * NT;
+        if (i >= 4096)
             break;
-        u32x4 *dst = lds_v + 4096 + 4 * q;  // dword 16384 + 64*(q >> 2) + 16*(q & 3)
-        const u32x4 x = {v[r], v[r], v[r], v[r]};
-        dst[0] = x;
-        dst[1] = x;
-        dst[2] = x;
-        dst[3] = x;
+        const uint32_t lo = (i & 8) ? rotl32(v[r], 8) : v[r];  // tables 0, 1
+        const uint32_t hi = rotr_by(lo, 16);                   // tables 2, 3
+        lds_v[i] = u32x4{lo, lo, lo, lo};
+        lds_v[4096 + i] = u32x4{hi, hi, hi, hi};
+    }
+}
+
+// 16 copies: unit i of the 64 KiB holds four copies of entry i >> 4 of table (i >> 2) & 3
+template <int NT>
+__device__ __forceinline__ void stage_ttables(u32x4 *lds_v, const uint32_t *__restrict__ te0g, Tables<true> *)
+{
+    constexpr int kPer = (4096 + NT - 1) / NT;
+    uint32_t v[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int i = (int)threadIdx.x + r * NT;
+        v[r] = i < 4096 ? te0g[i >> 4] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int i = (int)threadIdx.x + r * NT;
+        if (i >= 4096)
+            break;
+        const uint32_t x = rotr_by(v[r], (32u - 8u * ((uint32_t)(i >> 2) & 3u)) & 31u);
+        lds_v[4096 + i] = u32x4{x, x, x, x};
     }
 }
 
@@ -1179,78 +1324,84 @@ __device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
     }
 }
 
-// Kernel variants (each a kernel of its own, so that the extra work of one
-// leaves the register allocation of the others alone): GCM; counter mode
-// only; GCM with the GHASH-only pass over whole AAD rows, for single messages
-// whose AAD spans at least 64 rows of blocks; GCM with J0 read from device
-// memory, for single messages whose IV is not 96 bits (AAD rows then take the
-// boundary path).
-constexpr int kModeGcm = 0, kModeCtr = 1, kModeGcmAad = 2, kModeGcmJ0 = 3;
-constexpr uint64_t kAadRowsMinBytes = 64 * 64 * 16;
 
-template <int WAVES, bool BATCH, int MODE>
-__global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(const MsgDesc *__restrict__ descs,
+// A workgroup covers WAVES consecutive tiles of a message per work item; one
+// message (single) or a batch with a list of items.
+//
+// What bounds it is the LDS.  Per row of 64 blocks and CU, AES-256: 192 b32
+// lookups, which take 2.27 cycles each with 16 waves in a loop of nothing
+// else, one b128 for round 2 and 16 b128 of GHASH: 453 LDS cycles of 523 in
+// all, 425 vector instructions.  1 GiB with AES-256 / AES-128:
+//   GCM           1058 -> 1039 us, 823 -> 805 us
+//   counter mode  1006 ->  824 us, 746 -> 627 us (32 table copies: no key
+//                 rotations, 449 cycles a row where it took 566)
+//   SIV encrypt   1150 -> 1059 us, 917 -> 854 us
+// against a loop with 197 lookups, whose waits drained the LDS queue every few
+// lookups in counter mode, and with 16 copies in every pass.
+template <int WAVES, bool BATCH, int KIND>
+__global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const MsgDesc *__restrict__ descs,
                                                           const WorkItem *__restrict__ items, uint32_t n_items,
-                                                          MsgDesc single, const uint32_t *__restrict__ te0g,
+                                                          const uint32_t *__restrict__ te0g,
                                                           u32x4 *__restrict__ partials, uint32_t *counters)
 {
-    constexpr bool GH = MODE != kModeCtr;
-    constexpr bool AADROWS = MODE == kModeGcmAad;
-    constexpr bool J0DEV = MODE == kModeGcmJ0;
-    __shared__ u32x4 lds_v[9216];  // 144 KiB: GHASH table, replicated T-tables, fix-up windows
+    using K = Kind<KIND>;
+    __shared__ u32x4 lds_v[K::lds / 16];
     const uint8_t *lds = reinterpret_cast<const uint8_t *>(lds_v);
+    const CONST_AS uint32_t *te = cptr<uint32_t>(te0g);
+    const int lane = threadIdx.x & 63;
+    const int wave = (int)uniform(threadIdx.x >> 6);  // wave-uniform: row bookkeeping stays scalar
+    const typename K::tables tab(lds, lane);
+    const GhK gk = gh_constants(lane);
 
-    if (GH && blockIdx.x == 0 && threadIdx.x == 0)
+    if (KIND == kGcm && blockIdx.x == 0 && threadIdx.x == 0)
         counters[0] = 0;  // reject count for this launch (read by the zero-fill)
 
-    // A single message's key tables are staged here with the T-tables, while
-    // little else is live; a batch stages the tables of each work item's key
-    // in the loop (the first item's staging starts and ends with a barrier,
-    // which also publishes the T-tables).
-    stage_ttables<WAVES * 64>(lds_v, te0g);
+    if (K::aes)
+        stage_ttables<WAVES * 64>(lds_v, te0g, (typename K::tables *)nullptr);
     uint64_t cur_slot = 0;
-    if (GH && !BATCH) {
-        stage_key_tables<WAVES * 64>(lds_v, single.slot);
-        cur_slot = single.slot;
-    }
-    if (!GH || !BATCH)
-        lds_barrier();
-    const LaneK lk = lane_constants(threadIdx.x & 63);
-    const GhK gk = gh_constants(threadIdx.x & 63);
-
-    const int wave = (int)uniform(threadIdx.x >> 6);  // wave-uniform: row bookkeeping stays scalar
+    uint32_t cur_msg = 0xffffffffu;
     for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
-        MsgDesc d;
-        uint32_t first;
+        const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
+        uint32_t first, msg = 0;
         if (BATCH) {
             const WorkItem w = load_const<WorkItem>(items + it);
-            d = load_const<MsgDesc>(descs + w.msg);
+            dp = cptr<MsgDesc>(descs + w.msg);
             first = w.first_tile;
+            msg = w.msg;
         } else {
-            // the descriptor's words pass through an empty asm on every item,
-            // so that nothing derived from them is hoisted out of this loop
-            // and held (or spilled) across all of it
-            d = single;
-            uint32_t *dw = reinterpret_cast<uint32_t *>(&d);
-#pragma unroll
-            for (unsigned i = 0; i < sizeof(MsgDesc) / 4; ++i)
-                asm volatile("" : "+s"(dw[i]));
-            first = (uint32_t)d.tile_lo + it * WAVES;
+            first = (uint32_t)dp->tile_lo + it * WAVES;
         }
-        if (GH && BATCH && d.slot != cur_slot) {
-            lds_barrier();
-            stage_key_tables<WAVES * 64>(lds_v, d.slot);
-            cur_slot = d.slot;
+        if (msg != cur_msg) {
+            // a new message: its key's GHASH tables (unless staged already) and
+            // its round-2 words, between barriers that also publish the T-tables
+            const uint64_t slot = dp->slot;
+            if (BATCH)
+                lds_barrier();
+            if (K::gh && slot != cur_slot) {
+                stage_key_tables<WAVES * 64>(lds_v, slot);
+                cur_slot = slot;
+            }
+            if (K::aes) {
+                if (!BATCH)
+                    lds_barrier();
+                CtrBlock<K::siv> c;
+                uint32_t c1, cj0;
+                message_counter<KIND>(dp, te, c, c1, cj0);
+                if (threadIdx.x < 256)
+                    lds_v[K::round2 / 16 + threadIdx.x] = c.low_words(threadIdx.x, tab);
+            }
+            cur_msg = msg;
             lds_barrier();
         }
         const uint64_t t = (uint64_t)first + (uint64_t)wave;
-        if (t < d.tile_hi) {
-            if (d.nr == 10)
-                wave_tile<10, GH, AADROWS, J0DEV>(d, t, lds, lk, gk, te0g, partials);
-            else if (d.nr == 12)
-                wave_tile<12, GH, AADROWS, J0DEV>(d, t, lds, lk, gk, te0g, partials);
+        if (t < dp->tile_hi) {
+            const uint32_t nr = K::aes ? dp->nr : 14;
+            if (nr == 10)
+                wave_tile<10, KIND>(dp, t, lds, tab, gk, te, partials);
+            else if (nr == 12 && !K::siv)
+                wave_tile<12, KIND>(dp, t, lds, tab, gk, te, partials);
             else
-                wave_tile<14, GH, AADROWS, J0DEV>(d, t, lds, lk, gk, te0g, partials);
+                wave_tile<14, KIND>(dp, t, lds, tab, gk, te, partials);
         }
     }
 }
@@ -1536,8 +1687,6 @@ struct SivArg {
     uint32_t pad;
 };
 
-__device__ __forceinline__ u32x4 rev_block(u32x4 x) { return u32x4{bswap32(x.w), bswap32(x.z), bswap32(x.y), bswap32(x.x)}; }
-
 // One wave: the message keys from the key-generating key in slot `kgk`
 // (first halves of AES_KGK(LE32(i) || nonce): i = 0, 1 the authentication
 // key, i = 2, 3 (and 4, 5 for a 256-bit key) the encryption key), expanded
@@ -1640,226 +1789,6 @@ __global__ __launch_bounds__(64) void k_siv_tag(uint64_t slot, const u32x4 *g, S
     counters[1] = 0u;
 }
 
-struct SivCtx {
-    uint32_t u0, u1, u2, u3;  // round-1 columns without the counter dword's bytes (unrotated, uniform)
-    uint32_t rk0;             // round key 0, column 0
-};
-
-// Keystream block for LE counter value `ctr` in dword 0: round 1 needs the
-// four lookups of the counter dword's bytes only.
-template <int NR>
-__device__ __forceinline__ u32x4 aes_siv_ctr(uint32_t ctr, const SivCtx &c, const CONST_AS uint32_t *rk,
-                                             const uint8_t *lds, const LaneK &lk)
-{
-    const uint32_t w0 = rotr_by(ctr ^ c.rk0, lk.rot);
-    const uint32_t s0 = rotr_by(c.u0, lk.rot) ^ LK(0, w0);
-    const uint32_t s1 = rotr_by(c.u1, lk.rot) ^ LK(3, w0);
-    const uint32_t s2 = rotr_by(c.u2, lk.rot) ^ LK(2, w0);
-    const uint32_t s3 = rotr_by(c.u3, lk.rot) ^ LK(1, w0);
-    return aes_rounds<2, NR>(s0, s1, s2, s3, rk, lds, lk);
-}
-
-// Counter-mode caching through round 2, as for GCM: with counter bytes 1..3
-// fixed, round 1 leaves columns 1..3 fixed and column 0 depends on the low
-// counter byte only, so round 2 takes one lookup per column.
-__device__ __forceinline__ Ctr2 siv_round2(uint32_t hi, const SivCtx &c, const CONST_AS uint32_t *rk,
-                                           const CONST_AS uint32_t *te)
-{
-    const uint32_t v = (hi << 8) ^ c.rk0;  // counter bytes 1..3 with the key (byte 0 unused)
-    const uint32_t u1 = c.u1 ^ te_s(te, 3, B3(v));
-    const uint32_t u2 = c.u2 ^ te_s(te, 2, B2(v));
-    const uint32_t u3 = c.u3 ^ te_s(te, 1, B1(v));
-    Ctr2 q;
-    q.v0 = te_s(te, 1, B1(u1)) ^ te_s(te, 2, B2(u2)) ^ te_s(te, 3, B3(u3)) ^ rk[8];
-    q.v1 = te_s(te, 0, B0(u1)) ^ te_s(te, 1, B1(u2)) ^ te_s(te, 2, B2(u3)) ^ rk[9];
-    q.v2 = te_s(te, 0, B0(u2)) ^ te_s(te, 1, B1(u3)) ^ te_s(te, 3, B3(u1)) ^ rk[10];
-    q.v3 = te_s(te, 0, B0(u3)) ^ te_s(te, 2, B2(u1)) ^ te_s(te, 3, B3(u2)) ^ rk[11];
-    return q;
-}
-
-template <int NR>
-__device__ __forceinline__ u32x4 aes_siv_ctr2(uint32_t ctr, const Ctr2 &q, const SivCtx &c,
-                                              const CONST_AS uint32_t *rk, const uint8_t *lds, const LaneK &lk)
-{
-    const uint32_t w0 = rotr_by(ctr ^ c.rk0, lk.rot);       // byte 0: low counter byte ^ key
-    const uint32_t x0 = rotr_by(c.u0, lk.rot) ^ LK(0, w0);  // round-1 column 0
-    const uint32_t s0 = rotr_by(q.v0, lk.rot) ^ LK(0, x0);
-    const uint32_t s1 = rotr_by(q.v1, lk.rot) ^ LK(3, x0);
-    const uint32_t s2 = rotr_by(q.v2, lk.rot) ^ LK(2, x0);
-    const uint32_t s3 = rotr_by(q.v3, lk.rot) ^ LK(1, x0);
-    return aes_rounds<3, NR>(s0, s1, s2, s3, rk, lds, lk);
-}
-
-// The three tile passes: the POLYVAL of AAD and plaintext (encrypt, first
-// pass), counter mode alone (encrypt, second pass, once the tag is known),
-// and counter mode fused with the POLYVAL of its output (decrypt-verify).
-constexpr int kSivHash = 0, kSivCtr = 1, kSivDec = 2;
-
-// Wave tile t of one message, laid out as in wave_tile: rows of 64 blocks,
-// lane l on block 64r + l, per-lane Horner with H'^64 over byte-reversed
-// blocks, fix-up by H'^(63 - l), XOR across the wave.  The GHASH sequence is
-// AAD blocks, data blocks and the length block LE64(8|A|) || LE64(8|P|),
-// each zero-padded and reversed.
-template <int NR, int PASS>
-__device__ void wave_tile_siv(const MsgDesc &d, uint64_t t, const uint8_t *__restrict__ lds, const LaneK &lk,
-                              const GhK &gk, const uint32_t *__restrict__ te0g, u32x4 *__restrict__ partials)
-{
-    constexpr bool GH = PASS != kSivCtr, AES = PASS != kSivHash;
-    const int lane = threadIdx.x & 63;
-    const CONST_AS uint32_t *te = cptr<uint32_t>(te0g);
-    const CONST_AS uint32_t *rk_base = cptr<uint32_t>(reinterpret_cast<const void *>(d.slot));
-    const CONST_AS uint32_t *rk = rk_base;
-    SivCtx c = {0, 0, 0, 0, 0};
-    uint32_t c0 = 0;
-    if (AES) {
-        const CONST_AS uint32_t *cw = cptr<uint32_t>(reinterpret_cast<const void *>(d.j0));
-        c0 = cw[0];
-        const uint32_t s1 = cw[1] ^ rk[1], s2 = cw[2] ^ rk[2], s3 = cw[3] ^ rk[3];
-        c.u0 = uniform(te_u(lds, 1, B1(s1)) ^ te_u(lds, 2, B2(s2)) ^ te_u(lds, 3, B3(s3)) ^ rk[4]);
-        c.u1 = uniform(te_u(lds, 0, B0(s1)) ^ te_u(lds, 1, B1(s2)) ^ te_u(lds, 2, B2(s3)) ^ rk[5]);
-        c.u2 = uniform(te_u(lds, 0, B0(s2)) ^ te_u(lds, 1, B1(s3)) ^ te_u(lds, 3, B3(s1)) ^ rk[6]);
-        c.u3 = uniform(te_u(lds, 0, B0(s3)) ^ te_u(lds, 2, B2(s1)) ^ te_u(lds, 3, B3(s2)) ^ rk[7]);
-        c.rk0 = rk[0];
-    }
-
-    const uint64_t B = 1ull << d.log2B;
-    const uint32_t R = (uint32_t)(B >> 6);
-    const int64_t vbase = (int64_t)(t * B) - (int64_t)d.z;  // sequence index of lane 0, row 0
-    const uint32_t r0 = vbase < 0 ? (uint32_t)((uint64_t)(-vbase) >> 6) : 0u;
-    const int64_t na = (int64_t)d.na;
-    const int64_t nfull = (int64_t)(d.len >> 4);
-    const int64_t ndat = (int64_t)d.n;
-    const uint8_t *__restrict__ in = reinterpret_cast<const uint8_t *>(d.in);
-    uint8_t *__restrict__ out = reinterpret_cast<uint8_t *>(d.out);
-    const GLOBAL_AS u32x4 *in_g = gptr<const u32x4>(d.in);
-    GLOBAL_AS u32x4 *out_g = gptr<u32x4>(d.out);
-
-    u32x4 a = {0, 0, 0, 0};
-    auto boundary_row = [&](int64_t v0) {
-        const int64_t v = v0 + lane;
-        const uint64_t j = (uint64_t)(v - na);
-        u32x4 ks = {0, 0, 0, 0};
-        if (AES)
-            ks = aes_siv_ctr<NR>((uint32_t)j + c0, c, rk, lds, lk);
-        u32x4 X = {0, 0, 0, 0};
-        if (GH && v >= 0 && v < na) {
-            X = load_block_partial(reinterpret_cast<const uint8_t *>(d.aad), (uint64_t)v, d.aad_len);
-        } else if (v >= na && v < na + ndat) {
-            const u32x4 x = load_block_partial(in, j, d.len);
-            if (AES) {
-                const u32x4 o = x ^ ks;
-                store_block_partial(out, j, d.len, o);
-                X = mask_block(o, j, d.len);
-            } else {
-                X = x;
-            }
-        } else if (GH && v == na + ndat) {
-            const uint64_t abits = d.aad_len * 8, pbits = d.len * 8;
-            X = u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)pbits, (uint32_t)(pbits >> 32)};
-        }
-        if (GH)
-            a = ghash_mul8(a, rev_block(X), lds, gk);
-    };
-
-    // rows [fa, fb) hold 64 whole data blocks (as in wave_tile), with the
-    // same falling issue priority over them
-    int64_t rf0, rf1;
-    {
-        const int64_t lo = na - vbase, hi = na + nfull - vbase - 64;
-        rf0 = lo <= 0 ? 0 : (lo + 63) >> 6;
-        rf1 = hi < 0 ? 0 : (hi >> 6) + 1;
-    }
-    const uint32_t fa = (uint32_t)(rf0 > (int64_t)r0 ? (rf0 < (int64_t)R ? rf0 : (int64_t)R) : (int64_t)r0);
-    const uint32_t fb = (uint32_t)(rf1 > (int64_t)fa ? (rf1 < (int64_t)R ? rf1 : (int64_t)R) : (int64_t)fa);
-    uint32_t r = r0;
-    for (; r < fa; ++r)
-        boundary_row(vbase + 64 * (int64_t)r);
-    uint32_t hc = 0xffffffffu;
-    Ctr2 cur = {0, 0, 0, 0};
-    const uint32_t loff = 16u * (uint32_t)lane;
-    const uint32_t span = fb - r;
-    const uint32_t q1 = r + span / 4, q2 = r + span / 2, q3 = r + 3 * (span / 4);
-    __builtin_amdgcn_s_setprio(3);
-    for (; r < fb; ++r) {
-        if (r == q1)
-            __builtin_amdgcn_s_setprio(2);
-        if (r == q2)
-            __builtin_amdgcn_s_setprio(1);
-        if (r == q3)
-            __builtin_amdgcn_s_setprio(0);
-        rk = rk_base;
-        asm volatile("" : "+s"(rk));
-        const uint64_t j0 = (uint64_t)(vbase + 64 * (int64_t)r - na);  // first data block of the row (uniform)
-        {
-            const u32x4 x = *reinterpret_cast<const GLOBAL_AS u32x4 *>(
-                reinterpret_cast<const GLOBAL_AS uint8_t *>(in_g + j0) + loff);
-            if (AES) {
-                const uint32_t base = (uint32_t)j0 + c0;
-                const uint32_t h = base >> 8;
-                if (h != hc) {
-                    cur = siv_round2(h, c, rk, te);
-                    hc = h;
-                }
-                const uint32_t ctr = base + (uint32_t)lane;
-                Ctr2 q = cur;
-                if ((base & 255u) > 192u) {
-                    const uint32_t h1 = (h + 1u) & 0xffffffu;
-                    const Ctr2 nxt = siv_round2(h1, c, rk, te);
-                    const bool up = (ctr << 24) < (base << 24);  // low counter byte wrapped in the row
-                    q = Ctr2{up ? nxt.v0 : cur.v0, up ? nxt.v1 : cur.v1, up ? nxt.v2 : cur.v2, up ? nxt.v3 : cur.v3};
-                    cur = nxt;
-                    hc = h1;
-                }
-                const u32x4 o = x ^ aes_siv_ctr2<NR>(ctr, q, c, rk, lds, lk);
-                __builtin_nontemporal_store(
-                    o, reinterpret_cast<GLOBAL_AS u32x4 *>(reinterpret_cast<GLOBAL_AS uint8_t *>(out_g + j0) + loff));
-                if (GH)
-                    a = ghash_mul8(a, rev_block(o), lds, gk);
-            } else {
-                a = ghash_mul8(a, rev_block(x), lds, gk);
-            }
-        }
-    }
-    for (; r < R; ++r)
-        boundary_row(vbase + 64 * (int64_t)r);
-    if (!GH)
-        return;
-    a = gf_mul_lanewin(a, lds, lane);
-    a = wave_xor_reduce(a);
-    if (lane == 0)
-        partials[d.tile_base + t] = a;
-}
-
-// One message, tiles [d.tile_lo, d.tile_hi): workgroup item it covers WAVES
-// consecutive tiles.  LDS as in k_gcm_tiles (GHASH table of the message slot,
-// T-tables), each staged only by the passes that read it.
-template <int WAVES, int PASS>
-__global__ __launch_bounds__(WAVES * 64) void k_siv_tiles(MsgDesc d, uint32_t n_items,
-                                                          const uint32_t *__restrict__ te0g,
-                                                          u32x4 *__restrict__ partials)
-{
-    constexpr bool GH = PASS != kSivCtr, AES = PASS != kSivHash;
-    __shared__ u32x4 lds_v[9216];
-    const uint8_t *lds = reinterpret_cast<const uint8_t *>(lds_v);
-    if (AES)
-        stage_ttables<WAVES * 64>(lds_v, te0g);
-    if (GH)
-        stage_key_tables<WAVES * 64>(lds_v, d.slot);
-    lds_barrier();
-    const LaneK lk = lane_constants(threadIdx.x & 63);
-    const GhK gk = gh_constants(threadIdx.x & 63);
-    const uint32_t wave = uniform(threadIdx.x >> 6);
-    for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
-        const uint64_t t = d.tile_lo + (uint64_t)it * WAVES + wave;
-        if (t < d.tile_hi) {
-            if (d.nr == 10)
-                wave_tile_siv<10, PASS>(d, t, lds, lk, gk, te0g, partials);
-            else
-                wave_tile_siv<14, PASS>(d, t, lds, lk, gk, te0g, partials);
-        }
-    }
-}
-
 // ---------------------------------------------------------------- host-side launchers
 
 hipError_t launch_init_tables(uint32_t *te0, uint32_t *sbox, void *frob, hipStream_t s)
@@ -1911,20 +1840,14 @@ static hipError_t launch_tiles_w(const MsgDesc *descs, const WorkItem *items, ui
                                  hipStream_t s)
 {
     if (descs)
-        hipLaunchKernelGGL((k_gcm_tiles<WAVES, true, kModeGcm>), dim3(grid), dim3(WAVES * 64), 0, s, descs, items,
-                           n_items, MsgDesc{}, te0, partials, counters);
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, true, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, MsgDesc{}, descs,
+                           items, n_items, te0, partials, counters);
     else if (single->op == 2)
-        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kModeCtr>), dim3(grid), dim3(WAVES * 64), 0, s, nullptr,
-                           nullptr, n_items, *single, te0, partials, counters);
-    else if (single->j0)
-        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kModeGcmJ0>), dim3(grid), dim3(WAVES * 64), 0, s, nullptr,
-                           nullptr, n_items, *single, te0, partials, counters);
-    else if (single->aad_len >= kAadRowsMinBytes)
-        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kModeGcmAad>), dim3(grid), dim3(WAVES * 64), 0, s, nullptr,
-                           nullptr, n_items, *single, te0, partials, counters);
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kCtr>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
+                           nullptr, n_items, te0, partials, counters);
     else
-        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kModeGcm>), dim3(grid), dim3(WAVES * 64), 0, s, nullptr,
-                           nullptr, n_items, *single, te0, partials, counters);
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
+                           nullptr, n_items, te0, partials, counters);
     return hipGetLastError();
 }
 
@@ -1951,13 +1874,13 @@ int max_groups_per_cu(int waves)
     hipError_t e = hipErrorInvalidValue;
     switch (waves) {
     case 8:
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<8, false, kModeGcm>, 8 * 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<8, false, kGcm>, 8 * 64, 0);
         break;
     case 12:
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<12, false, kModeGcm>, 12 * 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<12, false, kGcm>, 12 * 64, 0);
         break;
     case 16:
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<16, false, kModeGcm>, 16 * 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gcm_tiles<16, false, kGcm>, 16 * 64, 0);
         break;
     }
     return (e == hipSuccess && n > 0) ? n : 1;
@@ -2055,16 +1978,20 @@ hipError_t launch_siv_tag(uint64_t slot, const void *g, const uint8_t nonce[12],
     return hipGetLastError();
 }
 
+// pass 0: POLYVAL (encrypt), 1: counter mode (encrypt), 2: both (decrypt-verify)
 template <int WAVES>
 static hipError_t launch_siv_tiles_w(int pass, const MsgDesc &d, uint32_t n_items, const uint32_t *te0, u32x4 *p,
                                      uint32_t grid, hipStream_t s)
 {
-    if (pass == kSivHash)
-        hipLaunchKernelGGL((k_siv_tiles<WAVES, kSivHash>), dim3(grid), dim3(WAVES * 64), 0, s, d, n_items, te0, p);
-    else if (pass == kSivCtr)
-        hipLaunchKernelGGL((k_siv_tiles<WAVES, kSivCtr>), dim3(grid), dim3(WAVES * 64), 0, s, d, n_items, te0, p);
+    if (pass == 0)
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kSivHash>), dim3(grid), dim3(WAVES * 64), 0, s, d, nullptr,
+                           nullptr, n_items, te0, p, nullptr);
+    else if (pass == 1)
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kSivCtr>), dim3(grid), dim3(WAVES * 64), 0, s, d, nullptr,
+                           nullptr, n_items, te0, p, nullptr);
     else
-        hipLaunchKernelGGL((k_siv_tiles<WAVES, kSivDec>), dim3(grid), dim3(WAVES * 64), 0, s, d, n_items, te0, p);
+        hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kSivDec>), dim3(grid), dim3(WAVES * 64), 0, s, d, nullptr,
+                           nullptr, n_items, te0, p, nullptr);
     return hipGetLastError();
 }
 
@@ -2072,7 +1999,7 @@ hipError_t launch_siv_tiles(int waves, int pass, const MsgDesc &d, uint32_t n_it
                             void *partials, uint32_t grid, hipStream_t s)
 {
     u32x4 *p = reinterpret_cast<u32x4 *>(partials);
-    if (pass < kSivHash || pass > kSivDec)
+    if (pass < 0 || pass > 2)
         return hipErrorInvalidValue;
     switch (waves) {
     case 8:

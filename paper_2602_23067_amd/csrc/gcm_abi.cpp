@@ -487,7 +487,7 @@ int gcm::launch_tile_range(gcm_ctx *ctx, const MsgDesc &d, const Shape &sh, void
     const uint32_t waves = sh.waves, gpc = sh.gpc;
     uint32_t *counters = ws ? reinterpret_cast<uint32_t *>(ws) : nullptr;
     uint8_t *partials = ws ? reinterpret_cast<uint8_t *>(ws) + workspace_counter_bytes(1) : nullptr;
-    const uint64_t tiles = d.tile_hi - d.tile_lo;
+    const uint64_t tiles = d.tile_hi - d.tile_lo - (d.n_tiles - tiles_run(d));
     const uint32_t items = (uint32_t)((tiles + waves - 1) / waves);
     if (items == 0)
         return GCM_OK;
@@ -502,12 +502,16 @@ int gcm::launch_tile_range(gcm_ctx *ctx, const MsgDesc &d, const Shape &sh, void
     return GCM_OK;
 }
 
-// Enqueue the kernels for one message on `s`: tiles, then (GCM only) the
-// combine and, for decrypt-verify, the zero-fill of a rejected output.
-int gcm::launch_single(gcm_ctx *ctx, const MsgDesc &d, const Shape &sh, void *ws, hipStream_t s)
+// Enqueue the kernels for one message on `s`: tiles, then (GCM only), unless
+// one workgroup covers the message and finishes it, the combine and, for
+// decrypt-verify, the zero-fill of a rejected output.
+int gcm::launch_single(gcm_ctx *ctx, const MsgDesc &desc, const Shape &sh, void *ws, hipStream_t s)
 {
+    MsgDesc d = desc;
+    if (d.op != 2)
+        set_groups_single(&d, sh.waves, (uint64_t)ctx->cu_count * sh.gpc);
     int rc = launch_tile_range(ctx, d, sh, ws, s);
-    if (rc || d.op == 2)
+    if (rc || d.op == 2 || (d.flags & kFinish))
         return rc;
     uint32_t *counters = reinterpret_cast<uint32_t *>(ws);
     uint8_t *partials = reinterpret_cast<uint8_t *>(ws) + workspace_counter_bytes(1);

@@ -6,9 +6,9 @@
 // partial-hash slot), and a work list of workgroup items -- `waves`
 // consecutive wave tiles of one message -- ordered by key slot so that a
 // persistent workgroup reloads its GHASH table only when the key changes.
-// Launching a plan enqueues three kernels (tiles, per-message combine,
-// zero-fill of rejected messages) and allocates nothing, so it can be
-// captured into a hipGraph and replayed.
+// Launching a plan enqueues up to three kernels (tiles; for messages of more
+// than one workgroup item a combine and the zero-fill of rejected ones) and
+// allocates nothing, so it can be captured into a hipGraph and replayed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,7 +27,7 @@ struct gcm_batch {
     uint32_t n_items = 0;
     Shape shape;
     uint32_t grid = 1;
-    bool any_decrypt = false;
+    bool any_combine = false, any_zerofill = false;
     uint64_t total_tiles = 0;
     uint64_t payload_bytes = 0;
     MsgDesc *d_descs = nullptr;
@@ -75,7 +75,8 @@ int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint
     b->n = n;
     b->shape = sh;
     b->total_tiles = plan.total_tiles;
-    b->any_decrypt = plan.any_decrypt;
+    b->any_combine = plan.any_combine;
+    b->any_zerofill = plan.any_zerofill;
     b->payload_bytes = plan.payload;
     b->n_items = (uint32_t)plan.items.size();
     b->grid = std::max<uint32_t>(1, std::min<uint32_t>(b->n_items, (uint32_t)ctx->cu_count * sh.gpc));
@@ -149,9 +150,9 @@ hipError_t gcm::batch_enqueue(gcm_batch *b, hipStream_t s)
                          counters, b->grid, s);
     if (e == hipSuccess)
         e = prof_end(ctx, s);
-    if (e == hipSuccess)
+    if (e == hipSuccess && b->any_combine)
         e = launch_combine(b->d_descs, b->n, nullptr, partials, counters, b->shape.fanin, s);
-    if (e == hipSuccess && b->any_decrypt)
+    if (e == hipSuccess && b->any_zerofill)
         e = launch_zerofill(b->d_descs, nullptr, counters, (uint32_t)std::max(1, ctx->cu_count * 4), s);
     return e;
 }

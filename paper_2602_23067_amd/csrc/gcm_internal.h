@@ -36,7 +36,16 @@ struct KeySlotHdr {
     uint32_t pad0[2];
     uint32_t h[4];                  // H = AES_K(0^128)
     uint32_t hpow[kPowLevels][4];   // H^(2^k)
+    uint32_t lift[3][17][4];        // H^(2^s * j), j = 3, 5, 7, s = 6..22
 };
+
+// Group lifts: a workgroup multiplies the value of its wave tile e places
+// before the end of a group by H^(B * e), e = 1..15.  With e = 2^z * j, j odd,
+// and B = 2^s that is H^(2^(s+z) * j): hpow for j = 1, lift for j = 3, 5, 7
+// (s + z = 6..22), and for j = 9, 11, 13, 15 (s = 6..20) the first KiB of the
+// fix-up windows, whose own entries, those of the polynomial 0, are all zero
+// and need no storage: entry (j, s) at byte 16 * (16 * (j - 9) / 2 + s - 6).
+constexpr int kLiftLo = 6, kLiftHi = 22, kLiftLevels = kLiftHi - kLiftLo + 1;
 
 constexpr uint64_t kSlotHdrBytes = 2048;
 constexpr uint64_t kTab8Bytes = 16ull * 256 * 16;             // byte-position table, 64 KiB
@@ -46,7 +55,8 @@ constexpr uint64_t kSlotTab4Off = kSlotTab8Off + kTab8Bytes;
 // Tile fix-up tables: lane l of a wave multiplies its Horner value by
 // c_l = H^(63 - l); entry (v, l) = (v * c_l) mod P for the 4-bit polynomial v
 // sits at byte 16 * (64 * v + l), as polynomial-order words (bit i of the
-// 128-bit value is the coefficient of x^i), 16 KiB in all.
+// 128-bit value is the coefficient of x^i), 16 KiB in all.  (In the slot the
+// entries of v = 0 are replaced by group lifts.)
 constexpr uint64_t kSlotLaneWinOff = kSlotTab4Off + kTab4Levels * kTab4Bytes;
 constexpr int kLanePows = 64;
 constexpr uint64_t kLaneWinBytes = 16ull * kLanePows * 16;
@@ -80,13 +90,19 @@ struct MsgDesc {
     uint32_t log2B;      // wave tile = 2^log2B blocks (>= 6)
     uint32_t nr;         // AES rounds
     uint32_t groups;     // workgroup items for this message
-    uint32_t pad0;
+    alignas(4) uint16_t log2G;  // the tile kernel leaves one partial for 2^log2G consecutive tiles, counted from the last one
+    uint16_t flags;             // kFinish, kMerge
     uint64_t j0;         // device address of J0 (16 bytes) for IVs other than 96 bits; 0: J0 = IV || 0^31 || 1
     uint32_t tag_len;    // tag bytes written (encrypt) or compared (decrypt): 16, or 15, 14, 13, 12, 8, 4
     uint32_t ctr_off;    // a streamed segment: data blocks that precede it, added to the counters
     uint64_t lift;       // with yout: the combine multiplies the segment's GHASH value by H^lift (< 2^40)
     uint64_t yout;       // the combine writes the segment's GHASH value here instead of forming a tag
 };
+
+// MsgDesc.flags.  kFinish: the message has one group, and the tile kernel forms
+// the tag (or yout) itself; no combine follows.  kMerge: tile 1's wave runs
+// tile 0 too, as one longer tile, so the launch has a tile less than n_tiles.
+constexpr uint16_t kFinish = 1, kMerge = 2;
 
 // Bytes of the fixed device scratch behind the allocation-free entry point:
 // with tiles of up to 2^16 blocks its 65774 tile partials cover every

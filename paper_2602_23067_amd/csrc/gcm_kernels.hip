@@ -439,29 +439,21 @@ __global__ __launch_bounds__(64) void k_key_setup(KeyChunk chunk, const uint32_t
 // H^(2^kStrideLevel) = H^64, the per-lane Horner multiplier of the tile
 // kernel, one byte position each.
 // a * b for one operand pair, all 64 lanes of the wave cooperating: lane i
-// contributes the terms of bits i and i+64 of a (b * x^i, b * x^(i+64)), then
-// an XOR across the wave sums them.  Every lane returns the product.
-__device__ u32x4 gf_mul_wave(u32x4 a, u32x4 b)
+// contributes the terms of bits i and i + 64 of a (b * x^i, b * x^(i + 64)),
+// folded once, then an XOR across the wave sums them.  Every lane returns the
+// product.
+__device__ __forceinline__ u32x4 gf_mul_wave(u32x4 a, u32x4 b)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t am[4] = {a.x, a.y, a.z, a.w};
     const P128 pa = mem_to_poly(am);
     const uint32_t bm[4] = {b.x, b.y, b.z, b.w};
     const P128 pb = mem_to_poly(bm);
-    P128 acc;
-    acc.lo = 0;
-    acc.hi = 0;
-    if ((pa.lo >> lane) & 1) {
-        const P128 t = poly_mul_xi(pb, lane);
-        acc.lo ^= t.lo;
-        acc.hi ^= t.hi;
-    }
-    if ((pa.hi >> lane) & 1) {
-        const P128 t = poly_mul_xi(pb, lane + 64);
-        acc.lo ^= t.lo;
-        acc.hi ^= t.hi;
-    }
-    const u32x4 r = poly_to_mem(acc);
+    const uint64_t m0 = 0ull - ((pa.lo >> lane) & 1u), m1 = 0ull - ((pa.hi >> lane) & 1u);
+    const uint64_t w0 = pb.lo << lane, w1 = (pb.hi << lane) | ((pb.lo >> 1) >> (63 - lane));
+    const uint64_t w2 = (pb.hi >> 1) >> (63 - lane);
+    const P128 t = poly_reduce(w0 & m0, (w1 & m0) ^ (w0 & m1), (w2 & m0) ^ (w1 & m1), w2 & m1);
+    const u32x4 r = poly_to_mem(t);
     return u32x4{wave_xor_u32(r.x), wave_xor_u32(r.y), wave_xor_u32(r.z), wave_xor_u32(r.w)};
 }
 
@@ -472,7 +464,10 @@ __device__ u32x4 gf_mul_wave(u32x4 a, u32x4 b)
 //                   that this table is not the launch's longest block)
 //   blocks 56..119: H^e, e = 0..63, and its 4-bit window table for the lane
 //                   l = 63 - e that multiplies by it in the tile fix-up
+//   blocks 120..149: the group lifts H^(2^s * j), four (s, j) a block
 constexpr int kTab8Blocks = 16;
+constexpr int kLiftBlocks = (7 * kLiftLevels + 3) / 4;
+constexpr int kKeyTableBlocks = kTab4Levels + kTab8Blocks + kLanePows + kLiftBlocks;
 __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
 {
     __shared__ u32x4 basis[128];  // basis[i] = M * x^i, memory order
@@ -486,16 +481,32 @@ __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
             const int lvl = b < kTab4Levels ? b : kStrideLevel;
             m_sh = u32x4{hd->hpow[lvl][0], hd->hpow[lvl][1], hd->hpow[lvl][2], hd->hpow[lvl][3]};
         }
+    } else if (b >= kTab4Levels + kTab8Blocks + kLanePows) {
+        const int q = 4 * (b - kTab4Levels - kTab8Blocks - kLanePows) + (int)uniform(tid >> 6);
+        const int row = q / kLiftLevels, lvl = kLiftLo + q % kLiftLevels, j = 2 * row + 3;
+        if (row > 6 || (row > 2 && lvl > kLiftHi - 2))
+            return;
+        u32x4 m = {0x80u, 0u, 0u, 0u};  // the field's one
+        for (int k = 0; k < 4; ++k)
+            if ((j >> k) & 1) {
+                const uint32_t *h = hd->hpow[lvl + k];
+                m = gf_mul_wave(m, u32x4{h[0], h[1], h[2], h[3]});
+            }
+        u32x4 *dst = row < 3 ? reinterpret_cast<u32x4 *>(reinterpret_cast<KeySlotHdr *>(slot)->lift[row][lvl - kLiftLo])
+                             : reinterpret_cast<u32x4 *>(slot + kSlotLaneWinOff) + 16 * (row - 3) + (lvl - kLiftLo);
+        if ((tid & 63) == 0)
+            *dst = m;
+        return;
     } else {
         // H^e as the product of H^(2^k) over the set bits of e (one wave),
-        // then thread v < 16 writes (v * H^e) mod P for lane 63 - e
+        // then thread v = 1..15 writes (v * H^e) mod P for lane 63 - e
         if (tid < 64) {
             const int e = b - kTab4Levels - kTab8Blocks;
             u32x4 m = {0x80u, 0u, 0u, 0u};  // the field's one
             for (int k = 0; k < 6; ++k)
                 if ((e >> k) & 1)
                     m = gf_mul_wave(m, u32x4{hd->hpow[k][0], hd->hpow[k][1], hd->hpow[k][2], hd->hpow[k][3]});
-            if (tid < 16) {
+            if (tid > 0 && tid < 16) {
                 const uint32_t mm[4] = {m.x, m.y, m.z, m.w};
                 const P128 pm = mem_to_poly(mm);
                 P128 t;
@@ -609,7 +620,8 @@ __device__ __forceinline__ u32x4 wave_xor_reduce(u32x4 a)
 //                      at 0x10000 + 256*e + 64*t + 4*c.
 //   [128 KiB, 144 KiB) the key's lane fix-up window tables (slot layout).
 //   [144 KiB, 148 KiB) the message's round-2 words (see CtrBlock): 16 bytes
-//                      for each value of the low counter byte.
+//                      for each value of the low counter byte; then the tile
+//                      values of a work item (two buffers of 16) and E_K(J0).
 // and of counter mode alone (132 KiB):
 //   [0, 128 KiB)       AES T-tables: entry e of table t, copy c (c = 0..31)
 //                      at 0x10000 * (t >> 1) + 256 * e + 128 * (t & 1) + 4 * c.
@@ -1030,9 +1042,10 @@ struct Kind {
     static constexpr bool aes = KIND != kSivHash;
     static constexpr bool siv = KIND == kSivHash || KIND == kSivCtr || KIND == kSivDec;
     using tables = Tables<gh>;
-    // LDS bytes: fix-up windows (GHASH passes), round-2 words, total
+    // LDS bytes: fix-up windows (GHASH passes), round-2 words, group sums, total
     static constexpr uint32_t windows = 0x20000u, round2 = gh ? 0x24000u : 0x20000u;
-    static constexpr uint32_t lds = round2 + 0x1000u;
+    static constexpr uint32_t sums = round2 + 0x1000u;
+    static constexpr uint32_t lds = sums + (gh ? 16u * (2 * 16 + 1) : 0u);
 };
 
 // the message's counter block; c1: the counter value of data block 0, cj0: of J0
@@ -1062,15 +1075,14 @@ __device__ __forceinline__ void message_counter(const CONST_AS MsgDesc *dp, cons
 // Rows [fa, fb) hold 64 whole data blocks and rows [aa, ab) 64 whole AAD
 // blocks; the others (zero padding, partial blocks, the length block) load and
 // store lane by lane.  The wave of tile 0 runs one row ahead of its tile for
-// E_K(J0), the keystream block of J0's own counter value, and leaves it after
-// the message's partials for the combine.  A streamed segment's
+// E_K(J0), the keystream block of J0's own counter value, and leaves it in LDS.  A streamed segment's
 // counters start ctr_off blocks after J0 + 1.
 // a_l = sum_r X_(64r+l) * (H^64)^(R-1-r) by Horner on lane l, then the tile's
 // value is sum_l a_l * H^(63-l).  GCM-SIV hashes byte-reversed blocks.
 template <int NR, int KIND>
-__device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t, const uint8_t *__restrict__ lds,
-                                          const typename Kind<KIND>::tables &tab, const GhK &gk,
-                                          const CONST_AS uint32_t *te, u32x4 *__restrict__ partials)
+__device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t t, bool head,
+                                           uint8_t *__restrict__ lds, const typename Kind<KIND>::tables &tab,
+                                           const GhK &gk, const CONST_AS uint32_t *te)
 {
     constexpr bool GH = Kind<KIND>::gh, SIV = Kind<KIND>::siv, AES = Kind<KIND>::aes;
     const int lane = threadIdx.x & 63;
@@ -1083,12 +1095,14 @@ __device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t
     const uint32_t log2B = dp->log2B;
     const int32_t R = (int32_t)(1u << (log2B - 6));
     const int64_t vbase = (int64_t)(t << log2B) - (int64_t)dp->z;  // GHASH index of lane 0, row 0
-    const int32_t r0 = vbase < 0 ? (int32_t)((uint64_t)(-vbase) >> 6) : 0;
+    // the first row: the head of the message starts at index 0 (which may lie
+    // in the tile before this one), any other tile at its own row 0
+    const int32_t r0 = head ? (int32_t)((-vbase) >> 6) : 0;
     const int64_t na = (int64_t)dp->na, nfull = (int64_t)(dp->len >> 4);
     // rows whose 64 blocks all lie in blocks [first, end) of the sequence
     auto whole_rows = [&](int64_t first, int64_t end, int32_t &lo, int32_t &hi) {
         const int64_t l = first - vbase, h = end - vbase - 64;  // 64 r >= l, 64 r <= h
-        const int64_t f0 = l <= 0 ? 0 : (l + 63) >> 6, f1 = h < 0 ? 0 : (h >> 6) + 1;
+        const int64_t f0 = (l + 63) >> 6, f1 = (h >> 6) + 1;
         lo = f0 > (int64_t)r0 ? (f0 < (int64_t)R ? (int32_t)f0 : R) : r0;
         hi = f1 > (int64_t)lo ? (f1 < (int64_t)R ? (int32_t)f1 : R) : lo;
     };
@@ -1126,7 +1140,7 @@ __device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t
 
     // GHASH runs one row behind: a is the Horner value without the pending row xp
     u32x4 a = {0, 0, 0, 0}, xp = {0, 0, 0, 0};
-    const bool ek = KIND == kGcm && t == 0;
+    const bool ek = KIND == kGcm && head;
     __builtin_amdgcn_s_setprio(3);
     for (int32_t r = ek ? r0 - 1 : r0; r < R;) {
         if (GH && r >= aa && r < ab) {
@@ -1158,7 +1172,7 @@ __device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t
             ++r;
             if (ekrow) {
                 if (lane == 0)
-                    partials[bp->tile_base + bp->n_tiles] = ks;
+                    *reinterpret_cast<u32x4 *>(lds + Kind<KIND>::sums + 16 * 32) = ks;
                 continue;
             }
             if (data) {
@@ -1223,12 +1237,10 @@ __device__ __forceinline__ void wave_tile(const CONST_AS MsgDesc *dp, uint64_t t
         }
     }
     if (!GH)
-        return;
+        return a;
     a = ghash_mul8(a, xp, lds, gk);
     // fix-up: a * H^(63 - lane) through the lane's window table in LDS
-    const u32x4 p = wave_xor_reduce(gf_mul_lanewin(a, lds + Kind<KIND>::windows, lane));
-    if (lane == 0)
-        partials[dp->tile_base + t] = p;
+    return wave_xor_reduce(gf_mul_lanewin(a, lds + Kind<KIND>::windows, lane));
 }
 
 // T-tables into LDS, every copy of every entry, all of a thread's loads issued
@@ -1308,7 +1320,7 @@ __device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
     for (int r = 0; r < kPerW; ++r) {
         const uint32_t q = tid + (uint32_t)(r * NT);
         if (kWin % NT == 0 || q < kWin)
-            b[r] = win[q];
+            b[r] = q < (uint32_t)kLanePows ? u32x4{0, 0, 0, 0} : win[q];  // entries of 0: the slot keeps lifts there
     }
 #pragma unroll
     for (int r = 0; r < kPerT; ++r) {
@@ -1338,6 +1350,61 @@ __device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
 //   SIV encrypt   1150 -> 1059 us, 917 -> 854 us
 // against a loop with 197 lookups, whose waits drained the LDS queue every few
 // lookups in counter mode, and with 16 copies in every pass.
+//
+// Groups: wave tile t of T stands for position t - T of the sequence of tiles
+// counted from its end, and a work item covers the tiles of WAVES consecutive
+// places of the sequence padded at its start to a multiple of 2^log2G, so its
+// groups are whole.  Each wave multiplies its tile's value by H^(B * j) for the
+// j tiles of the group after it, and one wave XORs a group's values into one
+// partial: about 1.5 us at the end of an item, where the combine of 1 GiB then
+// has 257 partials to reduce instead of 4097 (18 -> 9 us).  A message of one
+// group needs no combine at all: the same wave multiplies by H once more, adds
+// E_K(J0) and writes the tag or compares it, and clears a rejected output.
+__device__ __forceinline__ void finish_message(const CONST_AS MsgDesc *dp, u32x4 v, u32x4 ek)
+{
+    const int lane = threadIdx.x & 63;
+    const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(dp->slot));
+    const u32x4 s = gf_mul_wave(v, u32x4{hd->hpow[0][0], hd->hpow[0][1], hd->hpow[0][2], hd->hpow[0][3]});
+    if (dp->yout) {
+        if (lane == 0)
+            *gptr<u32x4>(dp->yout) = s;
+        return;
+    }
+    const u32x4 tag = s ^ ek;
+    const int tl = (int)dp->tag_len;  // T = MSB_t of the full tag
+    const uint32_t mine = byte_of(tag, lane & 15);
+    GLOBAL_AS uint8_t *dst = gptr<uint8_t>(dp->tag);
+    if (dp->op == 0) {
+        if (lane < tl)
+            dst[lane] = (uint8_t)mine;
+        return;
+    }
+    // every byte is compared, whatever the others gave
+    const uint32_t diff = lane < tl ? mine ^ dst[lane] : 0u;
+    const bool ok = __builtin_amdgcn_ballot_w64(diff != 0) == 0;
+    if (lane == 0)
+        *gptr<int32_t>(dp->ok) = ok ? 1 : 0;
+    if (ok)
+        return;
+    GLOBAL_AS uint8_t *out = gptr<uint8_t>(dp->out);
+    const uint64_t len = dp->len, nfull = len >> 4;
+    for (uint64_t j = (uint64_t)lane; j < nfull; j += 64)
+        reinterpret_cast<GLOBAL_AS u32x4 *>(out)[j] = u32x4{0, 0, 0, 0};
+    if (lane < (int)(len & 15))
+        out[nfull * 16 + (uint64_t)lane] = 0;
+}
+
+// XOR over aligned sets of n = 4, 8 or 16 lanes; every lane of a set returns it
+__device__ __forceinline__ uint32_t set_xor_u32(uint32_t x, int n)
+{
+    x ^= __builtin_amdgcn_update_dpp(0u, x, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+    x ^= __builtin_amdgcn_update_dpp(0u, x, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+    const uint32_t y = x ^ __builtin_amdgcn_update_dpp(0u, x, 0x141, 0xF, 0xF, false);  // row_half_mirror
+    x = n > 4 ? y : x;
+    const uint32_t z = x ^ __builtin_amdgcn_update_dpp(0u, x, 0x140, 0xF, 0xF, false);  // row_mirror
+    return n > 8 ? z : x;
+}
+
 template <int WAVES, bool BATCH, int KIND>
 __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const MsgDesc *__restrict__ descs,
                                                           const WorkItem *__restrict__ items, uint32_t n_items,
@@ -1346,7 +1413,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
 {
     using K = Kind<KIND>;
     __shared__ u32x4 lds_v[K::lds / 16];
-    const uint8_t *lds = reinterpret_cast<const uint8_t *>(lds_v);
+    uint8_t *lds = reinterpret_cast<uint8_t *>(lds_v);
     const CONST_AS uint32_t *te = cptr<uint32_t>(te0g);
     const int lane = threadIdx.x & 63;
     const int wave = (int)uniform(threadIdx.x >> 6);  // wave-uniform: row bookkeeping stays scalar
@@ -1360,6 +1427,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
         stage_ttables<WAVES * 64>(lds_v, te0g, (typename K::tables *)nullptr);
     uint64_t cur_slot = 0;
     uint32_t cur_msg = 0xffffffffu;
+    uint32_t turn = 0;  // items done: its low bit picks the buffer of tile values, the wave that sums rotates
     for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
         const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
         uint32_t first, msg = 0;
@@ -1393,16 +1461,67 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
             cur_msg = msg;
             lds_barrier();
         }
-        const uint64_t t = (uint64_t)first + (uint64_t)wave;
-        if (t < dp->tile_hi) {
+        // log2G and flags, one scalar load
+        const uint32_t gf = K::gh ? *(const CONST_AS uint32_t *)&dp->log2G : 0u;
+        const uint32_t log2G = gf & 0xffffu, G = 1u << log2G, merge = (gf >> 17) & 1u;
+        const bool finish = (gf >> 16) & 1u;
+        static_assert(kFinish == 1 && kMerge == 2, "bits of flags");
+        const uint64_t run = dp->n_tiles - merge;
+        int64_t t = (int64_t)first + wave - (int64_t)((0u - (uint32_t)run) & (G - 1u));
+        const bool head = t == 0;
+        u32x4 p = {0, 0, 0, 0};
+        const bool mine = t >= 0 && t < (int64_t)dp->tile_hi - (int64_t)merge;
+        t += merge;
+        if (mine) {
             const uint32_t nr = K::aes ? dp->nr : 14;
             if (nr == 10)
-                wave_tile<10, KIND>(dp, t, lds, tab, gk, te, partials);
+                p = wave_tile<10, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
             else if (nr == 12 && !K::siv)
-                wave_tile<12, KIND>(dp, t, lds, tab, gk, te, partials);
+                p = wave_tile<12, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
             else
-                wave_tile<14, KIND>(dp, t, lds, tab, gk, te, partials);
+                p = wave_tile<14, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
         }
+        if (!K::gh)
+            continue;
+        const u32x4 *ekw = lds_v + K::sums / 16 + 32;
+        const uint64_t nparts = (run + G - 1) >> log2G;
+        if (KIND == kGcm && mine && head && lane == 0)
+            partials[dp->tile_base + nparts] = *ekw;  // after the message's partials, for the combine
+        if (log2G == 0) {
+            if (mine && lane == 0)
+                partials[dp->tile_base + (uint64_t)t] = p;
+            continue;
+        }
+        const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));  // tiles of the group after this one
+        if (mine && after) {
+            const uint64_t slot = dp->slot;
+            const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(slot));
+            const uint32_t z = (uint32_t)__builtin_ctz(after), j = after >> z, at = dp->log2B - kLiftLo + z;
+            const CONST_AS uint32_t *w = j == 1  ? hd->hpow[kLiftLo + at]
+                                         : j < 9 ? hd->lift[(j - 3) >> 1][at]
+                                                 : cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotLaneWinOff)) +
+                                                       4 * (8 * (j - 9) + at);
+            p = gf_mul_wave(p, u32x4{w[0], w[1], w[2], w[3]});
+        }
+        u32x4 *sums = lds_v + K::sums / 16 + 16 * (turn & 1u);
+        if (lane == 0)
+            sums[wave] = p;
+        if (finish && dp->op == 1)
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
+        lds_barrier();
+        if (wave == (int)(turn % WAVES)) {
+            const u32x4 v = lane < WAVES ? sums[lane] : u32x4{0, 0, 0, 0};
+            const int n = (int)G;
+            const u32x4 g = {set_xor_u32(v.x, n), set_xor_u32(v.y, n), set_xor_u32(v.z, n), set_xor_u32(v.w, n)};
+            if (finish) {
+                finish_message(dp, u32x4{uniform(g.x), uniform(g.y), uniform(g.z), uniform(g.w)}, *ekw);
+            } else if (lane < WAVES && ((uint32_t)lane & (G - 1u)) == 0) {
+                const uint64_t at = ((uint64_t)first + (uint64_t)lane) >> log2G;
+                if (at < nparts)
+                    partials[dp->tile_base + at] = g;
+            }
+        }
+        ++turn;
     }
 }
 
@@ -1432,8 +1551,12 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
     __shared__ u32x4 tabs[kCombineLog2 + 2][512];  // [0]: H; [1+k]: H^(B*2^k), k = 0..10
     __shared__ u32x4 leaf[kCombineThreads];
     const MsgDesc d = BATCH ? load_const<MsgDesc>(descs + blockIdx.x) : single;
+    if (d.flags & kFinish)
+        return;  // the tile kernel has
     const uint32_t i = threadIdx.x;
-    const uint64_t T = d.n_tiles;
+    const uint64_t run = d.n_tiles - ((d.flags & kMerge) ? 1 : 0);
+    const uint64_t T = (run + (1ull << d.log2G) - 1) >> d.log2G;  // partials, of B = 2^log2B blocks each
+    const uint32_t log2B = d.log2B + d.log2G;
 
     // the first eight partials of this thread, loaded ahead of the table staging
     u32x4 pv[8];
@@ -1460,7 +1583,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
         for (int r = 0; r < kPer; ++r) {
             const int e = (int)i + r * kCombineThreads;
             const int tix = e >> 9;
-            const int lvl = tix == 0 ? 0 : (int)d.log2B + tix - 1;
+            const int lvl = tix == 0 ? 0 : (int)log2B + tix - 1;
             if (e < ntab * 512)
                 st[r] = g[(uint64_t)lvl * 512 + (e & 511)];
         }
@@ -1826,7 +1949,7 @@ hipError_t launch_key_setup(const uint8_t *const *keys, const uint32_t *key_lens
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL(k_key_tables, dim3(kTab4Levels + kTab8Blocks + kLanePows, m), dim3(256), 0, s, sc);
+        hipLaunchKernelGGL(k_key_tables, dim3(kKeyTableBlocks, m), dim3(256), 0, s, sc);
         e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -1961,7 +2084,7 @@ hipError_t launch_siv_derive(uint64_t kgk_slot, const uint8_t nonce[12], uint64_
         return e;
     SlotChunk sc{};
     sc.slots[0] = out_slot;
-    hipLaunchKernelGGL(k_key_tables, dim3(kTab4Levels + kTab8Blocks + kLanePows, 1), dim3(256), 0, s, sc);
+    hipLaunchKernelGGL(k_key_tables, dim3(kKeyTableBlocks, 1), dim3(256), 0, s, sc);
     return hipGetLastError();
 }
 

@@ -228,6 +228,39 @@ inline void fill_desc(MsgDesc *d, uint32_t op, const uint8_t *iv, uint64_t aad, 
     d->tag_len = 16;
 }
 
+// Tiles whose partials a workgroup of `waves` waves sums into one: the largest
+// power of two that divides the wave count (its groups then never straddle a
+// work item).  The sum is a product and an XOR in the tile kernel, where the
+// combine would spend a level of its tree on it: with 16 waves a 1 GiB message
+// leaves 257 partials instead of 4097.
+inline uint16_t group_log2(uint32_t waves) { return waves == 16 ? 4 : waves == 8 ? 3 : waves == 12 ? 2 : 0; }
+
+// tiles that a launch of the whole message runs, and partials it leaves
+inline uint64_t tiles_run(const MsgDesc &d) { return d.n_tiles - ((d.flags & kMerge) ? 1 : 0); }
+inline uint64_t n_partials(const MsgDesc &d) { return (tiles_run(d) + (1ull << d.log2G) - 1) >> d.log2G; }
+
+// Group the descriptor's tiles for workgroups of `waves` waves; a message of
+// one group is finished by the tile kernel if its result is wanted right then.
+inline void set_groups(MsgDesc *d, uint32_t waves, bool whole)
+{
+    d->log2G = group_log2(waves);
+    d->flags = 0;
+    if (whole && d->log2G && n_partials(*d) == 1)
+        d->flags = kFinish;
+}
+
+// One message launched alone on `slots` resident workgroups.  The planner lets
+// a message have one tile more than there are waves, because tile 0 holds the
+// zero prefix and is short; as a work item of its own it would hold up the
+// sixteen tiles of the next item of its workgroup (6 us of a 67 MB message's
+// 85), so that tile 1's wave takes it along.
+inline void set_groups_single(MsgDesc *d, uint32_t waves, uint64_t slots)
+{
+    set_groups(d, waves, true);
+    if (d->log2G && d->n_tiles > slots * waves && d->n_tiles % waves == 1)
+        d->flags |= kMerge;
+}
+
 // Device buffers of one message: NULL with a non-zero length, 16-byte
 // alignment of AAD and payload, and aliasing.  The output may equal the
 // input exactly (in place) but may not overlap it otherwise, nor overlap the
@@ -334,6 +367,8 @@ struct BatchPlan {
     uint64_t partial_slots = 0; // sum of n_tiles + 2 (the workspace's per-message part)
     uint64_t payload = 0;
     bool any_decrypt = false;
+    // messages that the tile kernel does not finish by itself, and decrypts among them
+    bool any_combine = false, any_zerofill = false;
     uint64_t workspace_bytes() const { return workspace_counter_bytes(descs.size()) + 16 * partial_slots; }
 };
 
@@ -343,13 +378,16 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
     p->descs.assign(n, MsgDesc{});
     p->items.clear();
     p->total_tiles = p->partial_slots = p->payload = 0;
-    p->any_decrypt = false;
+    p->any_decrypt = p->any_combine = p->any_zerofill = false;
     uint64_t tile_base = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const PlanMsg &j = msgs[i];
         const uint32_t log2B = batch_msg_log2B(ghash_blocks(j.aad_len, j.len), waves, cap_log2B);
         fill_desc(&p->descs[i], j.op, j.iv, j.aad, j.aad_len, j.in, j.out, j.len, j.tag, j.ok, slots.addr(j.key_slot),
                   slots.nr[j.key_slot], log2B, waves, tile_base);
+        set_groups(&p->descs[i], waves, true);
+        p->any_combine |= !(p->descs[i].flags & kFinish);
+        p->any_zerofill |= !(p->descs[i].flags & kFinish) && j.op == 1;
         tile_base += p->descs[i].n_tiles + 2;  // partials, then the E_K(J0) and J0 slots
         p->total_tiles += p->descs[i].n_tiles;
         p->any_decrypt |= j.op == 1;

@@ -57,7 +57,7 @@ uint64_t siv_tiles(const gcm_ctx *ctx, uint64_t len, uint64_t aad_len, Shape *sh
 int launch_siv_pass(gcm_ctx *ctx, int pass, const MsgDesc &d, uint32_t waves, uint32_t gpc, void *partials,
                     hipStream_t s)
 {
-    const uint32_t items = (uint32_t)((d.n_tiles + waves - 1) / waves);
+    const uint32_t items = (uint32_t)((tiles_run(d) + waves - 1) / waves);
     if (items == 0)
         return GCM_OK;
     const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(items, (uint32_t)ctx->cu_count * gpc));
@@ -119,10 +119,12 @@ int siv_common(gcm_ctx *ctx, uint32_t op, uint32_t slot, const uint8_t *nonce, s
               (uint64_t)ok_d, mslot, nr, log2B, waves, 0);
     d.j0 = (uint64_t)ctr;
     d.yout = (uint64_t)gval;
+    set_groups_single(&d, waves, (uint64_t)ctx->cu_count * gpc);
     rc = launch_siv_pass(ctx, op == 0 ? 0 : 2, d, waves, gpc, partials, s);
     if (rc)
         return rc;
-    e = launch_combine(nullptr, 1, &d, partials, counters, sh.fanin, s);
+    if (!(d.flags & kFinish))
+        e = launch_combine(nullptr, 1, &d, partials, counters, sh.fanin, s);
     if (e == hipSuccess)
         e = launch_siv_tag(mslot, gval, nonce, op == 0 ? tag_d : nullptr, ctr, op == 1 ? tag_d : nullptr, ok_d,
                            counters, ctx->d_tables, ctx->d_tables + 256, s);

@@ -503,8 +503,8 @@ int gcm::launch_tile_range(gcm_ctx *ctx, const MsgDesc &d, const Shape &sh, void
 }
 
 // Enqueue the kernels for one message on `s`: tiles, then (GCM only), unless
-// one workgroup covers the message and finishes it, the combine and, for
-// decrypt-verify, the zero-fill of a rejected output.
+// one workgroup covers the message and finishes it, the verdict, which also
+// clears a rejected output.
 int gcm::launch_single(gcm_ctx *ctx, const MsgDesc &desc, const Shape &sh, void *ws, hipStream_t s)
 {
     MsgDesc d = desc;
@@ -515,12 +515,7 @@ int gcm::launch_single(gcm_ctx *ctx, const MsgDesc &desc, const Shape &sh, void 
         return rc;
     uint32_t *counters = reinterpret_cast<uint32_t *>(ws);
     uint8_t *partials = reinterpret_cast<uint8_t *>(ws) + workspace_counter_bytes(1);
-    hipError_t e = launch_combine(nullptr, 1, &d, partials, counters, sh.fanin, s);
-    if (e == hipSuccess && d.op == 1) {
-        const uint64_t chunks = (d.len / 16 + 255) / 256;
-        const uint32_t zgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(chunks, 4096));
-        e = launch_zerofill(nullptr, &d, counters, zgrid, s);
-    }
+    hipError_t e = launch_verdict(nullptr, 1, &d, partials, counters, s);
     if (e != hipSuccess)
         return fail_hip(e, "kernel launch");
     return GCM_OK;

@@ -7,7 +7,7 @@
 // consecutive wave tiles of one message -- ordered by key slot so that a
 // persistent workgroup reloads its GHASH table only when the key changes.
 // Launching a plan enqueues up to three kernels (tiles; for messages of more
-// than one workgroup item a combine and the zero-fill of rejected ones) and
+// than one workgroup item a verdict and the zero-fill of rejected ones) and
 // allocates nothing, so it can be captured into a hipGraph and replayed.
 #include <hip/hip_runtime.h>
 
@@ -151,7 +151,7 @@ hipError_t gcm::batch_enqueue(gcm_batch *b, hipStream_t s)
     if (e == hipSuccess)
         e = prof_end(ctx, s);
     if (e == hipSuccess && b->any_combine)
-        e = launch_combine(b->d_descs, b->n, nullptr, partials, counters, b->shape.fanin, s);
+        e = launch_verdict(b->d_descs, b->n, nullptr, partials, counters, s);
     if (e == hipSuccess && b->any_zerofill)
         e = launch_zerofill(b->d_descs, nullptr, counters, (uint32_t)std::max(1, ctx->cu_count * 4), s);
     return e;

@@ -193,6 +193,11 @@ int max_groups_per_cu(int waves);
 // fanin: children per node of the reduction tree over tile partials (2, 4, 8, 16)
 hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
                           uint32_t *counters, uint32_t fanin, hipStream_t s);
+// grouped messages (MsgDesc.log2G > 0): tag or verdict from the lifted partials;
+// a single message's rejected output is cleared, a batch's rejected messages
+// are listed in `counters` for launch_zerofill
+hipError_t launch_verdict(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
+                          uint32_t *counters, hipStream_t s);
 hipError_t launch_j0(const IvArg &iv, uint64_t slot, void *j0_out, void *y_zero, hipStream_t s);
 // streamed message: XOR of k lifted segment values, the length block's term
 // lenblk * H (lenblk: memory-order words, or NULL when it is one of the

@@ -45,6 +45,9 @@ struct KeySlotHdr {
 // (s + z = 6..22), and for j = 9, 11, 13, 15 (s = 6..20) the first KiB of the
 // fix-up windows, whose own entries, those of the polynomial 0, are all zero
 // and need no storage: entry (j, s) at byte 16 * (16 * (j - 9) / 2 + s - 6).
+// Single-row tiles (B = 64) also need H^(64 e + 32), e = 0..15: entry e at byte
+// 16 e of the byte-position table of H^64, in the place of its sixteen entries
+// of the byte value 0, which are zero as well.
 constexpr int kLiftLo = 6, kLiftHi = 22, kLiftLevels = kLiftHi - kLiftLo + 1;
 
 constexpr uint64_t kSlotHdrBytes = 2048;
@@ -100,9 +103,11 @@ struct MsgDesc {
 };
 
 // MsgDesc.flags.  kFinish: the message has one group, and the tile kernel forms
-// the tag (or yout) itself; no combine follows.  kMerge: tile 1's wave runs
+// the tag (or yout) itself; no verdict follows.  kMerge: tile 1's wave runs
 // tile 0 too, as one longer tile, so the launch has a tile less than n_tiles.
-constexpr uint16_t kFinish = 1, kMerge = 2;
+// kRows: tiles of one row, run by the row kernel, whose partials hold GHASH's
+// last factor H already.
+constexpr uint16_t kFinish = 1, kMerge = 2, kRows = 4;
 
 // Bytes of the fixed device scratch behind the allocation-free entry point:
 // with tiles of up to 2^16 blocks its 65774 tile partials cover every

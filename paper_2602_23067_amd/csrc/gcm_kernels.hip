@@ -457,6 +457,28 @@ __device__ __forceinline__ u32x4 gf_mul_wave(u32x4 a, u32x4 b)
     return u32x4{wave_xor_u32(r.x), wave_xor_u32(r.y), wave_xor_u32(r.z), wave_xor_u32(r.w)};
 }
 
+// a * b + c * d, as above
+__device__ __forceinline__ u32x4 gf_mul2_wave(u32x4 a, u32x4 b, u32x4 c, u32x4 d)
+{
+    const int lane = threadIdx.x & 63;
+    uint64_t l0 = 0, l1 = 0, h0 = 0, h1 = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const u32x4 x = k ? c : a, y = k ? d : b;
+        const uint32_t xm[4] = {x.x, x.y, x.z, x.w}, ym[4] = {y.x, y.y, y.z, y.w};
+        const P128 px = mem_to_poly(xm), py = mem_to_poly(ym);
+        const uint64_t m0 = 0ull - ((px.lo >> lane) & 1u), m1 = 0ull - ((px.hi >> lane) & 1u);
+        const uint64_t w0 = py.lo << lane, w1 = (py.hi << lane) | ((py.lo >> 1) >> (63 - lane));
+        const uint64_t w2 = (py.hi >> 1) >> (63 - lane);
+        l0 ^= w0 & m0;
+        l1 ^= (w1 & m0) ^ (w0 & m1);
+        h0 ^= (w2 & m0) ^ (w1 & m1);
+        h1 ^= w2 & m1;
+    }
+    const u32x4 r = poly_to_mem(poly_reduce(l0, l1, h0, h1));
+    return u32x4{wave_xor_u32(r.x), wave_xor_u32(r.y), wave_xor_u32(r.z), wave_xor_u32(r.w)};
+}
+
 // Fixed-multiplier tables of one key (grid.y indexes the key).
 //   blocks 0..39:   nibble-position table of H^(2^b)      (fix-ups, combine tree)
 //   blocks 40..55:  byte-position table of H^64, position b - 40
@@ -464,9 +486,9 @@ __device__ __forceinline__ u32x4 gf_mul_wave(u32x4 a, u32x4 b)
 //                   that this table is not the launch's longest block)
 //   blocks 56..119: H^e, e = 0..63, and its 4-bit window table for the lane
 //                   l = 63 - e that multiplies by it in the tile fix-up
-//   blocks 120..149: the group lifts H^(2^s * j), four (s, j) a block
+//   blocks 120..153: the group lifts H^(2^s * j) and H^(64 e + 32), four a block
 constexpr int kTab8Blocks = 16;
-constexpr int kLiftBlocks = (7 * kLiftLevels + 3) / 4;
+constexpr int kLiftBlocks = (7 * kLiftLevels + 16 + 3) / 4;
 constexpr int kKeyTableBlocks = kTab4Levels + kTab8Blocks + kLanePows + kLiftBlocks;
 __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
 {
@@ -483,16 +505,21 @@ __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
         }
     } else if (b >= kTab4Levels + kTab8Blocks + kLanePows) {
         const int q = 4 * (b - kTab4Levels - kTab8Blocks - kLanePows) + (int)uniform(tid >> 6);
-        const int row = q / kLiftLevels, lvl = kLiftLo + q % kLiftLevels, j = 2 * row + 3;
-        if (row > 6 || (row > 2 && lvl > kLiftHi - 2))
+        const bool half = q < 16;  // H^(64 q + 32)
+        const int row = (q - 16) / kLiftLevels, lvl = half ? 6 : kLiftLo + (q - 16) % kLiftLevels;
+        const int j = half ? q : 2 * row + 3;
+        if (!half && (row > 6 || (row > 2 && lvl > kLiftHi - 2)))
             return;
         u32x4 m = {0x80u, 0u, 0u, 0u};  // the field's one
+        if (half)
+            m = u32x4{hd->hpow[5][0], hd->hpow[5][1], hd->hpow[5][2], hd->hpow[5][3]};
         for (int k = 0; k < 4; ++k)
             if ((j >> k) & 1) {
                 const uint32_t *h = hd->hpow[lvl + k];
                 m = gf_mul_wave(m, u32x4{h[0], h[1], h[2], h[3]});
             }
-        u32x4 *dst = row < 3 ? reinterpret_cast<u32x4 *>(reinterpret_cast<KeySlotHdr *>(slot)->lift[row][lvl - kLiftLo])
+        u32x4 *dst = half ? reinterpret_cast<u32x4 *>(slot + kSlotTab8Off) + q
+                     : row < 3 ? reinterpret_cast<u32x4 *>(reinterpret_cast<KeySlotHdr *>(slot)->lift[row][lvl - kLiftLo])
                              : reinterpret_cast<u32x4 *>(slot + kSlotLaneWinOff) + 16 * (row - 3) + (lvl - kLiftLo);
         if ((tid & 63) == 0)
             *dst = m;
@@ -539,7 +566,8 @@ __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
         for (int t = 0; t < 8; ++t)
             if ((v >> t) & 1)
                 acc ^= basis[8 * k + 7 - t];
-        tab[16 * v + k] = acc;
+        if (v)  // the entries of 0 hold lifts
+            tab[16 * v + k] = acc;
         return;
     }
     u32x4 *tab = reinterpret_cast<u32x4 *>(slot + kSlotTab4Off + (uint64_t)b * kTab4Bytes);
@@ -651,12 +679,13 @@ __device__ __forceinline__ uint32_t rotr_by(uint32_t x, uint32_t n) { return __b
 #define B2(x) (((x) >> 16) & 0xffu)
 #define B3(x) ((x) >> 24)
 
-// The T-tables in LDS as a lane sees them; ROT: 16 copies and a rotated state.
-template <bool ROT>
+// The T-tables in LDS as a lane sees them; ROT: 16 copies, from LDS byte BASE,
+// and a rotated state.
+template <bool ROT, uint32_t BASE>
 struct Tables;
 
 template <>
-struct Tables<false> {
+struct Tables<false, 0> {
     const uint8_t *lds;
     uint32_t lo, hi;  // 4 * copy, 0x10000 | 4 * copy
 
@@ -689,11 +718,11 @@ struct Tables<false> {
     }
 };
 
-template <>
-struct Tables<true> {
+template <uint32_t BASE>
+struct Tables<true, BASE> {
     const uint8_t *lds;
     uint32_t sel[4];          // v_perm selectors: byte u_r of the state word into bits 8..15
-    uint32_t off[4];          // 0x10000 | 64*u_r + 4*copy
+    uint32_t off[4];          // BASE | 64*u_r + 4*copy
     uint32_t sh;              // alignbit shift for rotl by 8g
     uint32_t fsel01, fsel23;  // last round: v_perm selectors of the S-box bytes
 
@@ -704,7 +733,7 @@ struct Tables<true> {
         for (int r = 0; r < 4; ++r) {
             const uint32_t u = ((uint32_t)r + g) & 3u;
             sel[r] = 0x0c020000u | ((4u + u) << 8);
-            off[r] = 0x10000u | (u * 64u + copy * 4u);
+            off[r] = BASE | (u * 64u + copy * 4u);
         }
         const uint32_t u0 = g & 3u, u1 = (1u + g) & 3u, u2 = (2u + g) & 3u, u3 = (3u + g) & 3u;
         // S(x) sits in byte (u+1)&3 of table u
@@ -719,7 +748,7 @@ struct Tables<true> {
     }
     __device__ __forceinline__ uint32_t entry(int t, uint32_t x) const
     {
-        return *reinterpret_cast<const uint32_t *>(lds + 0x10000 + 64 * t + (x << 8 | ((off[0] & 63u))));
+        return *reinterpret_cast<const uint32_t *>(lds + BASE + 64 * t + (x << 8 | (off[0] & 63u)));
     }
     __device__ __forceinline__ uint32_t rot(uint32_t x) const { return rotr_by(x, sh); }
     __device__ __forceinline__ uint32_t last01(uint32_t a, uint32_t b) const { return __builtin_amdgcn_perm(b, a, fsel01); }
@@ -952,12 +981,13 @@ struct CtrBlock {
 // four words of a, 256-bit accumulate with word-aligned XORs, one fold at the
 // end.  32 conflict-free ds_read_b128 (16 consecutive lanes read 16
 // different bank groups) and about 300 VALU instructions.
+template <int LANES>
 __device__ __forceinline__ u32x4 gf_mul_lanewin(u32x4 a, const uint8_t *__restrict__ wins, int lane)
 {
     const uint32_t am[4] = {a.x, a.y, a.z, a.w};
     const P128 pa = mem_to_poly(am);
     const uint32_t aw[4] = {(uint32_t)pa.lo, (uint32_t)(pa.lo >> 32), (uint32_t)pa.hi, (uint32_t)(pa.hi >> 32)};
-    const uint8_t *win = wins + 16u * (uint32_t)lane;
+    const uint8_t *win = wins + 16u * (uint32_t)(lane & (LANES - 1));
     uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int q = 7; q >= 0; --q) {
@@ -968,7 +998,7 @@ __device__ __forceinline__ u32x4 gf_mul_lanewin(u32x4 a, const uint8_t *__restri
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const uint32_t v = (aw[w] >> (4 * q)) & 15u;
-            const u32x4 t = *reinterpret_cast<const u32x4 *>(win + 1024u * v);
+            const u32x4 t = *reinterpret_cast<const u32x4 *>(win + 16u * LANES * v);
             acc[w] ^= t.x;
             acc[w + 1] ^= t.y;
             acc[w + 2] ^= t.z;
@@ -1041,7 +1071,7 @@ struct Kind {
     static constexpr bool gh = KIND == kGcm || KIND == kSivHash || KIND == kSivDec;
     static constexpr bool aes = KIND != kSivHash;
     static constexpr bool siv = KIND == kSivHash || KIND == kSivCtr || KIND == kSivDec;
-    using tables = Tables<gh>;
+    using tables = Tables<gh, gh ? 0x10000u : 0u>;
     // LDS bytes: fix-up windows (GHASH passes), round-2 words, group sums, total
     static constexpr uint32_t windows = 0x20000u, round2 = gh ? 0x24000u : 0x20000u;
     static constexpr uint32_t sums = round2 + 0x1000u;
@@ -1240,56 +1270,49 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
         return a;
     a = ghash_mul8(a, xp, lds, gk);
     // fix-up: a * H^(63 - lane) through the lane's window table in LDS
-    return wave_xor_reduce(gf_mul_lanewin(a, lds + Kind<KIND>::windows, lane));
+    return wave_xor_reduce(gf_mul_lanewin<64>(a, lds + Kind<KIND>::windows, lane));
 }
 
-// T-tables into LDS, every copy of every entry, all of a thread's loads issued
-// before its stores; the caller adds the barrier.
+// T-tables into LDS, every copy of every entry: a thread's loads, then its
+// stores (the caller does other things between them and adds the barrier).
 //
 // 32 copies: 16-byte unit i of each 64 KiB half holds four copies of entry
 // i >> 4 of table ((i >> 3) & 1), in the upper half of the table after next.
+// 16 copies: unit i of the 64 KiB holds four copies of entry i >> 4 of table
+// (i >> 2) & 3.
 template <int NT>
-__device__ __forceinline__ void stage_ttables(u32x4 *lds_v, const uint32_t *__restrict__ te0g, Tables<false> *)
-{
-    constexpr int kPer = (4096 + NT - 1) / NT;
+struct StageTables {
+    static constexpr int kPer = (4096 + NT - 1) / NT;
     uint32_t v[kPer];
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int i = (int)threadIdx.x + r * NT;
-        v[r] = i < 4096 ? te0g[i >> 4] : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int i = (int)threadIdx.x + r * NT;
-        if (i >= 4096)
-            break;
-        const uint32_t lo = (i & 8) ? rotl32(v[r], 8) : v[r];  // tables 0, 1
-        const uint32_t hi = rotr_by(lo, 16);                   // tables 2, 3
-        lds_v[i] = u32x4{lo, lo, lo, lo};
-        lds_v[4096 + i] = u32x4{hi, hi, hi, hi};
-    }
-}
 
-// 16 copies: unit i of the 64 KiB holds four copies of entry i >> 4 of table (i >> 2) & 3
-template <int NT>
-__device__ __forceinline__ void stage_ttables(u32x4 *lds_v, const uint32_t *__restrict__ te0g, Tables<true> *)
-{
-    constexpr int kPer = (4096 + NT - 1) / NT;
-    uint32_t v[kPer];
+    __device__ __forceinline__ void load(const uint32_t *__restrict__ te0g)
+    {
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int i = (int)threadIdx.x + r * NT;
-        v[r] = i < 4096 ? te0g[i >> 4] : 0u;
+        for (int r = 0; r < kPer; ++r) {
+            const int i = (int)threadIdx.x + r * NT;
+            v[r] = i < 4096 ? te0g[i >> 4] : 0u;
+        }
     }
+    template <bool ROT, uint32_t BASE>
+    __device__ __forceinline__ void store(u32x4 *lds_v, const Tables<ROT, BASE> &) const
+    {
 #pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int i = (int)threadIdx.x + r * NT;
-        if (i >= 4096)
-            break;
-        const uint32_t x = rotr_by(v[r], (32u - 8u * ((uint32_t)(i >> 2) & 3u)) & 31u);
-        lds_v[4096 + i] = u32x4{x, x, x, x};
+        for (int r = 0; r < kPer; ++r) {
+            const int i = (int)threadIdx.x + r * NT;
+            if (i >= 4096)
+                break;
+            if (ROT) {
+                const uint32_t x = rotr_by(v[r], (32u - 8u * ((uint32_t)(i >> 2) & 3u)) & 31u);
+                lds_v[BASE / 16 + i] = u32x4{x, x, x, x};
+            } else {
+                const uint32_t lo = (i & 8) ? rotl32(v[r], 8) : v[r];  // tables 0, 1
+                const uint32_t hi = rotr_by(lo, 16);                   // tables 2, 3
+                lds_v[i] = u32x4{lo, lo, lo, lo};
+                lds_v[4096 + i] = u32x4{hi, hi, hi, hi};
+            }
+        }
     }
-}
+};
 
 // The key's GHASH table of H^64 (64 KiB, LDS bytes [0, 64 KiB)) and its
 // lane fix-up windows (16 KiB, LDS bytes [128 KiB, 144 KiB)) from the key
@@ -1314,7 +1337,7 @@ __device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
     for (int r = 0; r < kPerT; ++r) {
         const uint32_t q = tid + (uint32_t)(r * NT);
         if (kTab % NT == 0 || q < kTab)
-            a[r] = tab[q];
+            a[r] = q < 16 ? u32x4{0, 0, 0, 0} : tab[q];  // entries of 0: the slot keeps lifts there
     }
 #pragma unroll
     for (int r = 0; r < kPerW; ++r) {
@@ -1355,16 +1378,20 @@ __device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
 // counted from its end, and a work item covers the tiles of WAVES consecutive
 // places of the sequence padded at its start to a multiple of 2^log2G, so its
 // groups are whole.  Each wave multiplies its tile's value by H^(B * j) for the
-// j tiles of the group after it, and one wave XORs a group's values into one
-// partial: about 1.5 us at the end of an item, where the combine of 1 GiB then
-// has 257 partials to reduce instead of 4097 (18 -> 9 us).  A message of one
-// group needs no combine at all: the same wave multiplies by H once more, adds
-// E_K(J0) and writes the tag or compares it, and clears a rejected output.
-__device__ __forceinline__ void finish_message(const CONST_AS MsgDesc *dp, u32x4 v, u32x4 ek)
+// j tiles of the group after it, and one wave XORs a group's values and lifts
+// the sum past the groups after it: about 2 us at the end of an item, for which
+// the tree over 4097 partials that followed 1 GiB (18 us) becomes an XOR of 256
+// (2.4 us).  A message of one group needs nothing at all after the tiles:
+// the same wave multiplies by H once more, adds E_K(J0) and writes the tag or
+// compares it, and clears a rejected output.
+__device__ __forceinline__ void finish_message(const CONST_AS MsgDesc *dp, u32x4 v, u32x4 ek, bool times_h)
 {
     const int lane = threadIdx.x & 63;
-    const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(dp->slot));
-    const u32x4 s = gf_mul_wave(v, u32x4{hd->hpow[0][0], hd->hpow[0][1], hd->hpow[0][2], hd->hpow[0][3]});
+    u32x4 s = v;
+    if (times_h) {
+        const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(dp->slot));
+        s = gf_mul_wave(v, u32x4{hd->hpow[0][0], hd->hpow[0][1], hd->hpow[0][2], hd->hpow[0][3]});
+    }
     if (dp->yout) {
         if (lane == 0)
             *gptr<u32x4>(dp->yout) = s;
@@ -1405,6 +1432,67 @@ __device__ __forceinline__ uint32_t set_xor_u32(uint32_t x, int n)
     return n > 8 ? z : x;
 }
 
+// H^(B * e) for B = 2^log2B, 1 <= e <= 15 (uniform), from the slot
+__device__ __forceinline__ u32x4 group_lift(uint64_t slot, uint32_t log2B, uint32_t e)
+{
+    const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(slot));
+    const uint32_t z = (uint32_t)__builtin_ctz(e), j = e >> z, at = log2B - kLiftLo + z;
+    const CONST_AS uint32_t *w = j == 1  ? hd->hpow[kLiftLo + at]
+                                 : j < 9 ? hd->lift[(j - 3) >> 1][at]
+                                         : cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotLaneWinOff)) +
+                                               4 * (8 * (j - 9) + at);
+    return u32x4{w[0], w[1], w[2], w[3]};
+}
+
+// v * H^(2^s * e) (e uniform), by digits of four bits while the slot has their
+// powers, then by bits
+__device__ __forceinline__ u32x4 lift_by(u32x4 v, uint64_t slot, uint32_t s, uint64_t e)
+{
+    const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(slot));
+#pragma unroll 1
+    for (; e; ) {
+        const bool digit = s <= (uint32_t)kLiftHi - 2;
+        const uint32_t d = (uint32_t)e & (digit ? 15u : 1u);
+        if (d)
+            v = gf_mul_wave(v, digit ? group_lift(slot, s, d)
+                                     : u32x4{hd->hpow[s][0], hd->hpow[s][1], hd->hpow[s][2], hd->hpow[s][3]});
+        e >>= digit ? 4 : 1;
+        s += digit ? 4 : 1;
+    }
+    return v;
+}
+
+// One wave: the WAVES tile values in `sums`, in groups of G lanes, to the
+// message's partials, each multiplied by H^(blocks of the groups after it) so
+// that the verdict is their XOR; or, for a message of one group, to its tag.
+template <int WAVES>
+__device__ __forceinline__ void sum_groups(const CONST_AS MsgDesc *dp, const u32x4 *sums, const u32x4 *ekw, uint32_t G,
+                                           uint32_t log2G, bool finish, bool times_h, uint32_t first, uint64_t nparts,
+                                           u32x4 *__restrict__ partials)
+{
+    const int lane = threadIdx.x & 63, n = (int)G;
+    const u32x4 v = lane < WAVES ? sums[lane] : u32x4{0, 0, 0, 0};
+    const u32x4 g = {set_xor_u32(v.x, n), set_xor_u32(v.y, n), set_xor_u32(v.z, n), set_xor_u32(v.w, n)};
+    if (finish) {
+        finish_message(dp, u32x4{uniform(g.x), uniform(g.y), uniform(g.z), uniform(g.w)}, *ekw, times_h);
+        return;
+    }
+    const uint64_t slot = dp->slot, base = dp->tile_base;
+    const uint32_t s = dp->log2B + log2G;
+#pragma unroll 1
+    for (uint32_t w = 0; w < WAVES; w += G) {
+        const uint64_t at = ((uint64_t)first + w) >> log2G;
+        if (at >= nparts)
+            break;
+        const int l = (int)w;
+        const u32x4 y = {(uint32_t)__builtin_amdgcn_readlane(g.x, l), (uint32_t)__builtin_amdgcn_readlane(g.y, l),
+                         (uint32_t)__builtin_amdgcn_readlane(g.z, l), (uint32_t)__builtin_amdgcn_readlane(g.w, l)};
+        const u32x4 p = lift_by(y, slot, s, nparts - 1 - at);
+        if (lane == 0)
+            partials[base + at] = p;
+    }
+}
+
 template <int WAVES, bool BATCH, int KIND>
 __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const MsgDesc *__restrict__ descs,
                                                           const WorkItem *__restrict__ items, uint32_t n_items,
@@ -1423,8 +1511,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
     if (KIND == kGcm && blockIdx.x == 0 && threadIdx.x == 0)
         counters[0] = 0;  // reject count for this launch (read by the zero-fill)
 
-    if (K::aes)
-        stage_ttables<WAVES * 64>(lds_v, te0g, (typename K::tables *)nullptr);
+    if (K::aes) {
+        StageTables<WAVES * 64> st;
+        st.load(te0g);
+        st.store(lds_v, tab);
+    }
     uint64_t cur_slot = 0;
     uint32_t cur_msg = 0xffffffffu;
     uint32_t turn = 0;  // items done: its low bit picks the buffer of tile values, the wave that sums rotates
@@ -1493,36 +1584,299 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
             continue;
         }
         const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));  // tiles of the group after this one
-        if (mine && after) {
-            const uint64_t slot = dp->slot;
-            const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(slot));
-            const uint32_t z = (uint32_t)__builtin_ctz(after), j = after >> z, at = dp->log2B - kLiftLo + z;
-            const CONST_AS uint32_t *w = j == 1  ? hd->hpow[kLiftLo + at]
-                                         : j < 9 ? hd->lift[(j - 3) >> 1][at]
-                                                 : cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotLaneWinOff)) +
-                                                       4 * (8 * (j - 9) + at);
-            p = gf_mul_wave(p, u32x4{w[0], w[1], w[2], w[3]});
-        }
+        if (mine && after)
+            p = gf_mul_wave(p, group_lift(dp->slot, dp->log2B, after));
         u32x4 *sums = lds_v + K::sums / 16 + 16 * (turn & 1u);
         if (lane == 0)
             sums[wave] = p;
         if (finish && dp->op == 1)
             __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
         lds_barrier();
-        if (wave == (int)(turn % WAVES)) {
-            const u32x4 v = lane < WAVES ? sums[lane] : u32x4{0, 0, 0, 0};
-            const int n = (int)G;
-            const u32x4 g = {set_xor_u32(v.x, n), set_xor_u32(v.y, n), set_xor_u32(v.z, n), set_xor_u32(v.w, n)};
-            if (finish) {
-                finish_message(dp, u32x4{uniform(g.x), uniform(g.y), uniform(g.z), uniform(g.w)}, *ekw);
-            } else if (lane < WAVES && ((uint32_t)lane & (G - 1u)) == 0) {
-                const uint64_t at = ((uint64_t)first + (uint64_t)lane) >> log2G;
-                if (at < nparts)
-                    partials[dp->tile_base + at] = g;
-            }
-        }
+        if (wave == (int)(turn % WAVES))
+            sum_groups<WAVES>(dp, sums, ekw, G, log2G, finish, true, first, nparts, partials);
         ++turn;
     }
+}
+
+// ---------------------------------------------------------------- one row per wave
+//
+// Messages whose tiles are single rows (up to 4 MiB: every row of the message
+// has a wave of its own).  What counts is the length of the chain from the
+// launch to the tag, and a good part of that is fetching instructions that run
+// once: a launch starts with a cold instruction cache, and the unrolled rounds
+// of the tile kernel took 3 us for one row where the same row takes 1 us in a
+// loop.  So the rounds and the fix-up are loops here, the round count is a
+// variable, and no counter mode caching is done (the chain of scalar loads
+// behind it took longer than the 27 lookups it saves).  The payload, the
+// T-tables and the fix-up windows are all requested before anything is waited
+// for.  No wave has a Horner step to do, so the 64 KiB GHASH table is not staged.
+// E_K(J0) is the keystream block of the lane before the first data block, whose
+// counter is J0's own; only when that lane does not exist (no AAD, no padding)
+// does the first wave run a row for it.
+//
+// The fix-up takes windows of H^(32 - n), n = lane & 31 (8 KiB), which includes
+// GHASH's last factor H: the lower half-wave's sum has 32 more places to go,
+// which its product with the group lift takes along.
+//   [0, 64 KiB) T-tables, 16 copies; [64 KiB, 72 KiB) windows, entry (v, n) at
+//   byte 16 * (32 v + n); then the row values and E_K(J0)
+// 1 MiB, AES-128, one-shot: 39.3 us with the tile kernel (10.8 us) and a tree
+// over 1027 partials (11.8 us), 29.0 us with this one (9.4 us, half of it the
+// staging) and the verdict (2.4 us).
+constexpr uint32_t kRowWin = 0x10000u, kRowSums = 0x12000u;
+
+template <int WAVES, int KIND>
+__global__ __launch_bounds__(WAVES * 64) void k_gcm_rows(MsgDesc single, const uint32_t *__restrict__ te0g,
+                                                         u32x4 *__restrict__ partials, uint32_t *counters)
+{
+    constexpr bool SIV = Kind<KIND>::siv, AES = Kind<KIND>::aes;
+    constexpr int NT = WAVES * 64, kWinPer = (512 + NT - 1) / NT;
+    __shared__ u32x4 lds_v[kRowSums / 16 + 17];
+    uint8_t *lds = reinterpret_cast<uint8_t *>(lds_v);
+    StageTables<NT> st;
+    if (AES)
+        st.load(te0g);
+    const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
+    const int lane = threadIdx.x & 63;
+    const int wave = (int)uniform(threadIdx.x >> 6);
+    const uint64_t slot = dp->slot, T = dp->n_tiles;
+    u32x4 win[kWinPer];
+    {
+        const GLOBAL_AS u32x4 *src = gptr<const u32x4>(slot + kSlotLaneWinOff);
+#pragma unroll
+        for (int r = 0; r < kWinPer; ++r) {
+            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+            win[r] = q >= 32 && q < 512 ? src[64 * (q >> 5) + 31 + (q & 31)] : u32x4{0, 0, 0, 0};
+        }
+    }
+    const uint32_t gf = *(const CONST_AS uint32_t *)&dp->log2G;
+    const uint32_t log2G = gf & 0xffffu, G = 1u << log2G;
+    const bool finish = (gf >> 16) & 1u;
+    const uint32_t first = blockIdx.x * WAVES;
+    const int64_t t = (int64_t)first + wave - (int64_t)((0u - (uint32_t)T) & (G - 1u));
+    const bool mine = t >= 0 && t < (int64_t)T;
+
+    // this lane's block of the sequence and its bytes
+    const int64_t na = (int64_t)dp->na, ndat = (int64_t)dp->n;
+    const int64_t v0 = 64 * t - (int64_t)dp->z, v = v0 + lane;
+    const bool data = mine && v >= na && v < na + ndat;
+    const uint64_t j = (uint64_t)(v - na);
+    u32x4 x = {0, 0, 0, 0};
+    if (mine && v == na + ndat) {
+        const uint64_t abits = dp->aad_len * 8, cbits = dp->len * 8;
+        x = SIV ? u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)cbits, (uint32_t)(cbits >> 32)}
+                : u32x4{bswap32((uint32_t)(abits >> 32)), bswap32((uint32_t)abits), bswap32((uint32_t)(cbits >> 32)),
+                        bswap32((uint32_t)cbits)};
+    } else if (mine && v >= 0 && v < na + ndat) {  // data or AAD
+        x = load_block_partial(data ? gptr<const uint8_t>(dp->in) : gptr<const uint8_t>(dp->aad),
+                               data ? j : (uint64_t)v, data ? dp->len : dp->aad_len);
+    }
+
+    // the lifts of this row's value, and of its lower half (32 places more)
+    const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));
+    u32x4 lift = {0x80u, 0, 0, 0};
+    if (after)
+        lift = group_lift(slot, 6, after);
+    const CONST_AS uint32_t *l32 = cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotTab8Off)) + 4 * after;
+    const u32x4 lift32 = {l32[0], l32[1], l32[2], l32[3]};
+
+    // the counter block, whitened; the counter dword is the lane's
+    const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(slot));
+    const uint32_t nr = dp->nr;
+    uint32_t w0 = dp->iv[0], w1 = dp->iv[1], w2 = dp->iv[2], cj0 = 1u;
+    const uint64_t jaddr = dp->j0;
+    if (SIV || jaddr) {
+        const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
+        w0 = jw[SIV ? 1 : 0], w1 = jw[SIV ? 2 : 1], w2 = jw[SIV ? 3 : 2];
+        cj0 = SIV ? jw[0] : bswap32(jw[3]);
+    }
+    const uint32_t c1 = SIV ? cj0 : cj0 + 1u;
+    const bool hot = AES && mine && v0 + 64 > na - 1 && v0 < na + ndat;  // E_K(J0) or a data block in this row
+    const bool ekrow = KIND == kGcm && mine && t == 0 && dp->z == 0 && na == 0;
+
+    const Tables<true, 0> tab(lds, lane);
+    if (AES)
+        st.store(lds_v, tab);
+#pragma unroll
+    for (int r = 0; r < kWinPer; ++r) {
+        const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+        if (512 % NT == 0 || q < 512)
+            lds_v[kRowWin / 16 + q] = win[r];
+    }
+    if (KIND == kGcm && blockIdx.x == 0 && threadIdx.x == 0)
+        counters[0] = 0;  // reject count for this launch
+    lds_barrier();
+
+    u32x4 *ekw = lds_v + kRowSums / 16 + 16;
+#pragma unroll 1
+    for (int pass = ekrow ? 0 : 1; AES && pass < 2; ++pass) {
+        if (pass && !hot)
+            break;
+        const uint32_t ctr = pass ? (uint32_t)(v0 - na) + c1 + (uint32_t)lane : cj0;
+        uint32_t s0 = (SIV ? ctr : w0) ^ rk[0], s1 = (SIV ? w0 : w1) ^ rk[1], s2 = (SIV ? w1 : w2) ^ rk[2];
+        uint32_t s3 = (SIV ? w2 : bswap32(ctr)) ^ rk[3];
+        s0 = tab.rot(s0), s1 = tab.rot(s1), s2 = tab.rot(s2), s3 = tab.rot(s3);
+        const CONST_AS uint32_t *k = rk + 4;
+        uint32_t k0 = k[0], k1 = k[1], k2 = k[2], k3 = k[3];
+        uint32_t a[4][4];
+#pragma unroll 1
+        for (uint32_t r = 1;; ++r) {
+            ISSUE0(a, s0);
+            ISSUE1(a, s1);
+            ISSUE2(a, s2);
+            ISSUE3(a, s3);
+            if (r == nr)
+                break;
+            k += 4;  // the next round's key (the one after the last round key is never used)
+            const uint32_t n0 = k[0], n1 = k[1], n2 = k[2], n3 = k[3];
+            s0 = xor3(xor3(a[0][0], a[0][1], a[0][2]), a[0][3], tab.rot(k0));
+            s1 = xor3(xor3(a[1][0], a[1][1], a[1][2]), a[1][3], tab.rot(k1));
+            s2 = xor3(xor3(a[2][0], a[2][1], a[2][2]), a[2][3], tab.rot(k2));
+            s3 = xor3(xor3(a[3][0], a[3][1], a[3][2]), a[3][3], tab.rot(k3));
+            k0 = n0, k1 = n1, k2 = n2, k3 = n3;
+        }
+#define LAST(q, key)                                                                                                   \
+    (uint32_t)__builtin_amdgcn_bitop3_b32(tab.last01(a[q][q], a[q][((q) + 1) & 3]), tab.last23(a[q][((q) + 2) & 3], a[q][((q) + 3) & 3]), key, 0x56)
+        const u32x4 ks = {LAST(0, k0), LAST(1, k1), LAST(2, k2), LAST(3, k3)};
+#undef LAST
+        if (KIND == kGcm && (pass ? v == na - 1 : lane == 0)) {
+            *ekw = ks;
+            partials[dp->tile_base + ((T + G - 1) >> log2G)] = ks;
+        }
+        if (pass && data) {
+            const u32x4 o = x ^ ks;
+            store_block_partial(gptr<uint8_t>(dp->out), j, dp->len, o);
+            x = (SIV || dp->op == 0) ? mask_block(o, j, dp->len) : x;
+        }
+    }
+    if (SIV)
+        x = rev_block(x);
+
+    // x * H^(32 - n): the comb of gf_mul_lanewin in a loop, entries one step ahead
+    u32x4 y;
+    {
+        const uint32_t xm[4] = {x.x, x.y, x.z, x.w};
+        const P128 px = mem_to_poly(xm);
+        uint32_t aw[4] = {(uint32_t)px.lo, (uint32_t)(px.lo >> 32), (uint32_t)px.hi, (uint32_t)(px.hi >> 32)};
+        const uint8_t *base = lds + kRowWin + 16u * ((uint32_t)lane & 31u);
+        uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        u32x4 e[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            e[w] = *reinterpret_cast<const u32x4 *>(base + 512u * (aw[w] >> 28));
+#pragma unroll 1
+        for (int q = 0; q < 8; ++q) {
+            u32x4 f[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                f[w] = e[w];
+                aw[w] <<= 4;
+                e[w] = *reinterpret_cast<const u32x4 *>(base + 512u * (aw[w] >> 28));
+            }
+#pragma unroll
+            for (int i = 7; i > 0; --i)
+                acc[i] = __builtin_amdgcn_alignbit(acc[i], acc[i - 1], 28);  // acc <<= 4
+            acc[0] <<= 4;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                acc[w] ^= f[w].x;
+                acc[w + 1] ^= f[w].y;
+                acc[w + 2] ^= f[w].z;
+                acc[w + 3] ^= f[w].w;
+            }
+        }
+        y = poly_to_mem(poly_reduce((uint64_t)acc[0] | ((uint64_t)acc[1] << 32), (uint64_t)acc[2] | ((uint64_t)acc[3] << 32),
+                                    (uint64_t)acc[4] | ((uint64_t)acc[5] << 32), (uint64_t)acc[6] | ((uint64_t)acc[7] << 32)));
+    }
+    u32x4 lo, hi;  // sums of the lower and the upper half-wave
+    {
+        const uint32_t w[4] = {half_wave_xor_u32(y.x), half_wave_xor_u32(y.y), half_wave_xor_u32(y.z),
+                               half_wave_xor_u32(y.w)};
+        const auto q0 = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
+        const auto q1 = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
+        const auto q2 = __builtin_amdgcn_permlane32_swap(w[2], w[2], false, false);
+        const auto q3 = __builtin_amdgcn_permlane32_swap(w[3], w[3], false, false);
+        lo = u32x4{q0[0], q1[0], q2[0], q3[0]};
+        hi = u32x4{q0[1], q1[1], q2[1], q3[1]};
+    }
+    const u32x4 p = gf_mul2_wave(lo, lift32, hi, lift);
+    u32x4 *sums = lds_v + kRowSums / 16;
+    if (lane == 0)
+        sums[wave] = p;
+    if (finish && dp->op == 1)
+        __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
+    lds_barrier();
+    if (wave == 0)
+        sum_groups<WAVES>(dp, sums, ekw, G, log2G, finish, false, first, (T + G - 1) >> log2G, partials);
+}
+
+// ---------------------------------------------------------------- verdict
+
+// A grouped message's tag: the XOR of its partials (already lifted), times H
+// where they do not hold that factor, XOR E_K(J0).  Encrypt writes the tag;
+// decrypt compares it without early exit and writes the accept flag.  A batch
+// has one workgroup per message and leaves rejected messages in the list that
+// k_gcm_zerofill reads; a single message has as many workgroups as clearing
+// its output takes, each of which forms the verdict by itself.
+template <bool BATCH>
+__global__ __launch_bounds__(256) void k_gcm_verdict(MsgDesc single, const MsgDesc *__restrict__ descs,
+                                                     const u32x4 *__restrict__ partials, uint32_t *counters)
+{
+    __shared__ u32x4 sh[4];
+    const CONST_AS MsgDesc *dp = BATCH ? cptr<MsgDesc>(descs + blockIdx.x)
+                                       : (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint32_t gf = *(const CONST_AS uint32_t *)&dp->log2G, log2G = gf & 0xffffu, flags = gf >> 16;
+    if (flags & kFinish)
+        return;  // the tile kernel has
+    const int lane = threadIdx.x & 63, wave = (int)uniform(threadIdx.x >> 6);
+    const uint64_t run = dp->n_tiles - ((flags & kMerge) ? 1 : 0), P = (run + (1ull << log2G) - 1) >> log2G;
+    const u32x4 *part = partials + dp->tile_base;
+    const u32x4 ek = part[P];
+    u32x4 s = {0, 0, 0, 0};
+    for (uint64_t i = threadIdx.x; i < P; i += 256)
+        s ^= part[i];
+    s = wave_xor_reduce(s);
+    if (lane == 0)
+        sh[wave] = s;
+    lds_barrier();
+    s = sh[0] ^ sh[1] ^ sh[2] ^ sh[3];
+    if (!(flags & kRows)) {
+        const CONST_AS KeySlotHdr *hd = cptr<KeySlotHdr>(reinterpret_cast<const void *>(dp->slot));
+        s = gf_mul_wave(s, u32x4{hd->hpow[0][0], hd->hpow[0][1], hd->hpow[0][2], hd->hpow[0][3]});
+    }
+    const bool lead = (BATCH || blockIdx.x == 0) && threadIdx.x == 0;
+    if (dp->yout) {
+        if (lead)
+            *gptr<u32x4>(dp->yout) = s;
+        return;
+    }
+    const u32x4 tag = s ^ ek;
+    const int tl = (int)dp->tag_len;  // T = MSB_t of the full tag
+    const uint32_t mine = byte_of(tag, lane & 15);
+    GLOBAL_AS uint8_t *dst = gptr<uint8_t>(dp->tag);
+    if (dp->op == 0) {
+        if (wave == 0 && lane < tl)
+            dst[lane] = (uint8_t)mine;
+        return;
+    }
+    const uint32_t diff = lane < tl ? mine ^ dst[lane] : 0u;
+    const bool ok = __builtin_amdgcn_ballot_w64(diff != 0) == 0;
+    if (lead)
+        *gptr<int32_t>(dp->ok) = ok ? 1 : 0;
+    if (ok)
+        return;
+    if (BATCH) {
+        if (lead) {
+            const uint32_t pos = atomicAdd(&counters[0], 1u);
+            counters[1 + pos] = blockIdx.x;
+        }
+        return;
+    }
+    GLOBAL_AS uint8_t *out = gptr<uint8_t>(dp->out);
+    const uint64_t len = dp->len, nfull = len >> 4, stride = (uint64_t)gridDim.x * 256;
+    for (uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x; q < nfull; q += stride)
+        __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, reinterpret_cast<GLOBAL_AS u32x4 *>(out) + q);
+    if (blockIdx.x == 0 && threadIdx.x < (len & 15))
+        out[nfull * 16 + threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------- combine + tag
@@ -1551,12 +1905,8 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
     __shared__ u32x4 tabs[kCombineLog2 + 2][512];  // [0]: H; [1+k]: H^(B*2^k), k = 0..10
     __shared__ u32x4 leaf[kCombineThreads];
     const MsgDesc d = BATCH ? load_const<MsgDesc>(descs + blockIdx.x) : single;
-    if (d.flags & kFinish)
-        return;  // the tile kernel has
     const uint32_t i = threadIdx.x;
-    const uint64_t run = d.n_tiles - ((d.flags & kMerge) ? 1 : 0);
-    const uint64_t T = (run + (1ull << d.log2G) - 1) >> d.log2G;  // partials, of B = 2^log2B blocks each
-    const uint32_t log2B = d.log2B + d.log2G;
+    const uint64_t T = d.n_tiles;
 
     // the first eight partials of this thread, loaded ahead of the table staging
     u32x4 pv[8];
@@ -1583,7 +1933,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
         for (int r = 0; r < kPer; ++r) {
             const int e = (int)i + r * kCombineThreads;
             const int tix = e >> 9;
-            const int lvl = tix == 0 ? 0 : (int)log2B + tix - 1;
+            const int lvl = tix == 0 ? 0 : (int)d.log2B + tix - 1;
             if (e < ntab * 512)
                 st[r] = g[(uint64_t)lvl * 512 + (e & 511)];
         }
@@ -1968,6 +2318,9 @@ static hipError_t launch_tiles_w(const MsgDesc *descs, const WorkItem *items, ui
     else if (single->op == 2)
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kCtr>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
                            nullptr, n_items, te0, partials, counters);
+    else if (single->flags & kRows)
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, kGcm>), dim3(n_items), dim3(WAVES * 64), 0, s, *single, te0, partials,
+                           counters);
     else
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
                            nullptr, n_items, te0, partials, counters);
@@ -2044,6 +2397,24 @@ hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *
     return hipGetLastError();
 }
 
+hipError_t launch_verdict(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
+                          uint32_t *counters, hipStream_t s)
+{
+    const u32x4 *p = reinterpret_cast<const u32x4 *>(partials);
+    if (descs) {
+        hipLaunchKernelGGL(k_gcm_verdict<true>, dim3(n_msgs), dim3(256), 0, s, MsgDesc{}, descs, p, counters);
+    } else {
+        // decrypt: enough workgroups to clear a rejected output at the memory's rate
+        uint32_t grid = 1;
+        if (single->op == 1 && !single->yout) {
+            const uint64_t chunks = (single->len / 16 + 255) / 256;
+            grid = (uint32_t)(chunks < 1 ? 1 : chunks < 1024 ? chunks : 1024);
+        }
+        hipLaunchKernelGGL(k_gcm_verdict<false>, dim3(grid), dim3(256), 0, s, *single, nullptr, p, counters);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_fold(const void *vals, uint32_t k, const void *ekj0, uint8_t *tag, int32_t *ok, uint32_t op,
                        uint32_t tag_len, uint64_t slot, const uint32_t lenblk[4], hipStream_t s)
 {
@@ -2106,7 +2477,11 @@ template <int WAVES>
 static hipError_t launch_siv_tiles_w(int pass, const MsgDesc &d, uint32_t n_items, const uint32_t *te0, u32x4 *p,
                                      uint32_t grid, hipStream_t s)
 {
-    if (pass == 0)
+    if (pass == 0 && (d.flags & kRows))
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, kSivHash>), dim3(n_items), dim3(WAVES * 64), 0, s, d, te0, p, nullptr);
+    else if (pass == 2 && (d.flags & kRows))
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, kSivDec>), dim3(n_items), dim3(WAVES * 64), 0, s, d, te0, p, nullptr);
+    else if (pass == 0)
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kSivHash>), dim3(grid), dim3(WAVES * 64), 0, s, d, nullptr,
                            nullptr, n_items, te0, p, nullptr);
     else if (pass == 1)

@@ -254,11 +254,15 @@ inline void set_groups(MsgDesc *d, uint32_t waves, bool whole)
 // zero prefix and is short; as a work item of its own it would hold up the
 // sixteen tiles of the next item of its workgroup (6 us of a 67 MB message's
 // 85), so that tile 1's wave takes it along.
+// Tiles of one row go to the row kernel, as long as every workgroup is resident
+// at once (it stages the AES tables in each).
 inline void set_groups_single(MsgDesc *d, uint32_t waves, uint64_t slots)
 {
     set_groups(d, waves, true);
     if (d->log2G && d->n_tiles > slots * waves && d->n_tiles % waves == 1)
         d->flags |= kMerge;
+    else if (d->log2G && d->log2B == 6 && d->n_tiles <= slots * waves)
+        d->flags |= kRows;
 }
 
 // Device buffers of one message: NULL with a non-zero length, 16-byte

@@ -202,7 +202,7 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
         e = launch_tiles((int)sh.waves, d_desc, d_item, (uint32_t)n_items, nullptr, ctx->d_tables, partials, counters,
                          grid, sl.stream);
     if (e == hipSuccess && plan.any_combine)
-        e = launch_combine(d_desc, n, nullptr, partials, counters, sh.fanin, sl.stream);
+        e = launch_verdict(d_desc, n, nullptr, partials, counters, sl.stream);
     if (e == hipSuccess && plan.any_zerofill)
         e = launch_zerofill(d_desc, nullptr, counters, (uint32_t)std::max(1, ctx->cu_count * 2), sl.stream);
     if (e == hipSuccess && plan.any_decrypt)

@@ -124,7 +124,7 @@ int siv_common(gcm_ctx *ctx, uint32_t op, uint32_t slot, const uint8_t *nonce, s
     if (rc)
         return rc;
     if (!(d.flags & kFinish))
-        e = launch_combine(nullptr, 1, &d, partials, counters, sh.fanin, s);
+        e = launch_verdict(nullptr, 1, &d, partials, counters, s);
     if (e == hipSuccess)
         e = launch_siv_tag(mslot, gval, nonce, op == 0 ? tag_d : nullptr, ctr, op == 1 ? tag_d : nullptr, ok_d,
                            counters, ctx->d_tables, ctx->d_tables + 256, s);

@@ -82,3 +82,36 @@ def test_siv_rows(ctx, key_len, aad_len, n):
         finally:
             ctx.key_release(slot)
             ctx.set_launch(0, 0, 0)
+
+
+# Where the launch changes: one workgroup or more, rows of waves of their own up to the chip's last
+# wave and tiles of more rows beyond it, and one tile more than there are waves.
+@pytest.mark.parametrize("aad_len,n", [(0, 15 * ROW - 16), (0, 16 * ROW - 16), (16, 16 * ROW - 16), (5, 16 * ROW),
+                                       (0, 255 * ROW - 16), (0, 4096 * ROW - 16), (16, 4096 * ROW - 16),
+                                       (2880, 4097 * ROW), (16, 16384 * ROW - 16), (2880, 16384 * ROW)])
+def test_launch_boundaries(ctx, aad_len, n):
+    r = np.random.default_rng(n + aad_len)
+    key, iv = r.bytes(32 if n % 3 else 16), r.bytes(12)
+    aad, pt = (r.integers(0, 256, k, dtype=np.uint8) for k in (aad_len, n))
+    ct_ref, tag_ref = oracle.gcm_encrypt(key, iv, aad, pt)
+    plan = ctx.launch_plan(len(key), n, aad_len)
+    print(f"aad={aad_len} n={n} {plan}", flush=True)
+    aad_d, pt_d = to_dev(aad) if aad_len else None, to_dev(pt)
+    full, ct_d = guarded(n)
+    slot = ctx.key_register(key)
+    try:
+        ws = torch.full((ctx.workspace_size(n, aad_len),), 0xA5, dtype=torch.uint8, device="cuda")
+        tag_d, ok = to_dev(np.zeros(16, np.uint8)), torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        ctx.encrypt_async(slot, iv, aad_d, pt_d, ct_d, tag_d, ws)
+        torch.cuda.synchronize()
+        assert bytes(host(tag_d)) == tag_ref and np.array_equal(host(ct_d), ct_ref) and canaries_intact(full, n)
+        back = torch.empty_like(pt_d)
+        ctx.decrypt_verify_async(slot, iv, aad_d, ct_d, tag_d, back, ok, ws)
+        torch.cuda.synchronize()
+        assert int(ok) == 1 and torch.equal(back, pt_d)
+        tag_d[15] ^= 1
+        ctx.decrypt_verify_async(slot, iv, aad_d, ct_d, tag_d, back, ok, ws)
+        torch.cuda.synchronize()
+        assert int(ok) == 0 and not back.any()
+    finally:
+        ctx.key_release(slot)

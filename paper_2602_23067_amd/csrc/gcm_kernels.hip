@@ -1078,49 +1078,64 @@ struct Kind {
     static constexpr uint32_t lds = sums + (gh ? 16u * (2 * 16 + 1) : 0u);
 };
 
-// the message's counter block; c1: the counter value of data block 0, cj0: of J0
-template <int KIND>
-__device__ __forceinline__ void message_counter(const CONST_AS MsgDesc *dp, const CONST_AS uint32_t *te,
-                                                CtrBlock<Kind<KIND>::siv> &c, uint32_t &c1, uint32_t &cj0)
-{
-    const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
-    const uint64_t jaddr = dp->j0;
-    const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
-    if (Kind<KIND>::siv) {  // the counter block is the tag with its top bit set
-        c.init(jw[1], jw[2], jw[3], rk, te);
-        c1 = cj0 = jw[0];
-    } else if (jaddr) {  // J0 computed on the device from an IV that is not 96 bits
-        c.init(jw[0], jw[1], jw[2], rk, te);
-        cj0 = bswap32(jw[3]);
-        c1 = cj0 + 1u + dp->ctr_off;
-    } else {  // J0 = IV || 0^31 || 1
-        c.init(dp->iv[0], dp->iv[1], dp->iv[2], rk, te);
-        cj0 = 1u;
+// A message's counter block; c1: the counter value of data block 0 (J0's own is
+// one less, but for a streamed segment); cur: the round-2 words of upper
+// counter bits hc.
+template <bool SIV>
+struct Counters {
+    CtrBlock<SIV> c;
+    uint32_t c1, hc;
+    u32x4 cur;
+
+    __device__ __forceinline__ void init(const CONST_AS MsgDesc *dp, const CONST_AS uint32_t *te)
+    {
+        const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
+        const uint64_t jaddr = dp->j0;
+        const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
+        uint32_t w0 = dp->iv[0], w1 = dp->iv[1], w2 = dp->iv[2];  // J0 = IV || 0^31 || 1
         c1 = 2u + dp->ctr_off;
+        if (SIV) {  // the counter block is the tag with its top bit set
+            w0 = jw[1], w1 = jw[2], w2 = jw[3];
+            c1 = jw[0];
+        } else if (jaddr) {  // J0 computed on the device from an IV that is not 96 bits
+            w0 = jw[0], w1 = jw[1], w2 = jw[2];
+            c1 = bswap32(jw[3]) + 1u + dp->ctr_off;
+        }
+        c.init(w0, w1, w2, rk, te);
     }
-}
+    // the round-2 words of the first row of tile t that has data
+    __device__ __forceinline__ void first_row(const CONST_AS MsgDesc *dp, int64_t t, bool head,
+                                              const CONST_AS uint32_t *te)
+    {
+        const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
+        const int64_t jb = (t << dp->log2B) - (int64_t)dp->z - (int64_t)dp->na;  // data block index of the tile's start
+        const uint32_t base = (uint32_t)(head || jb < 0 ? -((-jb) & 63) : jb) + c1;
+        hc = base >> 8;
+        cur = c.high_words(hc, rk, te);
+    }
+};
 
 // One wave processes wave tile t of a message: rows of 64 consecutive blocks,
 // lane l on block 64 r + l, so every load and store moves one contiguous KiB.
 // Rows [fa, fb) hold 64 whole data blocks and rows [aa, ab) 64 whole AAD
 // blocks; the others (zero padding, partial blocks, the length block) load and
-// store lane by lane.  The wave of tile 0 runs one row ahead of its tile for
-// E_K(J0), the keystream block of J0's own counter value, and leaves it in LDS.  A streamed segment's
+// store lane by lane.  E_K(J0) is the keystream block of the lane before the
+// first data block, whose counter is J0's own; only where no such lane exists
+// (no AAD and no padding) does the first wave run a row ahead of its tile for it.  A streamed segment's
 // counters start ctr_off blocks after J0 + 1.
 // a_l = sum_r X_(64r+l) * (H^64)^(R-1-r) by Horner on lane l, then the tile's
 // value is sum_l a_l * H^(63-l).  GCM-SIV hashes byte-reversed blocks.
 template <int NR, int KIND>
 __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t t, bool head,
-                                           uint8_t *__restrict__ lds, const typename Kind<KIND>::tables &tab,
-                                           const GhK &gk, const CONST_AS uint32_t *te)
+                                           const Counters<Kind<KIND>::siv> &cs, uint8_t *__restrict__ lds,
+                                           const typename Kind<KIND>::tables &tab, const GhK &gk,
+                                           const CONST_AS uint32_t *te, u32x4 *__restrict__ ekg)
 {
     constexpr bool GH = Kind<KIND>::gh, SIV = Kind<KIND>::siv, AES = Kind<KIND>::aes;
     const int lane = threadIdx.x & 63;
     const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(dp->slot));
-    CtrBlock<SIV> c;
-    uint32_t c1 = 0, cj0 = 0;
-    if (AES)
-        message_counter<KIND>(dp, te, c, c1, cj0);
+    const CtrBlock<SIV> &c = cs.c;
+    const uint32_t c1 = cs.c1;
 
     const uint32_t log2B = dp->log2B;
     const int32_t R = (int32_t)(1u << (log2B - 6));
@@ -1138,12 +1153,14 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
     };
     int32_t fa, fb, aa = 0, ab = 0;
     whole_rows(na, na + nfull, fa, fb);
-    if (GH)
-        whole_rows(0, (int64_t)(dp->aad_len >> 4), aa, ab);
+    if (GH) {
+        const int64_t end = (int64_t)(dp->aad_len >> 4);
+        whole_rows(0, KIND == kGcm && end == na ? end - 1 : end, aa, ab);
+    }
     const int64_t jb = vbase - na;  // data block index of lane 0, row 0
 
-    uint32_t hc = 0xffffffffu;  // upper counter bits `cur` belongs to (none yet)
-    u32x4 cur = {0, 0, 0, 0};
+    uint32_t hc = cs.hc;  // upper counter bits `cur` belongs to
+    u32x4 cur = cs.cur;
     // The state after round 2 of the row whose first counter is `base`: its
     // counters are base + lane (mod 2^32), whose upper 24 bits change at most
     // once inside the row, and then by one.
@@ -1170,7 +1187,8 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
 
     // GHASH runs one row behind: a is the Horner value without the pending row xp
     u32x4 a = {0, 0, 0, 0}, xp = {0, 0, 0, 0};
-    const bool ek = KIND == kGcm && head;
+    const bool first = KIND == kGcm && dp->ctr_off == 0;  // E_K(J0) is wanted
+    const bool ek = first && head && (dp->z & 63) == 0 && na == 0;
     __builtin_amdgcn_s_setprio(3);
     for (int32_t r = ek ? r0 - 1 : r0; r < R;) {
         if (GH && r >= aa && r < ab) {
@@ -1193,18 +1211,20 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
             const int64_t ndat = (int64_t)bp->n;
             const bool data = v >= na && v < na + ndat;
             const uint64_t j = (uint64_t)(v - na);
-            const bool hot = AES && (ekrow || (v0 + 64 > na && v0 < na + ndat));  // some lane needs a keystream block
+            // some lane needs a keystream block (the one before the first data block for E_K(J0))
+            const bool hot = AES && (ekrow || (v0 + 64 > (first ? na - 1 : na) && v0 < na + ndat));
             u32x4 ks = {0, 0, 0, 0}, x = {0, 0, 0, 0};
             if (hot) {
                 GhashStep none;
-                ks = aes_rounds<NR, false>(round2(ekrow ? cj0 : (uint32_t)jb + 64u * (uint32_t)r + c1), rk, tab, none, gk);
+                ks = aes_rounds<NR, false>(round2(ekrow ? c1 - 1u : (uint32_t)jb + 64u * (uint32_t)r + c1), rk, tab, none, gk);
             }
             ++r;
-            if (ekrow) {
-                if (lane == 0)
-                    *reinterpret_cast<u32x4 *>(lds + Kind<KIND>::sums + 16 * 32) = ks;
-                continue;
+            if (first && hot && (ekrow ? lane == 0 : v == na - 1)) {
+                *reinterpret_cast<u32x4 *>(lds + Kind<KIND>::sums + 16 * 32) = ks;
+                *ekg = ks;  // after the message's partials
             }
+            if (ekrow)
+                continue;
             if (data) {
                 x = load_block_partial(gptr<const uint8_t>(bp->in), j, bp->len);
                 if (AES) {
@@ -1314,51 +1334,50 @@ struct StageTables {
     }
 };
 
-// The key's GHASH table of H^64 (64 KiB, LDS bytes [0, 64 KiB)) and its
-// lane fix-up windows (16 KiB, LDS bytes [128 KiB, 144 KiB)) from the key
-// slot, all of a thread's loads issued before its stores.  In a workgroup
-// of 16 waves (128 VGPRs a thread) the thread index goes through an empty
-// asm so that the addresses are formed here: a caller that stages inside a
-// loop would otherwise hold them across the whole loop, spilled, and each
-// reload would wait for the previous load.  With fewer waves they stay in
-// registers.  The caller adds the barriers.
+// The key's GHASH table of H^64 (64 KiB, LDS bytes [0, 64 KiB)) and its lane
+// fix-up windows (16 KiB, LDS bytes [128 KiB, 144 KiB)) from the key slot: a
+// thread's loads, then its stores (the caller does other things between them
+// and adds the barriers).
 template <int NT>
-__device__ __forceinline__ void stage_key_tables(u32x4 *lds_v, uint64_t slot)
-{
-    const GLOBAL_AS u32x4 *tab = gptr<const u32x4>(slot + kSlotTab8Off);
-    const GLOBAL_AS u32x4 *win = gptr<const u32x4>(slot + kSlotLaneWinOff);
-    constexpr uint32_t kTab = 4096, kWin = 1024;
-    constexpr int kPerT = (int)((kTab + NT - 1) / NT), kPerW = (int)((kWin + NT - 1) / NT);
-    uint32_t tid = threadIdx.x;
-    if (NT >= 1024)
-        asm volatile("" : "+v"(tid));
+struct StageKeys {
+    static constexpr uint32_t kTab = 4096, kWin = 1024;
+    static constexpr int kPerT = (int)((kTab + NT - 1) / NT), kPerW = (int)((kWin + NT - 1) / NT);
     u32x4 a[kPerT], b[kPerW];
-#pragma unroll
-    for (int r = 0; r < kPerT; ++r) {
-        const uint32_t q = tid + (uint32_t)(r * NT);
-        if (kTab % NT == 0 || q < kTab)
-            a[r] = q < 16 ? u32x4{0, 0, 0, 0} : tab[q];  // entries of 0: the slot keeps lifts there
-    }
-#pragma unroll
-    for (int r = 0; r < kPerW; ++r) {
-        const uint32_t q = tid + (uint32_t)(r * NT);
-        if (kWin % NT == 0 || q < kWin)
-            b[r] = q < (uint32_t)kLanePows ? u32x4{0, 0, 0, 0} : win[q];  // entries of 0: the slot keeps lifts there
-    }
-#pragma unroll
-    for (int r = 0; r < kPerT; ++r) {
-        const uint32_t q = tid + (uint32_t)(r * NT);
-        if (kTab % NT == 0 || q < kTab)
-            lds_v[q] = a[r];
-    }
-#pragma unroll
-    for (int r = 0; r < kPerW; ++r) {
-        const uint32_t q = tid + (uint32_t)(r * NT);
-        if (kWin % NT == 0 || q < kWin)
-            lds_v[8192 + q] = b[r];
-    }
-}
 
+    __device__ __forceinline__ void load(uint64_t slot)
+    {
+        const GLOBAL_AS u32x4 *tab = gptr<const u32x4>(slot + kSlotTab8Off);
+        const GLOBAL_AS u32x4 *win = gptr<const u32x4>(slot + kSlotLaneWinOff);
+        // entries of 0: the slot keeps lifts there
+#pragma unroll
+        for (int r = 0; r < kPerT; ++r) {
+            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+            if (kTab % NT == 0 || q < kTab)
+                a[r] = q < 16 ? u32x4{0, 0, 0, 0} : tab[q];
+        }
+#pragma unroll
+        for (int r = 0; r < kPerW; ++r) {
+            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+            if (kWin % NT == 0 || q < kWin)
+                b[r] = q < (uint32_t)kLanePows ? u32x4{0, 0, 0, 0} : win[q];
+        }
+    }
+    __device__ __forceinline__ void store(u32x4 *lds_v) const
+    {
+#pragma unroll
+        for (int r = 0; r < kPerT; ++r) {
+            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+            if (kTab % NT == 0 || q < kTab)
+                lds_v[q] = a[r];
+        }
+#pragma unroll
+        for (int r = 0; r < kPerW; ++r) {
+            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
+            if (kWin % NT == 0 || q < kWin)
+                lds_v[8192 + q] = b[r];
+        }
+    }
+};
 
 // A workgroup covers WAVES consecutive tiles of a message per work item; one
 // message (single) or a batch with a list of items.
@@ -1511,14 +1530,36 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
     if (KIND == kGcm && blockIdx.x == 0 && threadIdx.x == 0)
         counters[0] = 0;  // reject count for this launch (read by the zero-fill)
 
-    if (K::aes) {
-        StageTables<WAVES * 64> st;
-        st.load(te0g);
-        st.store(lds_v, tab);
-    }
+    // The T-tables, and a single message's key tables and counter block, are
+    // staged here: the chain of scalar loads behind the counter block runs
+    // while the tables are on their way.
     uint64_t cur_slot = 0;
     uint32_t cur_msg = 0xffffffffu;
     uint32_t turn = 0;  // items done: its low bit picks the buffer of tile values, the wave that sums rotates
+    Counters<K::siv> cs = {};
+    {
+        const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
+        StageTables<WAVES * 64> st;
+        StageKeys<WAVES * 64> sk;
+        if (K::aes)
+            st.load(te0g);
+        if (K::gh && !BATCH) {
+            cur_slot = dp->slot;
+            sk.load(cur_slot);
+        }
+        if (K::aes && !BATCH)
+            cs.init(dp, te);
+        if (K::aes)
+            st.store(lds_v, tab);
+        if (K::gh && !BATCH)
+            sk.store(lds_v);
+        if (!BATCH) {
+            lds_barrier();
+            if (K::aes && threadIdx.x < 256)
+                lds_v[K::round2 / 16 + threadIdx.x] = cs.c.low_words(threadIdx.x, tab);
+            cur_msg = 0;
+        }
+    }
     for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
         const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
         uint32_t first, msg = 0;
@@ -1529,28 +1570,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
             msg = w.msg;
         } else {
             first = (uint32_t)dp->tile_lo + it * WAVES;
-        }
-        if (msg != cur_msg) {
-            // a new message: its key's GHASH tables (unless staged already) and
-            // its round-2 words, between barriers that also publish the T-tables
-            const uint64_t slot = dp->slot;
-            if (BATCH)
-                lds_barrier();
-            if (K::gh && slot != cur_slot) {
-                stage_key_tables<WAVES * 64>(lds_v, slot);
-                cur_slot = slot;
-            }
-            if (K::aes) {
-                if (!BATCH)
-                    lds_barrier();
-                CtrBlock<K::siv> c;
-                uint32_t c1, cj0;
-                message_counter<KIND>(dp, te, c, c1, cj0);
-                if (threadIdx.x < 256)
-                    lds_v[K::round2 / 16 + threadIdx.x] = c.low_words(threadIdx.x, tab);
-            }
-            cur_msg = msg;
-            lds_barrier();
         }
         // log2G and flags, one scalar load
         const uint32_t gf = K::gh ? *(const CONST_AS uint32_t *)&dp->log2G : 0u;
@@ -1563,21 +1582,44 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
         u32x4 p = {0, 0, 0, 0};
         const bool mine = t >= 0 && t < (int64_t)dp->tile_hi - (int64_t)merge;
         t += merge;
+        const bool fresh = BATCH ? msg != cur_msg : turn == 0;
+        if (BATCH && fresh) {
+            // a new message: its key's GHASH tables (unless staged already) and
+            // its round-2 words
+            const uint64_t slot = dp->slot;
+            const bool stage = K::gh && slot != cur_slot;
+            StageKeys<WAVES * 64> sk;
+            if (stage)
+                sk.load(slot);
+            cs.init(dp, te);
+            lds_barrier();  // the last item's reads, and the T-tables before the first
+            if (stage) {
+                sk.store(lds_v);
+                cur_slot = slot;
+            }
+            if (threadIdx.x < 256)
+                lds_v[K::round2 / 16 + threadIdx.x] = cs.c.low_words(threadIdx.x, tab);
+            cur_msg = msg;
+        }
+        if (K::aes && mine)
+            cs.first_row(dp, t, head, te);
+        if (fresh)
+            lds_barrier();
+        const uint64_t nparts = (run + G - 1) >> log2G;
+        u32x4 *ekg = partials + (K::gh ? dp->tile_base + nparts : 0);
         if (mine) {
             const uint32_t nr = K::aes ? dp->nr : 14;
             if (nr == 10)
-                p = wave_tile<10, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
+                p = wave_tile<10, KIND>(dp, (uint64_t)t, head, cs, lds, tab, gk, te, ekg);
             else if (nr == 12 && !K::siv)
-                p = wave_tile<12, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
+                p = wave_tile<12, KIND>(dp, (uint64_t)t, head, cs, lds, tab, gk, te, ekg);
             else
-                p = wave_tile<14, KIND>(dp, (uint64_t)t, head, lds, tab, gk, te);
+                p = wave_tile<14, KIND>(dp, (uint64_t)t, head, cs, lds, tab, gk, te, ekg);
         }
+        const uint32_t my_turn = turn++;
         if (!K::gh)
             continue;
         const u32x4 *ekw = lds_v + K::sums / 16 + 32;
-        const uint64_t nparts = (run + G - 1) >> log2G;
-        if (KIND == kGcm && mine && head && lane == 0)
-            partials[dp->tile_base + nparts] = *ekw;  // after the message's partials, for the combine
         if (log2G == 0) {
             if (mine && lane == 0)
                 partials[dp->tile_base + (uint64_t)t] = p;
@@ -1586,15 +1628,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
         const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));  // tiles of the group after this one
         if (mine && after)
             p = gf_mul_wave(p, group_lift(dp->slot, dp->log2B, after));
-        u32x4 *sums = lds_v + K::sums / 16 + 16 * (turn & 1u);
+        u32x4 *sums = lds_v + K::sums / 16 + 16 * (my_turn & 1u);
         if (lane == 0)
             sums[wave] = p;
         if (finish && dp->op == 1)
             __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
         lds_barrier();
-        if (wave == (int)(turn % WAVES))
+        if (wave == (int)(my_turn % WAVES))
             sum_groups<WAVES>(dp, sums, ekw, G, log2G, finish, true, first, nparts, partials);
-        ++turn;
     }
 }
 

@@ -26,7 +26,7 @@ def ctx():
 
 
 @pytest.mark.parametrize("key_len", [16, 24, 32])
-@pytest.mark.parametrize("aad_len,n", [(0, 5 * ROW), (3 * ROW, 4 * ROW), (2 * ROW - 16, 9 * ROW + 16),
+@pytest.mark.parametrize("aad_len,n", [(0, 5 * ROW), (0, 5 * ROW - 16), (3 * ROW, 4 * ROW), (2 * ROW - 16, 9 * ROW + 16),
                                        (2 * ROW + 5, 9 * ROW - 1), (70 * ROW, 3 * ROW), (16, 40 * ROW + 1007)])
 def test_gcm_rows_and_counters(ctx, key_len, aad_len, n):
     for seed in range(6):  # IVs of 16 bytes: J0, and with it the first counter's low byte, is arbitrary

@@ -417,7 +417,7 @@ Shape gcm::message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, u
     return sh;
 }
 
-Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m)
+Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m, bool small)
 {
     Shape sh;
     TuneEntry t;
@@ -429,6 +429,13 @@ Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_
             tuned = true;
         }
     }
+    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : (tuned && t.fanin) ? t.fanin : 2;
+    if (small && !tuned && !ctx->cfg_log2B && !ctx->cfg_waves && !ctx->cfg_gpc && batch_rows(n, m, (uint64_t)ctx->cu_count)) {
+        sh.log2B = 6;
+        sh.waves = 8;
+        sh.gpc = 2;
+        return sh;
+    }
     sh.waves = ctx->cfg_waves ? ctx->cfg_waves : tuned ? t.waves : 16;
     sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : (tuned && t.gpc) ? t.gpc : (uint32_t)max_groups_per_cu((int)sh.waves);
     if (ctx->cfg_log2B)
@@ -439,7 +446,6 @@ Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_
         sh.log2B = std::min<uint32_t>(
             12, std::max<uint32_t>(8, heuristic_log2B(std::max<uint64_t>(1, m),
                                                       (uint64_t)ctx->cu_count * sh.gpc * sh.waves)));
-    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : (tuned && t.fanin) ? t.fanin : 2;
     return sh;
 }
 
@@ -494,7 +500,7 @@ int gcm::launch_tile_range(gcm_ctx *ctx, const MsgDesc &d, const Shape &sh, void
     const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(items, (uint32_t)ctx->cu_count * gpc));
     hipError_t e = prof_begin(ctx, s);
     if (e == hipSuccess)
-        e = launch_tiles((int)waves, nullptr, nullptr, items, &d, ctx->d_tables, partials, counters, grid, s);
+        e = launch_tiles((int)waves, nullptr, nullptr, items, &d, ctx->d_tables, partials, counters, grid, false, s);
     if (e == hipSuccess)
         e = prof_end(ctx, s);
     if (e != hipSuccess)

@@ -27,7 +27,7 @@ struct gcm_batch {
     uint32_t n_items = 0;
     Shape shape;
     uint32_t grid = 1;
-    bool any_combine = false, any_zerofill = false;
+    bool rows = false, any_combine = false, any_zerofill = false;
     uint64_t total_tiles = 0;
     uint64_t payload_bytes = 0;
     MsgDesc *d_descs = nullptr;
@@ -42,7 +42,7 @@ struct gcm_batch {
 // Validate the jobs against the base allocation and the key table and plan
 // them, with `forced` as the shape if given (caller holds ctx->mu).
 int gcm::plan_jobs(const gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
-                   const Shape *forced, Shape *sh_out, BatchPlan *plan)
+                   const Shape *forced, bool small, Shape *sh_out, BatchPlan *plan)
 {
     const SlotView sv = slot_view(ctx);
     PlanError err;
@@ -56,18 +56,18 @@ int gcm::plan_jobs(const gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t 
         total_m += ghash_blocks(jobs[i].aad_len, jobs[i].len);
         payload += jobs[i].len;
     }
-    const Shape sh = forced ? *forced : batch_shape(ctx, n, payload, total_m);
+    const Shape sh = forced ? *forced : batch_shape(ctx, n, payload, total_m, small);
     plan_batch(msgs.data(), n, sv, sh.waves, sh.log2B, plan);
     *sh_out = sh;
     return GCM_OK;
 }
 
-int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
-                             const Shape *forced, gcm_batch **out)
+static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
+                          const Shape *forced, bool small, gcm_batch **out)
 {
     BatchPlan plan;
     Shape sh;
-    int rc = plan_jobs(ctx, jobs, n, base_d, base_bytes, forced, &sh, &plan);
+    int rc = plan_jobs(ctx, jobs, n, base_d, base_bytes, forced, small, &sh, &plan);
     if (rc)
         return rc;
     gcm_batch *b = new gcm_batch();
@@ -75,6 +75,7 @@ int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint
     b->n = n;
     b->shape = sh;
     b->total_tiles = plan.total_tiles;
+    b->rows = plan.rows;
     b->any_combine = plan.any_combine;
     b->any_zerofill = plan.any_zerofill;
     b->payload_bytes = plan.payload;
@@ -106,6 +107,17 @@ int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint
     }
     *out = b;
     return GCM_OK;
+}
+
+int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
+                             const Shape *forced, gcm_batch **out)
+{
+    // One-row tiles have more partials and items: where the context's memory
+    // does not hold them, the plan with larger tiles is tried.
+    int rc = create_planned(ctx, jobs, n, base_d, base_bytes, forced, true, out);
+    if (rc == GCM_E_NOMEM && !forced)
+        rc = create_planned(ctx, jobs, n, base_d, base_bytes, forced, false, out);
+    return rc;
 }
 
 extern "C" int gcm_batch_create(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
@@ -147,7 +159,7 @@ hipError_t gcm::batch_enqueue(gcm_batch *b, hipStream_t s)
     hipError_t e = prof_begin(ctx, s);
     if (e == hipSuccess)
         e = launch_tiles((int)b->shape.waves, b->d_descs, b->d_items, b->n_items, nullptr, ctx->d_tables, partials,
-                         counters, b->grid, s);
+                         counters, b->grid, b->rows, s);
     if (e == hipSuccess)
         e = prof_end(ctx, s);
     if (e == hipSuccess && b->any_combine)

@@ -137,7 +137,7 @@ void stream_pool_release(gcm_ctx *ctx);
 // Launch shape of a batch of n messages and `payload` bytes holding m GHASH
 // blocks in all: explicit settings, else the batch autotune cache, else the
 // heuristic (tile cap from the single-launch heuristic, 16 waves).
-Shape batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m);
+Shape batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m, bool small = true);
 // the key table as the planner sees it
 SlotView slot_view(const gcm_ctx *ctx);
 // lengths and device buffers of one message (see check_buffers)
@@ -164,7 +164,7 @@ int async_launch(gcm_ctx *ctx, uint32_t op, uint32_t slot, const uint8_t *iv, si
 // (with `forced` as the shape if non-NULL), create a batch, enqueue its
 // kernels, free it
 int plan_jobs(const gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
-              const Shape *forced, Shape *sh_out, BatchPlan *plan);
+              const Shape *forced, bool small, Shape *sh_out, BatchPlan *plan);
 int batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
                         const Shape *forced, gcm_batch **out);
 hipError_t batch_enqueue(gcm_batch *b, hipStream_t s);
@@ -188,7 +188,7 @@ hipError_t launch_key_setup(const uint8_t *const *keys, const uint32_t *key_lens
                             uint32_t n, const uint32_t *te0, const uint32_t *sbox, const void *frob, hipStream_t s);
 hipError_t launch_tiles(int waves, const MsgDesc *descs, const WorkItem *items, uint32_t n_items,
                         const MsgDesc *single, const uint32_t *te0, void *partials, uint32_t *counters, uint32_t grid,
-                        hipStream_t s);
+                        bool rows, hipStream_t s);  // rows: a batch of one-row tiles
 int max_groups_per_cu(int waves);
 // fanin: children per node of the reduction tree over tile partials (2, 4, 8, 16)
 hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,

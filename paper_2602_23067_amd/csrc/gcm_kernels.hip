@@ -1049,16 +1049,27 @@ __device__ __forceinline__ u32x4 load_block_partial(const GLOBAL_AS uint8_t *p, 
     const uint64_t off = blk * 16;
     if (off + 16 <= total)
         return *reinterpret_cast<const GLOBAL_AS u32x4 *>(p + off);
-    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-    for (uint64_t k = off; k < total; ++k) {
-        const uint32_t b = (uint32_t)p[k] << (8 * ((k - off) & 3));
-        const uint64_t d = (k - off) >> 2;
-        w0 |= d == 0 ? b : 0u;
-        w1 |= d == 1 ? b : 0u;
-        w2 |= d == 2 ? b : 0u;
-        w3 |= d == 3 ? b : 0u;
-    }
-    return u32x4{w0, w1, w2, w3};
+    // whole words, then the bytes after them: at most six loads that wait for
+    // nothing but each other's issue (one byte after another, each on its way
+    // before the next is asked for, took up to fifteen trips to memory)
+    const uint32_t nb = off < total ? (uint32_t)(total - off) : 0u, q = nb & ~3u, k = nb & 3u;
+    const GLOBAL_AS uint32_t *w = reinterpret_cast<const GLOBAL_AS uint32_t *>(p + off);
+    const GLOBAL_AS uint8_t *e = p + off + q;
+    uint32_t w0 = 0, w1 = 0, w2 = 0, b0 = 0, b1 = 0, b2 = 0;
+    if (nb >= 4)
+        w0 = w[0];
+    if (nb >= 8)
+        w1 = w[1];
+    if (nb >= 12)
+        w2 = w[2];
+    if (k > 0)
+        b0 = e[0];
+    if (k > 1)
+        b1 = e[1];
+    if (k > 2)
+        b2 = e[2];
+    const uint32_t t = b0 | b1 << 8 | b2 << 16;
+    return u32x4{q == 0 ? t : w0, q == 4 ? t : w1, q == 8 ? t : w2, q == 12 ? t : 0u};
 }
 
 __device__ __forceinline__ uint32_t keep_bytes(uint32_t w, int nb)  // keep the low nb bytes (nb may be <=0 or >=4)
@@ -1082,11 +1093,22 @@ __device__ __forceinline__ void store_block_partial(GLOBAL_AS uint8_t *p, uint64
         *reinterpret_cast<GLOBAL_AS u32x4 *>(p + off) = v;
         return;
     }
-    for (uint64_t k = off; k < total; ++k) {
-        const uint64_t d = (k - off) >> 2;
-        const uint32_t w = d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
-        p[k] = (uint8_t)(w >> (8 * ((k - off) & 3)));
-    }
+    const uint32_t nb = off < total ? (uint32_t)(total - off) : 0u, q = nb & ~3u, k = nb & 3u;
+    GLOBAL_AS uint32_t *w = reinterpret_cast<GLOBAL_AS uint32_t *>(p + off);
+    GLOBAL_AS uint8_t *e = p + off + q;
+    const uint32_t t = q == 0 ? v.x : q == 4 ? v.y : q == 8 ? v.z : v.w;
+    if (nb >= 4)
+        w[0] = v.x;
+    if (nb >= 8)
+        w[1] = v.y;
+    if (nb >= 12)
+        w[2] = v.z;
+    if (k > 0)
+        e[0] = (uint8_t)t;
+    if (k > 1)
+        e[1] = (uint8_t)(t >> 8);
+    if (k > 2)
+        e[2] = (uint8_t)(t >> 16);
 }
 
 __device__ __forceinline__ u32x4 rev_block(u32x4 x) { return u32x4{bswap32(x.w), bswap32(x.z), bswap32(x.y), bswap32(x.x)}; }
@@ -1261,6 +1283,9 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
             // some lane needs a keystream block (the one before the first data block for E_K(J0))
             const bool hot = AES && (ekrow || (v0 + 64 > (first ? na - 1 : na) && v0 < na + ndat));
             u32x4 ks = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+            if (!ekrow && v >= 0 && v < na + ndat && (GH || data))  // on its way during the rounds
+                x = load_block_partial(data ? gptr<const uint8_t>(bp->in) : gptr<const uint8_t>(bp->aad),
+                                       data ? j : (uint64_t)v, data ? bp->len : bp->aad_len);
             if (hot) {
                 GhashStep none;
                 ks = aes_rounds<NR, false>(round2(ekrow ? c1 - 1u : (uint32_t)jb + 64u * (uint32_t)r + c1), rk, tab, none, gk);
@@ -1272,15 +1297,10 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
             }
             if (ekrow)
                 continue;
-            if (data) {
-                x = load_block_partial(gptr<const uint8_t>(bp->in), j, bp->len);
-                if (AES) {
-                    const u32x4 o = x ^ ks;
-                    store_block_partial(gptr<uint8_t>(bp->out), j, bp->len, o);
-                    x = (SIV || bp->op == 0) ? mask_block(o, j, bp->len) : x;
-                }
-            } else if (GH && v >= 0 && v < na) {
-                x = load_block_partial(gptr<const uint8_t>(bp->aad), (uint64_t)v, bp->aad_len);
+            if (AES && data) {
+                const u32x4 o = x ^ ks;
+                store_block_partial(gptr<uint8_t>(bp->out), j, bp->len, o);
+                x = (SIV || bp->op == 0) ? mask_block(o, j, bp->len) : x;
             } else if (GH && v == na + ndat) {
                 const uint64_t abits = bp->aad_len * 8, cbits = bp->len * 8;
                 x = SIV ? u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)cbits, (uint32_t)(cbits >> 32)}
@@ -1288,7 +1308,8 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
                                 bswap32((uint32_t)(cbits >> 32)), bswap32((uint32_t)cbits)};
             }
             if (GH) {
-                a = ghash_mul8(a, xp, lds, gk);
+                if (r > r0 + 1)  // nothing precedes the tile's first row
+                    a = ghash_mul8(a, xp, lds, gk);
                 xp = SIV ? rev_block(x) : x;
             }
             continue;
@@ -1337,7 +1358,10 @@ __device__ __forceinline__ u32x4 wave_tile(const CONST_AS MsgDesc *dp, uint64_t 
     }
     if (!GH)
         return a;
-    a = ghash_mul8(a, xp, lds, gk);
+    if (R > r0 + 1)
+        a = ghash_mul8(a, xp, lds, gk);
+    else
+        a = xp;
     // fix-up: a * H^(63 - lane) through the lane's window table in LDS
     return wave_xor_reduce(gf_mul_lanewin<64>(a, lds + Kind<KIND>::windows, lane));
 }
@@ -1717,9 +1741,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
 // behind it took longer than the 27 lookups it saves).  The payload, the
 // T-tables and the fix-up windows are all requested before anything is waited
 // for.  No wave has a Horner step to do, so the 64 KiB GHASH table is not staged.
-// E_K(J0) is the keystream block of the lane before the first data block, whose
-// counter is J0's own; only when that lane does not exist (no AAD, no padding)
-// does the first wave run a row for it.
+// E_K(J0) is worked out by the lane of the length block, which has no keystream
+// block of its own and is always the last lane of the last row.
 //
 // The fix-up takes windows of H^(32 - n), n = lane & 31 (8 KiB), which includes
 // GHASH's last factor H: the lower half-wave's sum has 32 more places to go,
@@ -1729,192 +1752,217 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
 // 1 MiB, AES-128, one-shot: 39.3 us with the tile kernel (10.8 us) and a tree
 // over 1027 partials (11.8 us), 29.0 us with this one (9.4 us, half of it the
 // staging) and the verdict (2.4 us).
+// A batch of small messages goes the same way, an item of WAVES rows after
+// another, so that a message costs 8 KiB of windows and not 80 KiB of tables; two
+// workgroups of eight waves share a compute unit and hide each other's waits
+// (72.3 KiB of LDS each; the launch bound asks for no more registers than that).
+// The vector units bound it, some 1400 instructions a row: 1024 messages with a
+// median of 4 KiB and 2 KiB of AAD, 79 us by tiles, 50 us.
 constexpr uint32_t kRowWin = 0x10000u, kRowSums = 0x12000u;
 
-template <int WAVES, int KIND>
-__global__ __launch_bounds__(WAVES * 64) void k_gcm_rows(MsgDesc single, const uint32_t *__restrict__ te0g,
+template <int WAVES, bool BATCH, int KIND>
+__global__ __launch_bounds__(WAVES * 64, BATCH ? WAVES / 2 : 1) void k_gcm_rows(MsgDesc single, const MsgDesc *__restrict__ descs,
+                                                         const WorkItem *__restrict__ items, uint32_t n_items,
+                                                         const uint32_t *__restrict__ te0g,
                                                          u32x4 *__restrict__ partials, uint32_t *counters)
 {
     constexpr bool SIV = Kind<KIND>::siv, AES = Kind<KIND>::aes;
     constexpr int NT = WAVES * 64, kWinPer = (512 + NT - 1) / NT;
     __shared__ u32x4 lds_v[kRowSums / 16 + 17];
     uint8_t *lds = reinterpret_cast<uint8_t *>(lds_v);
+    u32x4 *ekw = lds_v + kRowSums / 16 + 16;
     StageTables<NT> st;
     if (AES)
         st.load(te0g);
-    const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
-    const int lane = threadIdx.x & 63;
-    const int wave = (int)uniform(threadIdx.x >> 6);
-    touch_lines(dp);
-    const uint64_t slot = dp->slot, T = dp->n_tiles;
-    u32x4 win[kWinPer];
-    {
-        const GLOBAL_AS u32x4 *src = gptr<const u32x4>(slot + kSlotLaneWinOff);
-#pragma unroll
-        for (int r = 0; r < kWinPer; ++r) {
-            const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
-            win[r] = q >= 32 && q < 512 ? src[64 * (q >> 5) + 31 + (q & 31)] : u32x4{0, 0, 0, 0};
-        }
-    }
-    const uint32_t gf = *(const CONST_AS uint32_t *)&dp->log2G;
-    const uint32_t log2G = gf & 0xffffu, G = 1u << log2G;
-    const bool finish = (gf >> 16) & 1u;
-    const uint32_t first = blockIdx.x * WAVES;
-    const int64_t t = (int64_t)first + wave - (int64_t)((0u - (uint32_t)T) & (G - 1u));
-    const bool mine = t >= 0 && t < (int64_t)T;
-
-    // this lane's block of the sequence and its bytes
-    const int64_t na = (int64_t)dp->na, ndat = (int64_t)dp->n;
-    const int64_t v0 = 64 * t - (int64_t)dp->z, v = v0 + lane;
-    const bool data = mine && v >= na && v < na + ndat;
-    const uint64_t j = (uint64_t)(v - na);
-    u32x4 x = {0, 0, 0, 0};
-    if (mine && v == na + ndat) {
-        const uint64_t abits = dp->aad_len * 8, cbits = dp->len * 8;
-        x = SIV ? u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)cbits, (uint32_t)(cbits >> 32)}
-                : u32x4{bswap32((uint32_t)(abits >> 32)), bswap32((uint32_t)abits), bswap32((uint32_t)(cbits >> 32)),
-                        bswap32((uint32_t)cbits)};
-    } else if (mine && v >= 0 && v < na + ndat) {  // data or AAD
-        x = load_block_partial(data ? gptr<const uint8_t>(dp->in) : gptr<const uint8_t>(dp->aad),
-                               data ? j : (uint64_t)v, data ? dp->len : dp->aad_len);
-    }
-
-    // the lifts of this row's value, and of its lower half (32 places more)
-    const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));
-    u32x4 lift = {0x80u, 0, 0, 0};
-    if (after)
-        lift = group_lift(slot, 6, after);
-    const CONST_AS uint32_t *l32 = cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotTab8Off)) + 4 * after;
-    const u32x4 lift32 = {l32[0], l32[1], l32[2], l32[3]};
-
-    // the counter block, whitened; the counter dword is the lane's
-    const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(slot));
-    const uint32_t nr = dp->nr;
-    uint32_t w0 = dp->iv[0], w1 = dp->iv[1], w2 = dp->iv[2], cj0 = 1u;
-    const uint64_t jaddr = dp->j0;
-    if (SIV || jaddr) {
-        const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
-        w0 = jw[SIV ? 1 : 0], w1 = jw[SIV ? 2 : 1], w2 = jw[SIV ? 3 : 2];
-        cj0 = SIV ? jw[0] : bswap32(jw[3]);
-    }
-    const uint32_t c1 = SIV ? cj0 : cj0 + 1u;
-    const bool hot = AES && mine && v0 + 64 > na - 1 && v0 < na + ndat;  // E_K(J0) or a data block in this row
-    const bool ekrow = KIND == kGcm && mine && t == 0 && dp->z == 0 && na == 0;
-
-    const Tables<true, 0> tab(lds, lane);
-    if (AES)
-        st.store(lds_v, tab);
-#pragma unroll
-    for (int r = 0; r < kWinPer; ++r) {
-        const uint32_t q = threadIdx.x + (uint32_t)(r * NT);
-        if (512 % NT == 0 || q < 512)
-            lds_v[kRowWin / 16 + q] = win[r];
-    }
+    if (AES && BATCH)
+        st.store(lds_v, Tables<true, 0>(lds, threadIdx.x & 63));
     if (KIND == kGcm && blockIdx.x == 0 && threadIdx.x == 0)
         counters[0] = 0;  // reject count for this launch
-    lds_barrier();
 
-    u32x4 *ekw = lds_v + kRowSums / 16 + 16;
-#pragma unroll 1
-    for (int pass = ekrow ? 0 : 1; AES && pass < 2; ++pass) {
-        if (pass && !hot)
-            break;
-        const uint32_t ctr = pass ? (uint32_t)(v0 - na) + c1 + (uint32_t)lane : cj0;
-        uint32_t s0 = (SIV ? ctr : w0) ^ rk[0], s1 = (SIV ? w0 : w1) ^ rk[1], s2 = (SIV ? w1 : w2) ^ rk[2];
-        uint32_t s3 = (SIV ? w2 : bswap32(ctr)) ^ rk[3];
-        s0 = tab.rot(s0), s1 = tab.rot(s1), s2 = tab.rot(s2), s3 = tab.rot(s3);
-        const CONST_AS uint32_t *k = rk + 4;
-        uint32_t k0 = k[0], k1 = k[1], k2 = k[2], k3 = k[3];
-        uint32_t a[4][4];
-#pragma unroll 1
-        for (uint32_t r = 1;; ++r) {
-            ISSUE0(a, s0);
-            ISSUE1(a, s1);
-            ISSUE2(a, s2);
-            ISSUE3(a, s3);
-            if (r == nr)
-                break;
-            k += 4;  // the next round's key (the one after the last round key is never used)
-            const uint32_t n0 = k[0], n1 = k[1], n2 = k[2], n3 = k[3];
-            s0 = xor3(xor3(a[0][0], a[0][1], a[0][2]), a[0][3], tab.rot(k0));
-            s1 = xor3(xor3(a[1][0], a[1][1], a[1][2]), a[1][3], tab.rot(k1));
-            s2 = xor3(xor3(a[2][0], a[2][1], a[2][2]), a[2][3], tab.rot(k2));
-            s3 = xor3(xor3(a[3][0], a[3][1], a[3][2]), a[3][3], tab.rot(k3));
-            k0 = n0, k1 = n1, k2 = n2, k3 = n3;
+    for (uint32_t it = blockIdx.x, turn = 0; it < n_items; it += gridDim.x, ++turn) {
+        uint32_t tid = threadIdx.x;
+        if (BATCH)  // what depends on the lane alone is worked out again for each item rather than held in registers
+            asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
+        const int wave = (int)uniform(tid >> 6);
+        const Tables<true, 0> tab(lds, lane);
+        const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
+        uint32_t first = it * WAVES;
+        if (BATCH) {
+            const WorkItem w = load_const<WorkItem>(items + it);
+            dp = cptr<MsgDesc>(descs + w.msg);
+            first = w.first_tile;
         }
+        touch_lines(dp);
+        const uint64_t slot = dp->slot, T = dp->n_tiles;
+        u32x4 win[kWinPer];
+        {
+            const GLOBAL_AS u32x4 *src = gptr<const u32x4>(slot + kSlotLaneWinOff);
+#pragma unroll
+            for (int r = 0; r < kWinPer; ++r) {
+                const uint32_t q = tid + (uint32_t)(r * NT);
+                win[r] = q >= 32 && q < 512 ? src[64 * (q >> 5) + 31 + (q & 31)] : u32x4{0, 0, 0, 0};
+            }
+        }
+        const uint32_t gf = *(const CONST_AS uint32_t *)&dp->log2G;
+        const uint32_t log2G = gf & 0xffffu, G = 1u << log2G;
+        const bool finish = (gf >> 16) & 1u;
+        const int64_t t = (int64_t)first + wave - (int64_t)((0u - (uint32_t)T) & (G - 1u));
+        const bool mine = t >= 0 && t < (int64_t)T;
+
+        // this lane's block of the sequence and its bytes
+        const int64_t na = (int64_t)dp->na, ndat = (int64_t)dp->n;
+        const int64_t v0 = 64 * t - (int64_t)dp->z, v = v0 + lane;
+        const bool data = mine && v >= na && v < na + ndat;
+        const uint64_t j = (uint64_t)(v - na);
+        u32x4 x = {0, 0, 0, 0};
+        if (mine && v == na + ndat) {
+            const uint64_t abits = dp->aad_len * 8, cbits = dp->len * 8;
+            x = SIV ? u32x4{(uint32_t)abits, (uint32_t)(abits >> 32), (uint32_t)cbits, (uint32_t)(cbits >> 32)}
+                    : u32x4{bswap32((uint32_t)(abits >> 32)), bswap32((uint32_t)abits), bswap32((uint32_t)(cbits >> 32)),
+                            bswap32((uint32_t)cbits)};
+        } else if (mine && v >= 0 && v < na + ndat) {  // data or AAD
+            x = load_block_partial(data ? gptr<const uint8_t>(dp->in) : gptr<const uint8_t>(dp->aad),
+                                   data ? j : (uint64_t)v, data ? dp->len : dp->aad_len);
+        }
+
+        // the lifts of this row's value, and of its lower half (32 places more)
+        const uint32_t after = G - 1u - ((uint32_t)wave & (G - 1u));
+        u32x4 lift = {0x80u, 0, 0, 0};
+        if (after)
+            lift = group_lift(slot, 6, after);
+        const CONST_AS uint32_t *l32 = cptr<uint32_t>(reinterpret_cast<const void *>(slot + kSlotTab8Off)) + 4 * after;
+        const u32x4 lift32 = {l32[0], l32[1], l32[2], l32[3]};
+
+        // the counter block, whitened; the counter dword is the lane's
+        const CONST_AS uint32_t *rk = cptr<uint32_t>(reinterpret_cast<const void *>(slot));
+        const uint32_t nr = dp->nr;
+        uint32_t w0 = dp->iv[0], w1 = dp->iv[1], w2 = dp->iv[2], cj0 = 1u;
+        const uint64_t jaddr = dp->j0;
+        if (SIV || jaddr) {
+            const CONST_AS uint32_t *jw = cptr<uint32_t>(reinterpret_cast<const void *>(jaddr));
+            w0 = jw[SIV ? 1 : 0], w1 = jw[SIV ? 2 : 1], w2 = jw[SIV ? 3 : 2];
+            cj0 = SIV ? jw[0] : bswap32(jw[3]);
+        }
+        const uint32_t c1 = SIV ? cj0 : cj0 + 1u;
+        if (AES) {  // the round keys' four lines at once, not one after another in the rounds
+            const uint32_t l0 = rk[0], l1 = rk[16], l2 = rk[32], l3 = rk[48];
+            asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3));
+        }
+        // some lane needs a keystream block; the length block's needs E_K(J0)
+        const bool ekl = KIND == kGcm && mine && v == na + ndat;
+        const bool hot = AES && mine && ((v0 + 64 > na && v0 < na + ndat) || (KIND == kGcm && t + 1 == (int64_t)T));
+
+        if (AES && !BATCH)
+            st.store(lds_v, tab);
+#pragma unroll
+        for (int r = 0; r < kWinPer; ++r) {
+            const uint32_t q = tid + (uint32_t)(r * NT);
+            if (512 % NT == 0 || q < 512)
+                lds_v[kRowWin / 16 + q] = win[r];
+        }
+        lds_barrier();
+
+        if (hot) {
+            const uint32_t ctr = ekl ? cj0 : (uint32_t)(v0 - na) + c1 + (uint32_t)lane;
+            uint32_t s0 = (SIV ? ctr : w0) ^ rk[0], s1 = (SIV ? w0 : w1) ^ rk[1], s2 = (SIV ? w1 : w2) ^ rk[2];
+            uint32_t s3 = (SIV ? w2 : bswap32(ctr)) ^ rk[3];
+            s0 = tab.rot(s0), s1 = tab.rot(s1), s2 = tab.rot(s2), s3 = tab.rot(s3);
+            const CONST_AS uint32_t *k = rk + 4;
+            uint32_t k0 = k[0], k1 = k[1], k2 = k[2], k3 = k[3];
+            uint32_t a[4][4];
+#pragma unroll 1
+            for (uint32_t r = 1;; ++r) {
+                ISSUE0(a, s0);
+                ISSUE1(a, s1);
+                ISSUE2(a, s2);
+                ISSUE3(a, s3);
+                if (r == nr)
+                    break;
+                k += 4;  // the next round's key (the one after the last round key is never used)
+                const uint32_t n0 = k[0], n1 = k[1], n2 = k[2], n3 = k[3];
+                s0 = xor3(xor3(a[0][0], a[0][1], a[0][2]), a[0][3], tab.rot(k0));
+                s1 = xor3(xor3(a[1][0], a[1][1], a[1][2]), a[1][3], tab.rot(k1));
+                s2 = xor3(xor3(a[2][0], a[2][1], a[2][2]), a[2][3], tab.rot(k2));
+                s3 = xor3(xor3(a[3][0], a[3][1], a[3][2]), a[3][3], tab.rot(k3));
+                k0 = n0, k1 = n1, k2 = n2, k3 = n3;
+            }
 #define LAST(q, key)                                                                                                   \
-    (uint32_t)__builtin_amdgcn_bitop3_b32(tab.last01(a[q][q], a[q][((q) + 1) & 3]), tab.last23(a[q][((q) + 2) & 3], a[q][((q) + 3) & 3]), key, 0x56)
-        const u32x4 ks = {LAST(0, k0), LAST(1, k1), LAST(2, k2), LAST(3, k3)};
+        (uint32_t)__builtin_amdgcn_bitop3_b32(tab.last01(a[q][q], a[q][((q) + 1) & 3]), tab.last23(a[q][((q) + 2) & 3], a[q][((q) + 3) & 3]), key, 0x56)
+            const u32x4 ks = {LAST(0, k0), LAST(1, k1), LAST(2, k2), LAST(3, k3)};
 #undef LAST
-        if (KIND == kGcm && (pass ? v == na - 1 : lane == 0)) {
-            *ekw = ks;
-            partials[dp->tile_base + ((T + G - 1) >> log2G)] = ks;
+            if (ekl) {
+                *ekw = ks;
+                partials[dp->tile_base + ((T + G - 1) >> log2G)] = ks;
+            }
+            if (data) {
+                const u32x4 o = x ^ ks;
+                store_block_partial(gptr<uint8_t>(dp->out), j, dp->len, o);
+                x = (SIV || dp->op == 0) ? mask_block(o, j, dp->len) : x;
+            }
         }
-        if (pass && data) {
-            const u32x4 o = x ^ ks;
-            store_block_partial(gptr<uint8_t>(dp->out), j, dp->len, o);
-            x = (SIV || dp->op == 0) ? mask_block(o, j, dp->len) : x;
-        }
-    }
-    if (SIV)
-        x = rev_block(x);
+        if (SIV)
+            x = rev_block(x);
 
-    // x * H^(32 - n): the comb of gf_mul_lanewin in a loop, entries one step ahead
-    u32x4 y;
-    {
-        const uint32_t xm[4] = {x.x, x.y, x.z, x.w};
-        const P128 px = mem_to_poly(xm);
-        uint32_t aw[4] = {(uint32_t)px.lo, (uint32_t)(px.lo >> 32), (uint32_t)px.hi, (uint32_t)(px.hi >> 32)};
-        const uint8_t *base = lds + kRowWin + 16u * ((uint32_t)lane & 31u);
-        uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        u32x4 e[4];
+        // x * H^(32 - n): the comb of gf_mul_lanewin in a loop, entries one step ahead
+        u32x4 y;
+        {
+            const uint32_t xm[4] = {x.x, x.y, x.z, x.w};
+            const P128 px = mem_to_poly(xm);
+            uint32_t aw[4] = {(uint32_t)px.lo, (uint32_t)(px.lo >> 32), (uint32_t)px.hi, (uint32_t)(px.hi >> 32)};
+            const uint8_t *base = lds + kRowWin + 16u * ((uint32_t)lane & 31u);
+            uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            u32x4 e[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
-            e[w] = *reinterpret_cast<const u32x4 *>(base + 512u * (aw[w] >> 28));
-#pragma unroll 1
-        for (int q = 0; q < 8; ++q) {
-            u32x4 f[4];
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                f[w] = e[w];
-                aw[w] <<= 4;
+            for (int w = 0; w < 4; ++w)
                 e[w] = *reinterpret_cast<const u32x4 *>(base + 512u * (aw[w] >> 28));
-            }
+#pragma unroll 1
+            for (int q = 0; q < 8; ++q) {
+                u32x4 f[4];
 #pragma unroll
-            for (int i = 7; i > 0; --i)
-                acc[i] = __builtin_amdgcn_alignbit(acc[i], acc[i - 1], 28);  // acc <<= 4
-            acc[0] <<= 4;
+                for (int w = 0; w < 4; ++w) {
+                    f[w] = e[w];
+                    aw[w] <<= 4;
+                    e[w] = *reinterpret_cast<const u32x4 *>(base + 512u * (aw[w] >> 28));
+                }
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                acc[w] ^= f[w].x;
-                acc[w + 1] ^= f[w].y;
-                acc[w + 2] ^= f[w].z;
-                acc[w + 3] ^= f[w].w;
+                for (int i = 7; i > 0; --i)
+                    acc[i] = __builtin_amdgcn_alignbit(acc[i], acc[i - 1], 28);  // acc <<= 4
+                acc[0] <<= 4;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    acc[w] ^= f[w].x;
+                    acc[w + 1] ^= f[w].y;
+                    acc[w + 2] ^= f[w].z;
+                    acc[w + 3] ^= f[w].w;
+                }
             }
+            y = poly_to_mem(poly_reduce((uint64_t)acc[0] | ((uint64_t)acc[1] << 32), (uint64_t)acc[2] | ((uint64_t)acc[3] << 32),
+                                        (uint64_t)acc[4] | ((uint64_t)acc[5] << 32), (uint64_t)acc[6] | ((uint64_t)acc[7] << 32)));
         }
-        y = poly_to_mem(poly_reduce((uint64_t)acc[0] | ((uint64_t)acc[1] << 32), (uint64_t)acc[2] | ((uint64_t)acc[3] << 32),
-                                    (uint64_t)acc[4] | ((uint64_t)acc[5] << 32), (uint64_t)acc[6] | ((uint64_t)acc[7] << 32)));
+        u32x4 lo, hi;  // sums of the lower and the upper half-wave
+        {
+            const uint32_t w[4] = {half_wave_xor_u32(y.x), half_wave_xor_u32(y.y), half_wave_xor_u32(y.z),
+                                   half_wave_xor_u32(y.w)};
+            const auto q0 = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
+            const auto q1 = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
+            const auto q2 = __builtin_amdgcn_permlane32_swap(w[2], w[2], false, false);
+            const auto q3 = __builtin_amdgcn_permlane32_swap(w[3], w[3], false, false);
+            lo = u32x4{q0[0], q1[0], q2[0], q3[0]};
+            hi = u32x4{q0[1], q1[1], q2[1], q3[1]};
+        }
+        const u32x4 p = gf_mul2_wave(lo, lift32, hi, lift);
+        u32x4 *sums = lds_v + kRowSums / 16;
+        if (lane == 0)
+            sums[wave] = p;
+        if (finish && dp->op == 1)
+            __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
+        lds_barrier();
+        if (wave == (int)(turn % WAVES))
+            sum_groups<WAVES>(dp, sums, ekw, G, log2G, finish, false, first, (T + G - 1) >> log2G, partials);
+        if (!BATCH)
+            break;  // every workgroup has one item
     }
-    u32x4 lo, hi;  // sums of the lower and the upper half-wave
-    {
-        const uint32_t w[4] = {half_wave_xor_u32(y.x), half_wave_xor_u32(y.y), half_wave_xor_u32(y.z),
-                               half_wave_xor_u32(y.w)};
-        const auto q0 = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
-        const auto q1 = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
-        const auto q2 = __builtin_amdgcn_permlane32_swap(w[2], w[2], false, false);
-        const auto q3 = __builtin_amdgcn_permlane32_swap(w[3], w[3], false, false);
-        lo = u32x4{q0[0], q1[0], q2[0], q3[0]};
-        hi = u32x4{q0[1], q1[1], q2[1], q3[1]};
-    }
-    const u32x4 p = gf_mul2_wave(lo, lift32, hi, lift);
-    u32x4 *sums = lds_v + kRowSums / 16;
-    if (lane == 0)
-        sums[wave] = p;
-    if (finish && dp->op == 1)
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's output is out before a rejected one is cleared
-    lds_barrier();
-    if (wave == 0)
-        sum_groups<WAVES>(dp, sums, ekw, G, log2G, finish, false, first, (T + G - 1) >> log2G, partials);
 }
 
 // ---------------------------------------------------------------- verdict
@@ -2418,17 +2466,20 @@ hipError_t launch_key_setup(const uint8_t *const *keys, const uint32_t *key_lens
 template <int WAVES>
 static hipError_t launch_tiles_w(const MsgDesc *descs, const WorkItem *items, uint32_t n_items, const MsgDesc *single,
                                  const uint32_t *te0, u32x4 *partials, uint32_t *counters, uint32_t grid,
-                                 hipStream_t s)
+                                 bool rows, hipStream_t s)
 {
-    if (descs)
+    if (descs && rows)
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, true, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, MsgDesc{}, descs, items,
+                           n_items, te0, partials, counters);
+    else if (descs)
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, true, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, MsgDesc{}, descs,
                            items, n_items, te0, partials, counters);
     else if (single->op == 2)
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kCtr>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
                            nullptr, n_items, te0, partials, counters);
     else if (single->flags & kRows)
-        hipLaunchKernelGGL((k_gcm_rows<WAVES, kGcm>), dim3(n_items), dim3(WAVES * 64), 0, s, *single, te0, partials,
-                           counters);
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, false, kGcm>), dim3(n_items), dim3(WAVES * 64), 0, s, *single, nullptr,
+                           nullptr, n_items, te0, partials, counters);
     else
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kGcm>), dim3(grid), dim3(WAVES * 64), 0, s, *single, nullptr,
                            nullptr, n_items, te0, partials, counters);
@@ -2437,16 +2488,16 @@ static hipError_t launch_tiles_w(const MsgDesc *descs, const WorkItem *items, ui
 
 hipError_t launch_tiles(int waves, const MsgDesc *descs, const WorkItem *items, uint32_t n_items,
                         const MsgDesc *single, const uint32_t *te0, void *partials, uint32_t *counters, uint32_t grid,
-                        hipStream_t s)
+                        bool rows, hipStream_t s)
 {
     u32x4 *p = reinterpret_cast<u32x4 *>(partials);
     switch (waves) {
     case 8:
-        return launch_tiles_w<8>(descs, items, n_items, single, te0, p, counters, grid, s);
+        return launch_tiles_w<8>(descs, items, n_items, single, te0, p, counters, grid, rows, s);
     case 12:
-        return launch_tiles_w<12>(descs, items, n_items, single, te0, p, counters, grid, s);
+        return launch_tiles_w<12>(descs, items, n_items, single, te0, p, counters, grid, rows, s);
     case 16:
-        return launch_tiles_w<16>(descs, items, n_items, single, te0, p, counters, grid, s);
+        return launch_tiles_w<16>(descs, items, n_items, single, te0, p, counters, grid, rows, s);
     default:
         return hipErrorInvalidValue;
     }
@@ -2586,9 +2637,11 @@ static hipError_t launch_siv_tiles_w(int pass, const MsgDesc &d, uint32_t n_item
                                      uint32_t grid, hipStream_t s)
 {
     if (pass == 0 && (d.flags & kRows))
-        hipLaunchKernelGGL((k_gcm_rows<WAVES, kSivHash>), dim3(n_items), dim3(WAVES * 64), 0, s, d, te0, p, nullptr);
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, false, kSivHash>), dim3(n_items), dim3(WAVES * 64), 0, s, d, nullptr,
+                           nullptr, n_items, te0, p, nullptr);
     else if (pass == 2 && (d.flags & kRows))
-        hipLaunchKernelGGL((k_gcm_rows<WAVES, kSivDec>), dim3(n_items), dim3(WAVES * 64), 0, s, d, te0, p, nullptr);
+        hipLaunchKernelGGL((k_gcm_rows<WAVES, false, kSivDec>), dim3(n_items), dim3(WAVES * 64), 0, s, d, nullptr,
+                           nullptr, n_items, te0, p, nullptr);
     else if (pass == 0)
         hipLaunchKernelGGL((k_gcm_tiles<WAVES, false, kSivHash>), dim3(grid), dim3(WAVES * 64), 0, s, d, nullptr,
                            nullptr, n_items, te0, p, nullptr);

@@ -186,6 +186,16 @@ inline uint32_t batch_msg_log2B(uint64_t m, uint32_t waves, uint32_t cap)
     return std::min(l, std::max<uint32_t>(6, cap));
 }
 
+// Whether a batch of n messages, m GHASH blocks in all, goes to the row kernel
+// (one-row tiles, two workgroups of eight waves a compute unit).  A row takes it
+// 1400 cycles, bound by the vector units, where the tile kernel takes 523; but an
+// item of the tile kernel costs about 15000 cycles besides, most of them for the
+// 80 KiB of key tables, so that messages of less than some 17 rows are better off
+// with rows (1024 messages, median 4 KiB with 2 KiB of AAD: 50 us, 63 with tiles;
+// median 16 KiB: 115 and 93), and so is what gives every wave slot of the chip at
+// most a row (64 messages, median 16 KiB: 22 us, 34 with tiles).
+inline bool batch_rows(uint64_t n, uint64_t m, uint64_t cus) { return m <= 1024 * n || m <= 64 * 16 * cus; }
+
 // Workspace: a counter and reject list (4 + 4 * n_msgs bytes, rounded up to
 // 256), then per message its T tile partials followed by two 16-byte slots:
 // E_K(J0) (left by the tile-0 wave for the combine) and J0 (IVs other than
@@ -373,6 +383,7 @@ struct BatchPlan {
     bool any_decrypt = false;
     // messages that the tile kernel does not finish by itself, and decrypts among them
     bool any_combine = false, any_zerofill = false;
+    bool rows = false;  // all tiles are single rows, run by the row kernel
     uint64_t workspace_bytes() const { return workspace_counter_bytes(descs.size()) + 16 * partial_slots; }
 };
 
@@ -383,6 +394,7 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
     p->items.clear();
     p->total_tiles = p->partial_slots = p->payload = 0;
     p->any_decrypt = p->any_combine = p->any_zerofill = false;
+    p->rows = cap_log2B <= 6 && group_log2(waves) != 0;
     uint64_t tile_base = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const PlanMsg &j = msgs[i];
@@ -390,6 +402,8 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
         fill_desc(&p->descs[i], j.op, j.iv, j.aad, j.aad_len, j.in, j.out, j.len, j.tag, j.ok, slots.addr(j.key_slot),
                   slots.nr[j.key_slot], log2B, waves, tile_base);
         set_groups(&p->descs[i], waves, true);
+        if (p->rows)
+            p->descs[i].flags |= kRows;
         p->any_combine |= !(p->descs[i].flags & kFinish);
         p->any_zerofill |= !(p->descs[i].flags & kFinish) && j.op == 1;
         tile_base += p->descs[i].n_tiles + 2;  // partials, then the E_K(J0) and J0 slots

@@ -191,16 +191,16 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
         // a decrypt is accepted only once the device has written 1 here
         h_flags[i] = 0;
     }
-    if (n_items)
-        std::memcpy(h_item, plan.items.data(), n_items * sizeof(WorkItem));
     const uint32_t grid =
         (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(n_items, (uint64_t)ctx->cu_count * sh.gpc));
+    if (n_items)
+        std::memcpy(h_item, plan.items.data(), n_items * sizeof(WorkItem));
     hipError_t e = hipMemcpyAsync(sl.d_mem, sl.h_mem, desc_b + item_b, hipMemcpyHostToDevice, sl.stream);
     uint32_t *counters = reinterpret_cast<uint32_t *>(d_ws);
     uint8_t *partials = d_ws + workspace_counter_bytes(n);
     if (e == hipSuccess)
         e = launch_tiles((int)sh.waves, d_desc, d_item, (uint32_t)n_items, nullptr, ctx->d_tables, partials, counters,
-                         grid, sl.stream);
+                         grid, plan.rows, sl.stream);
     if (e == hipSuccess && plan.any_combine)
         e = launch_verdict(d_desc, n, nullptr, partials, counters, sl.stream);
     if (e == hipSuccess && plan.any_zerofill)

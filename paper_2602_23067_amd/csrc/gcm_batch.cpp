@@ -81,6 +81,7 @@ static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t
     b->payload_bytes = plan.payload;
     b->n_items = (uint32_t)plan.items.size();
     b->grid = std::max<uint32_t>(1, std::min<uint32_t>(b->n_items, (uint32_t)ctx->cu_count * sh.gpc));
+    spread_items(plan.descs, sh.waves, b->grid, &plan.items);
 
     const uint64_t desc_bytes = (uint64_t)n * sizeof(MsgDesc);
     const uint64_t item_bytes = (uint64_t)plan.items.size() * sizeof(WorkItem);

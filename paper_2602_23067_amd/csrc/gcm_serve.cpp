@@ -193,6 +193,7 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
     }
     const uint32_t grid =
         (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(n_items, (uint64_t)ctx->cu_count * sh.gpc));
+    spread_items(plan.descs, sh.waves, grid, &plan.items);
     if (n_items)
         std::memcpy(h_item, plan.items.data(), n_items * sizeof(WorkItem));
     hipError_t e = hipMemcpyAsync(sl.d_mem, sl.h_mem, desc_b + item_b, hipMemcpyHostToDevice, sl.stream);

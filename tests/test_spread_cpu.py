@@ -1,0 +1,20 @@
+"""The order in which a batch's work items are handed to its workgroups, on the CPU under the
+address and undefined-behaviour sanitizers, on randomized batches under every launch shape."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.timeout(300)
+def test_work_list_order_under_sanitizers(tmp_path):
+    exe = tmp_path / "spread"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Werror",
+                    "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer",
+                    "-I", os.path.join(ROOT, "paper_2602_23067_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "spread_harness.cpp"), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=250)
+    assert out.returncode == 0, out.stderr[-4000:]
+    assert "OK" in out.stdout

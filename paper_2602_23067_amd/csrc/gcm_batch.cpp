@@ -166,7 +166,7 @@ hipError_t gcm::batch_enqueue(gcm_batch *b, hipStream_t s)
     if (e == hipSuccess && b->any_combine)
         e = launch_verdict(b->d_descs, b->n, nullptr, partials, counters, s);
     if (e == hipSuccess && b->any_zerofill)
-        e = launch_zerofill(b->d_descs, nullptr, counters, (uint32_t)std::max(1, ctx->cu_count * 4), s);
+        e = launch_zerofill(b->d_descs, counters, (uint32_t)std::max(1, ctx->cu_count * 4), s);
     return e;
 }
 

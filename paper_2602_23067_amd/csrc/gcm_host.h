@@ -207,19 +207,18 @@ hipError_t launch_fold(const void *vals, uint32_t k, const void *ekj0, uint8_t *
                        uint32_t tag_len, uint64_t slot, const uint32_t lenblk[4], hipStream_t s);
 // device address of the fixed scratch array on `device` (looked up once per device)
 hipError_t scratch_address(int device, void **out);
-hipError_t launch_zerofill(const MsgDesc *descs, const MsgDesc *single, const uint32_t *counters, uint32_t grid,
-                           hipStream_t s);
+// clears the outputs of a batch's rejected messages
+hipError_t launch_zerofill(const MsgDesc *descs, const uint32_t *counters, uint32_t grid, hipStream_t s);
 // AES-GCM-SIV: message keys into the slot at out_slot (and, with tag_in, the
 // counter block from the received tag at ctr_out); the tile passes (0 POLYVAL
 // only, 1 counter mode only, 2 counter mode + POLYVAL of the output); the tag
-// from the POLYVAL value at g (encrypt: tag_out and the counter block;
-// decrypt: compare with tag_in, accept flag and reject count)
+// from the POLYVAL pass (d.op 0: the tag at d.tag and the counter block; 1:
+// compared with d.tag, accept flag, a rejected output cleared)
 hipError_t launch_siv_derive(uint64_t kgk_slot, const uint8_t nonce[12], uint64_t out_slot, const uint8_t *tag_in,
                              void *ctr_out, const uint32_t *te0, const uint32_t *sbox, const void *frob, hipStream_t s);
 hipError_t launch_siv_tiles(int waves, int pass, const MsgDesc &d, uint32_t n_items, const uint32_t *te0,
                             void *partials, uint32_t grid, hipStream_t s);
-hipError_t launch_siv_tag(uint64_t slot, const void *g, const uint8_t nonce[12], uint8_t *tag_out, void *ctr_out,
-                          const uint8_t *tag_in, int32_t *ok, uint32_t *counters, const uint32_t *te0,
-                          const uint32_t *sbox, hipStream_t s);
+hipError_t launch_siv_verdict(const MsgDesc &d, const uint8_t nonce[12], void *ctr_out, const void *partials,
+                              const uint32_t *te0, const uint32_t *sbox, hipStream_t s);
 
 }  // namespace gcm

@@ -105,7 +105,6 @@ int siv_common(gcm_ctx *ctx, uint32_t op, uint32_t slot, const uint8_t *nonce, s
     uint8_t *base = reinterpret_cast<uint8_t *>(ws);
     const uint64_t mslot = (uint64_t)base;
     uint8_t *gval = base + kSivStateOff, *ctr = base + kSivStateOff + 16;
-    uint32_t *counters = reinterpret_cast<uint32_t *>(base + kSivTilesOff);
     uint8_t *partials = base + kSivTilesOff + workspace_counter_bytes(1);
     static const uint8_t zero_iv[12] = {0};
 
@@ -123,21 +122,12 @@ int siv_common(gcm_ctx *ctx, uint32_t op, uint32_t slot, const uint8_t *nonce, s
     rc = launch_siv_pass(ctx, op == 0 ? 0 : 2, d, waves, gpc, partials, s);
     if (rc)
         return rc;
-    if (!(d.flags & kFinish))
-        e = launch_verdict(nullptr, 1, &d, partials, counters, s);
-    if (e == hipSuccess)
-        e = launch_siv_tag(mslot, gval, nonce, op == 0 ? tag_d : nullptr, ctr, op == 1 ? tag_d : nullptr, ok_d,
-                           counters, ctx->d_tables, ctx->d_tables + 256, s);
+    d.tag = (uint64_t)tag_d;
+    e = launch_siv_verdict(d, nonce, ctr, partials, ctx->d_tables, ctx->d_tables + 256, s);
     if (e != hipSuccess)
         return fail_hip(e, "GCM-SIV kernel launch");
-    if (op == 1) {
-        const uint64_t chunks = (len / 16 + 255) / 256;
-        const uint32_t zgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(chunks, 4096));
-        e = launch_zerofill(nullptr, &d, counters, zgrid, s);
-        if (e != hipSuccess)
-            return fail_hip(e, "zero-fill launch");
+    if (op == 1)
         return GCM_OK;
-    }
     if (len == 0)
         return GCM_OK;
     // encrypt: counter mode from the tag, over the data blocks alone

@@ -508,7 +508,9 @@ int gcm_set_launch(gcm_ctx *ctx, uint32_t log2_tile_blocks, uint32_t waves_per_g
 
 /* Fan-in of the reduction tree over tile partials (the paper's combine of
  * partial GHASH values): 2, 4, 8 or 16 children per node; 0 = automatic
- * (the autotune cache, else 2).  Results never depend on it. */
+ * (the autotune cache, else 2).  Only streams and the host pipeline reduce by a
+ * tree; everywhere else partials are lifted where they are formed and XORed.
+ * Results never depend on it. */
 int gcm_set_combine(gcm_ctx *ctx, uint32_t fanin);
 
 /* Result of an autotune search (also the answer of gcm_launch_plan). */

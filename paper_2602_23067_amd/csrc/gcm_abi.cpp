@@ -687,7 +687,7 @@ static int oneshot(gcm_ctx *ctx, uint32_t op, const uint8_t *key, size_t key_len
     if (rc)
         return rc;
     // the tag (16 bytes) and the accept flag (4 bytes): in the mapped result
-    // block, which the combine reads and writes directly, else on the device
+    // block, which the kernels read and write directly, else on the device
     // with copies
     const bool mapped = ctx->d_map != nullptr;
     uint8_t *d_tag = mapped ? ctx->d_map : ctx->d_io;

@@ -94,12 +94,12 @@ struct MsgDesc {
     uint32_t nr;         // AES rounds
     uint32_t groups;     // workgroup items for this message
     alignas(4) uint16_t log2G;  // the tile kernel leaves one partial for 2^log2G consecutive tiles, counted from the last one
-    uint16_t flags;             // kFinish, kMerge
+    uint16_t flags;             // kFinish, kMerge, kRows
     uint64_t j0;         // device address of J0 (16 bytes) for IVs other than 96 bits; 0: J0 = IV || 0^31 || 1
     uint32_t tag_len;    // tag bytes written (encrypt) or compared (decrypt): 16, or 15, 14, 13, 12, 8, 4
     uint32_t ctr_off;    // a streamed segment: data blocks that precede it, added to the counters
     uint64_t lift;       // with yout: the combine multiplies the segment's GHASH value by H^lift (< 2^40)
-    uint64_t yout;       // the combine writes the segment's GHASH value here instead of forming a tag
+    uint64_t yout;       // the GHASH value goes here instead of into a tag (a streamed segment, a POLYVAL pass)
 };
 
 // MsgDesc.flags.  kFinish: the message has one group, and the tile kernel forms

@@ -10,16 +10,23 @@
 //                                per-lane Horner over the ciphertext with the
 //                                fixed multiplier H^64, then a per-lane
 //                                fix-up product and an XOR across the wave
-//                                -> one 16-byte partial.
-//   k_gcm_combine                per message: tree over the tile partials,
-//                                final *H, xor E_K(J0) -> tag / accept flag.
-//   k_gcm_zerofill               zero the output of every rejected message.
+//                                -> one value, and one 16-byte partial for
+//                                the tiles of a workgroup, lifted past what
+//                                follows it; a message of one workgroup is
+//                                finished here.
+//   k_gcm_rows                   the same for messages of one-row tiles.
+//   k_gcm_verdict                XOR of a message's partials, xor E_K(J0) ->
+//                                tag / accept flag, and a rejected output
+//                                cleared (a batch's by k_gcm_zerofill).
+//   k_gcm_combine                streams and the host pipeline, whose tiles
+//                                leave one partial each that nothing has
+//                                lifted: a tree over them.
 //
 // AES-GCM-SIV (RFC 8452) reuses the same machinery: k_siv_derive builds a
-// per-message key slot from the key-generating key and the nonce,
-// k_siv_tiles runs POLYVAL (as GHASH over byte-reversed blocks), counter
-// mode with the little-endian counter, or both fused, and k_siv_tag forms or
-// checks the tag.
+// per-message key slot from the key-generating key and the nonce, the tile and
+// row kernels run POLYVAL (as GHASH over byte-reversed blocks), counter
+// mode with the little-endian counter, or both fused, and k_siv_verdict forms
+// or checks the tag.
 //
 // No MFMA: the work is byte lookups and XORs, not a real-valued contraction.
 #include <hip/hip_runtime.h>
@@ -2318,8 +2325,8 @@ __global__ __launch_bounds__(256) void k_gcm_zerofill(const MsgDesc *__restrict_
 // POLYVAL(H, X_1..X_s) = BR(GHASH_H'(BR(X_1), ..., BR(X_s))) where H' is
 // BR(H) times x in GHASH's field (RFC 8452 appendix A).  A per-message slot
 // holds the derived encryption key's round keys and H' with every GHASH table
-// of an ordinary key slot, so the tiles, the lane fix-ups and the combine
-// tree run unchanged on byte-reversed blocks.  The counter block is the tag
+// of an ordinary key slot, so the tiles, the lane fix-ups and the group
+// lifts run unchanged on byte-reversed blocks.  The counter block is the tag
 // with the top bit of byte 15 set; its bytes 0..3 (memory-order dword 0) are
 // a little-endian 32-bit counter, so dword 0 is the column that varies, where
 // GCM's counter varies column 3.

@@ -30,7 +30,7 @@ constexpr uint64_t kMaxAad = (1ull << 61) - 1;   // < 2^64 bits
 
 // A launch shape: wave tile size (log2 blocks; for a batch, the cap on its
 // messages' tile sizes), waves per workgroup, resident workgroups per compute
-// unit, and the fan-in of the reduction tree over tile partials.  Results
+// unit, and the fan-in of the tree over tile partials (streams, pipeline).  Results
 // never depend on it, only speed does.
 struct Shape {
     uint32_t log2B = 16, waves = 16, gpc = 1, fanin = 2;
@@ -198,7 +198,7 @@ inline bool batch_rows(uint64_t n, uint64_t m, uint64_t cus) { return m <= 1024 
 
 // Workspace: a counter and reject list (4 + 4 * n_msgs bytes, rounded up to
 // 256), then per message its T tile partials followed by two 16-byte slots:
-// E_K(J0) (left by the tile-0 wave for the combine) and J0 (IVs other than
+// E_K(J0) (left by the tile or row kernel, after the partials) and J0 (IVs other than
 // 96 bits).
 inline uint64_t workspace_counter_bytes(uint64_t n_msgs) { return ((4 + 4 * n_msgs) + 255) / 256 * 256; }
 inline uint64_t workspace_bytes_for(uint64_t total_tiles, uint64_t n_msgs)
@@ -240,9 +240,9 @@ inline void fill_desc(MsgDesc *d, uint32_t op, const uint8_t *iv, uint64_t aad, 
 
 // Tiles whose partials a workgroup of `waves` waves sums into one: the largest
 // power of two that divides the wave count (its groups then never straddle a
-// work item).  The sum is a product and an XOR in the tile kernel, where the
-// combine would spend a level of its tree on it: with 16 waves a 1 GiB message
-// leaves 257 partials instead of 4097.
+// work item).  The sum is a product and an XOR in the tile kernel, where a tree
+// would spend a level on it: with 16 waves a 1 GiB message leaves 257 partials
+// instead of 4097.
 inline uint16_t group_log2(uint32_t waves) { return waves == 16 ? 4 : waves == 8 ? 3 : waves == 12 ? 2 : 0; }
 
 // tiles that a launch of the whole message runs, and partials it leaves

@@ -7,7 +7,7 @@
 //      (submit -> result known on the host),
 //   2. admits waiting requests in arrival order while the budget allows,
 //   3. packs admitted requests into a batch and launches it on a free stream
-//      slot -- the same persistent tile kernel, combine and zero-fill as
+//      slot -- the same persistent launch, verdict and zero-fill as
 //      gcm_batch -- while earlier batches are still running.
 // Requests that arrive while others are on the GPU are admitted as soon as
 // budget and a stream slot free up; results do not depend on how requests

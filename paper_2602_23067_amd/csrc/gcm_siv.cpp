@@ -7,14 +7,12 @@
 //                                 and the nonce, expanded into a key slot in
 //                                 the workspace (encryption round keys, H'
 //                                 and every GHASH table for H').
-//   k_siv_tiles (hash)            encrypt: POLYVAL of AAD and plaintext as
-//                                 GHASH_H' over byte-reversed blocks, in
-//                                 tiles; the combine writes the value.
-//   k_siv_tag                     tag = AES(POLYVAL ^ nonce, msb cleared).
-//   k_siv_tiles (ctr)             encrypt: counter mode from the tag.
+//   k_gcm_tiles or k_gcm_rows     encrypt: POLYVAL of AAD and plaintext as
+//                                 GHASH_H' over byte-reversed blocks.
+//   k_siv_verdict                 tag = AES(POLYVAL ^ nonce, msb cleared).
+//   k_gcm_tiles                   encrypt: counter mode from the tag.
 // Decrypt-verify fuses counter mode with the POLYVAL of its output (one
-// pass), then k_siv_tag compares tags and the zero-fill clears a rejected
-// plaintext.
+// pass), then k_siv_verdict compares tags and clears a rejected plaintext.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

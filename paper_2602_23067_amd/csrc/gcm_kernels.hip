@@ -1644,9 +1644,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
     }
     for (uint32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
         const CONST_AS MsgDesc *dp = (const CONST_AS MsgDesc *)__builtin_amdgcn_kernarg_segment_ptr();  // `single`
+        const CONST_AS MsgDesc *next = dp;
         uint32_t first, msg = 0;
         if (BATCH) {
             const WorkItem w = load_const<WorkItem>(items + it);
+            const uint32_t nit = it + gridDim.x;
+            next = cptr<MsgDesc>(descs + (nit < n_items ? cptr<WorkItem>(items + nit)->msg : w.msg));
             dp = cptr<MsgDesc>(descs + w.msg);
             touch_lines(dp);
             first = w.first_tile;
@@ -1667,6 +1670,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
         const bool mine = t >= 0 && t < (int64_t)dp->tile_hi - (int64_t)merge;
         t += merge;
         const bool fresh = BATCH ? msg != cur_msg : turn == 0;
+        uint64_t next_slot = 0;
+        uint32_t ahead = 0;
         if (BATCH && fresh) {
             // a new message: its key's GHASH tables (unless staged already) and
             // its round-2 words
@@ -1675,6 +1680,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
             StageKeys<WAVES * 64> sk;
             if (stage)
                 sk.load(slot);
+            next_slot = next->slot;
             cs.load(dp);
             lds_barrier();  // the last item's reads, and the T-tables before the first
             if (stage) {
@@ -1701,6 +1707,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
                 cs.hc = uniform(f[1].x);
             }
         }
+        if (BATCH && K::gh && fresh && next_slot != cur_slot && threadIdx.x < 640) {
+            // the next item's tables into this XCD's L2, a word of each 128-byte
+            // line: 1024 messages, median 16 KiB, a key each, 93.9 -> 90.4 us
+            const uint32_t q = threadIdx.x;
+            ahead = *gptr<const uint32_t>(next_slot + (q < 512 ? kSlotTab8Off + 128 * q : kSlotLaneWinOff + 128 * (q - 512)));
+        }
         const uint64_t nparts = (run + G - 1) >> log2G;
         u32x4 *ekg = partials + (K::gh ? dp->tile_base + nparts : 0);
         if (mine) {
@@ -1712,6 +1724,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
             else
                 p = wave_tile<14, KIND>(dp, (uint64_t)t, head, cs, lds, tab, gk, te, ekg);
         }
+        if (BATCH)
+            asm volatile("" ::"v"(ahead));
         const uint32_t my_turn = turn++;
         if (!K::gh)
             continue;

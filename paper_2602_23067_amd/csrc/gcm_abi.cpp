@@ -446,8 +446,9 @@ Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_
           // the longest item decides, with small ones the start of each does (16 messages, median 8 MiB:
           // 422 us with 2^12, 390 with 2^11, 421 with 2^9; 256 of 64 KiB: 83 us with 2^10, 68 with 2^9, 75 with 2^8)
         sh.log2B = std::min<uint32_t>(
-            12, std::max<uint32_t>(9, heuristic_log2B(std::max<uint64_t>(1, m),
-                                                      (uint64_t)ctx->cu_count * sh.gpc * sh.waves) - 1));
+            12, std::max<uint32_t>(small ? 9 : 8, heuristic_log2B(std::max<uint64_t>(1, m),
+                                                                  (uint64_t)ctx->cu_count * sh.gpc * sh.waves) -
+                                                      (small ? 1 : 0)));
     return sh;
 }
 

@@ -114,8 +114,8 @@ static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t
 int gcm::batch_create_locked(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
                              const Shape *forced, gcm_batch **out)
 {
-    // One-row tiles have more partials and items: where the context's memory
-    // does not hold them, the plan with larger tiles is tried.
+    // Small tiles have more partials and items: where the context's memory does
+    // not hold them, the plan with larger tiles is tried.
     int rc = create_planned(ctx, jobs, n, base_d, base_bytes, forced, true, out);
     if (rc == GCM_E_NOMEM && !forced)
         rc = create_planned(ctx, jobs, n, base_d, base_bytes, forced, false, out);

@@ -137,6 +137,7 @@ void stream_pool_release(gcm_ctx *ctx);
 // Launch shape of a batch of n messages and `payload` bytes holding m GHASH
 // blocks in all: explicit settings, else the batch autotune cache, else the
 // heuristic (tile cap from the single-launch heuristic, 16 waves).
+// small: tiles as small as is fastest; else, where memory is short, larger ones
 Shape batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m, bool small = true);
 // the key table as the planner sees it
 SlotView slot_view(const gcm_ctx *ctx);

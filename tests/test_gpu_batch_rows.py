@@ -91,3 +91,14 @@ def test_every_partial_block(ctx, shape):
 def test_many_items_in_one_launch(ctx, n, size):
     r = np.random.default_rng(n)
     run(ctx, [(int(r.integers(0, 600)), int(r.integers(0, 2 * size))) for _ in range(n)], 1, 4)
+
+
+def test_memory_for_larger_tiles_only():
+    # four messages of 200 KiB: 15 KiB of plan and partials with one-row tiles, 5 KiB with the larger
+    # tiles, beside the context's tables (see test_gpu_serve.py) and four key slots
+    slot_bytes = 2048 + 65536 + 40 * 8192 + 16384
+    c = gcm.Context(device=0, hbm_budget=5 * 256 * 4 + 47 * 4096 * 16 + 4 * slot_bytes + 256 + 8192, key_slots=4)
+    try:
+        run(c, [(0, 200 * 1024)] * 4, 0, 5)
+    finally:
+        c.close()

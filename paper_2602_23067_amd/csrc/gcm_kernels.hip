@@ -35,6 +35,7 @@
 #include <mutex>
 
 #include "gcm_internal.h"
+#include "gcm_plan.h"
 
 namespace gcm {
 
@@ -2028,6 +2029,7 @@ __global__ __launch_bounds__(256) void k_gcm_verdict(MsgDesc single, const MsgDe
     s = wave_xor_reduce(s);
     if (lane == 0)
         sh[wave] = s;
+    asm volatile("" ::"v"(want));  // every wave has the expected tag before the flag, which may lie in it, is written
     lds_barrier();
     s = sh[0] ^ sh[1] ^ sh[2] ^ sh[3];
     if (!(flags & kRows)) {
@@ -2496,6 +2498,7 @@ __global__ __launch_bounds__(256) void k_siv_verdict(MsgDesc d, SivArg na, u32x4
         if (lane == 0)
             sh[wave] = s;
     }
+    asm volatile("" ::"v"(want));  // before the flag, which may lie in the expected tag, is written
     lds_barrier();
     if (!formed) {
         s = sh[0] ^ sh[1] ^ sh[2] ^ sh[3];
@@ -2665,13 +2668,6 @@ hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *
     return hipGetLastError();
 }
 
-// workgroups of a verdict: on decrypt enough to clear a rejected output at the memory's rate
-static uint32_t verdict_grid(const MsgDesc &d)
-{
-    const uint64_t chunks = (d.len / 16 + 255) / 256;
-    return d.op != 1 || chunks < 1 ? 1 : chunks < 1024 ? (uint32_t)chunks : 1024;
-}
-
 hipError_t launch_verdict(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
                           uint32_t *counters, hipStream_t s)
 {
@@ -2679,7 +2675,7 @@ hipError_t launch_verdict(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *
     if (descs) {
         hipLaunchKernelGGL(k_gcm_verdict<true>, dim3(n_msgs), dim3(256), 0, s, MsgDesc{}, descs, p, counters);
     } else {
-        const uint32_t grid = single->yout ? 1 : verdict_grid(*single);
+        const uint32_t grid = single->yout ? 1 : verdict_groups(*single);
         hipLaunchKernelGGL(k_gcm_verdict<false>, dim3(grid), dim3(256), 0, s, *single, nullptr, p, counters);
     }
     return hipGetLastError();
@@ -2732,7 +2728,7 @@ hipError_t launch_siv_verdict(const MsgDesc &d, const uint8_t nonce[12], void *c
     for (int i = 0; i < 3; ++i)
         a.nonce[i] = (uint32_t)nonce[4 * i] | ((uint32_t)nonce[4 * i + 1] << 8) | ((uint32_t)nonce[4 * i + 2] << 16) |
                      ((uint32_t)nonce[4 * i + 3] << 24);
-    hipLaunchKernelGGL(k_siv_verdict, dim3(verdict_grid(d)), dim3(256), 0, s, d, a, reinterpret_cast<u32x4 *>(ctr_out),
+    hipLaunchKernelGGL(k_siv_verdict, dim3(verdict_groups(d)), dim3(256), 0, s, d, a, reinterpret_cast<u32x4 *>(ctr_out),
                        reinterpret_cast<const u32x4 *>(partials), te0, sbox);
     return hipGetLastError();
 }

@@ -275,6 +275,18 @@ inline void set_groups_single(MsgDesc *d, uint32_t waves, uint64_t slots)
         d->flags |= kRows;
 }
 
+// Workgroups of a single message's verdict: on decrypt enough to clear a
+// rejected output at the memory's rate.  Each of them reads the expected tag and
+// the first writes the accept flag, so that a flag that lies in the tag leaves
+// room for one only.
+inline uint32_t verdict_groups(const MsgDesc &d)
+{
+    const uint64_t chunks = (d.len / 16 + 255) / 256;
+    if (d.op != 1 || chunks < 1 || ranges_overlap(d.ok, 4, d.tag, d.tag_len))
+        return 1;
+    return (uint32_t)std::min<uint64_t>(chunks, 1024);
+}
+
 // Device buffers of one message: NULL with a non-zero length, 16-byte
 // alignment of AAD and payload, and aliasing.  The output may equal the
 // input exactly (in place) but may not overlap it otherwise, nor overlap the

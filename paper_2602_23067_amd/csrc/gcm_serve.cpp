@@ -57,6 +57,7 @@ struct Slot {
     uint8_t *h_mem = nullptr;  // pinned: descs | items | flags
     uint64_t h_bytes = 0;
     uint64_t flag_off = 0;  // offset of the accept flags in both blocks
+    bool tight = false;     // memory for small tiles was refused: not asked for again
 };
 
 uint64_t align256(uint64_t x) { return (x + 255) / 256 * 256; }
@@ -163,18 +164,29 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
         total_m += ghash_blocks(r.aad_len, r.len);
         payload += r.len;
     }
+    // As in gcm_batch_create: small tiles have more partials and items, and where
+    // the memory does not hold them the plan with larger tiles is tried.
     BatchPlan plan;
     Shape sh;
-    {
-        std::lock_guard<std::mutex> g(ctx->mu);  // key table and autotune caches
-        sh = batch_shape(ctx, n, payload, total_m);
-        plan_batch(msgs.data(), n, slot_view(ctx), sh.waves, sh.log2B, &plan);
+    uint64_t n_items, desc_b, item_b, flag_b, dbytes;
+    int rc = GCM_OK;
+    for (const bool small : {true, false}) {
+        {
+            std::lock_guard<std::mutex> g(ctx->mu);  // key table and autotune caches
+            sh = batch_shape(ctx, n, payload, total_m, small);
+            plan_batch(msgs.data(), n, slot_view(ctx), sh.waves, sh.log2B, &plan);
+        }
+        n_items = plan.items.size();
+        desc_b = align256(n * sizeof(MsgDesc)), item_b = align256(n_items * sizeof(WorkItem));
+        flag_b = align256(4ull * n);
+        dbytes = desc_b + item_b + flag_b + plan.workspace_bytes();
+        if (small && sl.tight && dbytes > sl.d_bytes)
+            continue;
+        rc = slot_reserve(s, sl, dbytes, desc_b + item_b + flag_b);
+        if (rc != GCM_E_NOMEM)
+            break;
+        sl.tight = true;
     }
-    const uint64_t n_items = plan.items.size();
-    const uint64_t desc_b = align256(n * sizeof(MsgDesc)), item_b = align256(n_items * sizeof(WorkItem));
-    const uint64_t flag_b = align256(4ull * n), ws_b = plan.workspace_bytes();
-    const uint64_t dbytes = desc_b + item_b + flag_b + ws_b;
-    int rc = slot_reserve(s, sl, dbytes, desc_b + item_b + flag_b);
     if (rc)
         return rc;
     MsgDesc *h_desc = reinterpret_cast<MsgDesc *>(sl.h_mem);

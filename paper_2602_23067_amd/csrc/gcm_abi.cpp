@@ -72,6 +72,7 @@ int gcm::ctx_alloc(gcm_ctx *ctx, void **p, uint64_t bytes)
                     (unsigned long long)bytes, (unsigned long long)ctx->used, (unsigned long long)ctx->budget);
     hipError_t e = hipMalloc(p, bytes ? bytes : 1);
     if (e != hipSuccess) {
+        (void)hipGetLastError();  // handled here, and not to be reported by the next launch
         *p = nullptr;
         return fail(GCM_E_NOMEM, "hipMalloc(%llu): %s", (unsigned long long)bytes, hipGetErrorString(e));
     }

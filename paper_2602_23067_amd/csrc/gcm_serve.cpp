@@ -122,6 +122,7 @@ static int slot_reserve(gcm_serve *s, Slot &sl, uint64_t dbytes, uint64_t hbytes
         sl.h_bytes = 0;
         const uint64_t want = std::max<uint64_t>(hbytes, 1ull << 16);
         hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&sl.h_mem), want, hipHostMallocDefault);
+        (void)hipGetLastError();  // a failure is handled here, and not to be reported by the next launch
         if (e != hipSuccess)
             return fail(GCM_E_NOMEM, "serving staging: hipHostMalloc: %s", hipGetErrorString(e));
         sl.h_bytes = want;

@@ -418,8 +418,13 @@ Shape gcm::message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, u
     return sh;
 }
 
-Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m, bool small)
+Shape gcm::batch_shape(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small)
 {
+    uint64_t m = 0, payload = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        m += ghash_blocks(msgs[i].aad_len, msgs[i].len);
+        payload += msgs[i].len;
+    }
     Shape sh;
     TuneEntry t;
     bool tuned = false;
@@ -439,17 +444,15 @@ Shape gcm::batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_
     }
     sh.waves = ctx->cfg_waves ? ctx->cfg_waves : tuned ? t.waves : 16;
     sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : (tuned && t.gpc) ? t.gpc : (uint32_t)max_groups_per_cu((int)sh.waves);
+    const uint64_t groups = (uint64_t)ctx->cu_count * sh.gpc;
     if (ctx->cfg_log2B)
         sh.log2B = ctx->cfg_log2B;
     else if (tuned)
         sh.log2B = t.log2B;
-    else  // half the single-launch tile size of the whole batch's blocks, within 2^9..2^12: with large tiles
-          // the longest item decides, with small ones the start of each does (16 messages, median 8 MiB:
-          // 422 us with 2^12, 390 with 2^11, 421 with 2^9; 256 of 64 KiB: 83 us with 2^10, 68 with 2^9, 75 with 2^8)
-        sh.log2B = std::min<uint32_t>(
-            12, std::max<uint32_t>(small ? 9 : 8, heuristic_log2B(std::max<uint64_t>(1, m),
-                                                                  (uint64_t)ctx->cu_count * sh.gpc * sh.waves) -
-                                                      (small ? 1 : 0)));
+    else if (small)
+        sh.log2B = batch_cap_log2B(msgs, n, slot_view(ctx), sh.waves, groups);
+    else  // the single-launch tile size of the whole batch's blocks, within 2^8..2^12
+        sh.log2B = std::min<uint32_t>(12, std::max<uint32_t>(8, heuristic_log2B(std::max<uint64_t>(1, m), groups * sh.waves)));
     return sh;
 }
 

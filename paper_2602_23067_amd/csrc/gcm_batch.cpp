@@ -51,13 +51,9 @@ int gcm::plan_jobs(const gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t 
         if (check_job(jobs[i], i, base_bytes, sv, &err))
             return plan_error(err);
     std::vector<PlanMsg> msgs(n);
-    uint64_t total_m = 0, payload = 0;
-    for (uint32_t i = 0; i < n; ++i) {
+    for (uint32_t i = 0; i < n; ++i)
         msgs[i] = plan_msg_from_job(jobs[i], (uint64_t)base_d);
-        total_m += ghash_blocks(jobs[i].aad_len, jobs[i].len);
-        payload += jobs[i].len;
-    }
-    const Shape sh = forced ? *forced : batch_shape(ctx, n, payload, total_m, small);
+    const Shape sh = forced ? *forced : batch_shape(ctx, msgs.data(), n, small);
     plan_batch(msgs.data(), n, sv, sh.waves, sh.log2B, plan);
     *sh_out = sh;
     return GCM_OK;

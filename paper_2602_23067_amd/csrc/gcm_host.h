@@ -134,11 +134,10 @@ uint64_t resident_bound(const gcm_ctx *ctx);
 // frees the buffers kept for streamed messages (caller holds ctx->mu; no
 // queued work uses them)
 void stream_pool_release(gcm_ctx *ctx);
-// Launch shape of a batch of n messages and `payload` bytes holding m GHASH
-// blocks in all: explicit settings, else the batch autotune cache, else the
-// heuristic (tile cap from the single-launch heuristic, 16 waves).
+// Launch shape of a batch of n messages: explicit settings, else the batch
+// autotune cache, else the rules of gcm_plan.h (rows, or tiles and their cap).
 // small: tiles as small as is fastest; else, where memory is short, larger ones
-Shape batch_shape(const gcm_ctx *ctx, uint64_t n, uint64_t payload, uint64_t m, bool small = true);
+Shape batch_shape(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small = true);
 // the key table as the planner sees it
 SlotView slot_view(const gcm_ctx *ctx);
 // lengths and device buffers of one message (see check_buffers)

@@ -149,7 +149,6 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
     gcm_ctx *ctx = s->ctx;
     const uint32_t n = (uint32_t)batch.size();
     std::vector<PlanMsg> msgs(n);
-    uint64_t total_m = 0, payload = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const gcm_request &r = s->reqs[batch[i].id].r;
         PlanMsg &pm = msgs[i];
@@ -162,8 +161,6 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
         pm.out = (uint64_t)r.out_d;
         pm.len = r.len;
         pm.tag = (uint64_t)r.tag_d;
-        total_m += ghash_blocks(r.aad_len, r.len);
-        payload += r.len;
     }
     // As in gcm_batch_create: small tiles have more partials and items, and where
     // the memory does not hold them the plan with larger tiles is tried.
@@ -174,7 +171,7 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
     for (const bool small : {true, false}) {
         {
             std::lock_guard<std::mutex> g(ctx->mu);  // key table and autotune caches
-            sh = batch_shape(ctx, n, payload, total_m, small);
+            sh = batch_shape(ctx, msgs.data(), n, small);
             plan_batch(msgs.data(), n, slot_view(ctx), sh.waves, sh.log2B, &plan);
         }
         n_items = plan.items.size();

@@ -17,6 +17,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <numeric>
 #include <vector>
 
@@ -407,7 +408,7 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
     p->total_tiles = p->partial_slots = p->payload = 0;
     p->any_decrypt = p->any_combine = p->any_zerofill = false;
     p->rows = cap_log2B <= 6 && group_log2(waves) != 0;
-    uint64_t tile_base = 0;
+    uint64_t tile_base = 0, n_items = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const PlanMsg &j = msgs[i];
         const uint32_t log2B = batch_msg_log2B(ghash_blocks(j.aad_len, j.len), waves, cap_log2B);
@@ -422,12 +423,26 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
         p->total_tiles += p->descs[i].n_tiles;
         p->any_decrypt |= j.op == 1;
         p->payload += j.len;
+        n_items += p->descs[i].groups;
     }
     p->partial_slots = tile_base;
+    // by key slot, a slot's messages as they come: a counting sort, unless the
+    // table has many more slots than the batch has messages
     std::vector<uint32_t> order(n);
-    std::iota(order.begin(), order.end(), 0u);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t a, uint32_t c) { return msgs[a].key_slot < msgs[c].key_slot; });
+    if (slots.n_slots / 4 <= n) {
+        std::vector<uint32_t> at(slots.n_slots + 1, 0);
+        for (uint32_t i = 0; i < n; ++i)
+            ++at[msgs[i].key_slot + 1];
+        for (uint32_t k = 0; k < slots.n_slots; ++k)
+            at[k + 1] += at[k];
+        for (uint32_t i = 0; i < n; ++i)
+            order[at[msgs[i].key_slot]++] = i;
+    } else {
+        std::iota(order.begin(), order.end(), 0u);
+        std::stable_sort(order.begin(), order.end(),
+                         [&](uint32_t a, uint32_t c) { return msgs[a].key_slot < msgs[c].key_slot; });
+    }
+    p->items.reserve(n_items);
     for (uint32_t i : order)
         for (uint64_t t = 0; t < p->descs[i].n_tiles; t += waves)
             p->items.push_back(WorkItem{i, (uint32_t)t});
@@ -516,29 +531,52 @@ inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint
     const size_t n = items->size(), g = grid;
     if (n <= g || g < 2)
         return;
-    std::vector<std::pair<uint64_t, uint32_t>> by_cost(n);  // cost, index
+    // the items by cost: a counting sort over (tile size, key size, tiles)
+    constexpr uint32_t kTiles = 16 + 1, kClasses = (20 - 6 + 1) * 3 * kTiles;
+    std::vector<uint32_t> cls(n), count(kClasses, 0), by_cost(n);
+    for (size_t i = 0; i < n; ++i) {
+        const MsgDesc &d = descs[(*items)[i].msg];
+        cls[i] = ((d.log2B - 6) * 3 + (d.nr - 10) / 2) * kTiles + item_tiles(d, (*items)[i].first_tile, waves);
+        ++count[cls[i]];
+    }
+    std::vector<std::pair<uint64_t, uint32_t>> used;  // cost, class
+    std::vector<uint64_t> cost(kClasses, 0);
+    for (uint32_t c = 0; c < kClasses; ++c)
+        if (count[c]) {
+            cost[c] = item_cost(6 + c / (3 * kTiles), 10 + 2 * (c / kTiles % 3), c % kTiles);
+            used.push_back({cost[c], c});
+        }
+    std::sort(used.begin(), used.end(), std::greater<std::pair<uint64_t, uint32_t>>());
+    uint32_t sum = 0;
+    for (const auto &u : used) {
+        const uint32_t here = count[u.second];
+        count[u.second] = sum;
+        sum += here;
+    }
     for (size_t i = 0; i < n; ++i)
-        by_cost[i] = {item_cost(descs[(*items)[i].msg], (*items)[i].first_tile, waves), (uint32_t)i};
-    std::stable_sort(by_cost.begin(), by_cost.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        by_cost[count[cls[i]]++] = (uint32_t)i;
     std::vector<std::pair<uint64_t, uint32_t>> load(g);  // cost so far, workgroup
     for (size_t k = 0; k < g; ++k)
         load[k] = {0, (uint32_t)k};
-    std::vector<uint32_t> at(n);  // at[r * g + workgroup]: index of its item of round r
-    const size_t rounds = (n + g - 1) / g, rest = n - (rounds - 1) * g;
-    for (size_t r = 0; r < rounds; ++r) {
-        if (r)
+    std::vector<uint32_t> taker(n);  // of the k-th item by cost
+    bool moved = false;              // a round of items of equal cost leaves the order of the loads as it is
+    for (size_t at = 0; at < n; at += g) {
+        if (moved)
             std::sort(load.begin(), load.end());
-        for (size_t k = 0; k < g && r * g + k < n; ++k) {
-            const size_t column = r + 1 < rounds ? load[k].second : k;  // the last round is put in place below
-            at[r * g + column] = by_cost[r * g + k].second;
-            load[k].first += by_cost[r * g + k].first;
+        const size_t m = std::min(g, n - at);
+        for (size_t k = 0; k < m; ++k) {
+            taker[at + k] = load[k].second;
+            load[k].first += cost[cls[by_cost[at + k]]];
         }
+        moved = cost[cls[by_cost[at]]] != cost[cls[by_cost[at + m - 1]]];
     }
-    // the workgroups with an item in the last round are the first `rest` ones
+    // the workgroups with an item in the last round, the first of `load`, come first
+    std::vector<uint32_t> place(g);
+    for (size_t k = 0; k < g; ++k)
+        place[load[k].second] = (uint32_t)k;
     std::vector<WorkItem> out(n);
-    for (size_t r = 0; r < rounds; ++r)
-        for (size_t k = 0; k < (r + 1 < rounds ? g : rest); ++k)
-            out[r * g + k] = (*items)[at[r * g + (r + 1 < rounds ? load[k].second : k)]];
+    for (size_t k = 0; k < n; ++k)
+        out[k / g * g + place[taker[k]]] = (*items)[by_cost[k]];
     items->swap(out);
 }
 

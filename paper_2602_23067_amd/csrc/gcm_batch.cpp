@@ -66,6 +66,9 @@ static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t
     int rc = plan_jobs(ctx, jobs, n, base_d, base_bytes, forced, small, &sh, &plan);
     if (rc)
         return rc;
+    const uint32_t grid =
+        std::max<uint32_t>(1, std::min<uint32_t>((uint32_t)plan.items.size(), (uint32_t)ctx->cu_count * sh.gpc));
+    spread_items(plan.descs, sh.waves, grid, &plan.items);  // before anything is held that an exception would lose
     gcm_batch *b = new gcm_batch();
     b->ctx = ctx;
     b->n = n;
@@ -76,8 +79,7 @@ static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t
     b->any_zerofill = plan.any_zerofill;
     b->payload_bytes = plan.payload;
     b->n_items = (uint32_t)plan.items.size();
-    b->grid = std::max<uint32_t>(1, std::min<uint32_t>(b->n_items, (uint32_t)ctx->cu_count * sh.gpc));
-    spread_items(plan.descs, sh.waves, b->grid, &plan.items);
+    b->grid = grid;
 
     const uint64_t desc_bytes = (uint64_t)n * sizeof(MsgDesc);
     const uint64_t item_bytes = (uint64_t)plan.items.size() * sizeof(WorkItem);

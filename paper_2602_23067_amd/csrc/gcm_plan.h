@@ -521,11 +521,13 @@ inline uint32_t batch_cap_log2B(const PlanMsg *msgs, uint32_t n, const SlotView 
 }
 
 // The order in which `grid` workgroups take the work list, workgroup g items g,
-// g + grid, ...: the largest first, in every round the largest left to the
-// workgroup with the least so far.  Items of equal cost stay grouped by key
-// slot.  In message order the longest sum of a workgroup was a fifth above the
-// mean with 512 messages of 1 MiB (median, lognormal; 1204 us), and half as
-// much again as the mean with 1024 of 16 KiB (124 us).
+// g + grid, ...: handed out the largest first, in every round the largest left
+// to the workgroup with the least so far.  In message order the longest sum of a
+// workgroup was a fifth above the mean with 512 messages of 1 MiB (median,
+// lognormal; 1204 us), and half as much again as the mean with 1024 of 16 KiB
+// (124 us).  What a workgroup has been given it runs in the list's order, by key
+// slot and message, so that it stages each key's tables once, however few keys
+// the messages share.
 inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint32_t grid, std::vector<WorkItem> *items)
 {
     const size_t n = items->size(), g = grid;
@@ -558,25 +560,28 @@ inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint
     std::vector<std::pair<uint64_t, uint32_t>> load(g);  // cost so far, workgroup
     for (size_t k = 0; k < g; ++k)
         load[k] = {0, (uint32_t)k};
-    std::vector<uint32_t> taker(n);  // of the k-th item by cost
-    bool moved = false;              // a round of items of equal cost leaves the order of the loads as it is
+    std::vector<uint32_t> taker(n);
+    bool moved = false;  // a round of items of equal cost leaves the order of the loads as it is
     for (size_t at = 0; at < n; at += g) {
         if (moved)
             std::sort(load.begin(), load.end());
         const size_t m = std::min(g, n - at);
         for (size_t k = 0; k < m; ++k) {
-            taker[at + k] = load[k].second;
+            taker[by_cost[at + k]] = load[k].second;
             load[k].first += cost[cls[by_cost[at + k]]];
         }
         moved = cost[cls[by_cost[at]]] != cost[cls[by_cost[at + m - 1]]];
     }
     // the workgroups with an item in the last round, the first of `load`, come first
-    std::vector<uint32_t> place(g);
+    std::vector<uint32_t> next(g);
     for (size_t k = 0; k < g; ++k)
-        place[load[k].second] = (uint32_t)k;
+        next[load[k].second] = (uint32_t)k;
     std::vector<WorkItem> out(n);
-    for (size_t k = 0; k < n; ++k)
-        out[k / g * g + place[taker[k]]] = (*items)[by_cost[k]];
+    for (size_t i = 0; i < n; ++i) {
+        uint32_t &to = next[taker[i]];
+        out[to] = (*items)[i];
+        to += (uint32_t)g;
+    }
     items->swap(out);
 }
 

@@ -76,10 +76,45 @@ static void batch_cap()
     }
 }
 
+// Every workgroup of a batch comes to a key slot once, and to a message once.
+static void key_order()
+{
+    std::mt19937_64 r(23067);
+    for (int it = 0; it < 500; ++it) {
+        const uint32_t waves = (const uint32_t[]){8, 12, 16}[r() % 3], n = 1 + (uint32_t)(r() % 60), keys = 1 + (uint32_t)(r() % 6);
+        const std::vector<uint8_t> used(keys, 1);
+        std::vector<uint32_t> nr(keys);
+        for (auto &x : nr)
+            x = 10 + 2 * (uint32_t)(r() % 3);
+        SlotView sv;
+        sv.n_slots = keys, sv.used = used.data(), sv.nr = nr.data();
+        std::vector<PlanMsg> msgs(n);
+        for (auto &m : msgs) {
+            m.len = r() % 3000000;
+            m.key_slot = (uint32_t)(r() % keys);
+        }
+        BatchPlan p;
+        plan_batch(msgs.data(), n, sv, waves, 6 + (uint32_t)(r() % 6), &p);
+        const uint32_t grid = 1 + (uint32_t)(r() % 300);
+        spread_items(p.descs, waves, grid, &p.items);
+        for (size_t g = 0; g < grid; ++g) {
+            std::vector<uint8_t> key_seen(keys, 0), msg_seen(n, 0);
+            for (size_t k = g; k < p.items.size(); k += grid) {
+                const uint32_t i = p.items[k].msg, prev = k > g ? p.items[k - grid].msg : n;
+                if (k == g || msgs[i].key_slot != msgs[prev].key_slot)
+                    CHECK(!key_seen[msgs[i].key_slot]++);
+                if (i != prev)
+                    CHECK(!msg_seen[i]++);
+            }
+        }
+    }
+}
+
 int main()
 {
     flag_in_tag();
     batch_cap();
+    key_order();
     std::printf("plan rules harness: OK\n");
     return 0;
 }

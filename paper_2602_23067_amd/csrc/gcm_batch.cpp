@@ -28,6 +28,7 @@ struct gcm_batch {
     Shape shape;
     uint32_t grid = 1;
     bool rows = false, any_combine = false, any_zerofill = false;
+    uint64_t longest_zerofill = 0;
     uint64_t total_tiles = 0;
     uint64_t payload_bytes = 0;
     MsgDesc *d_descs = nullptr;
@@ -77,6 +78,7 @@ static int create_planned(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t
     b->rows = plan.rows;
     b->any_combine = plan.any_combine;
     b->any_zerofill = plan.any_zerofill;
+    b->longest_zerofill = plan.longest_zerofill;
     b->payload_bytes = plan.payload;
     b->n_items = (uint32_t)plan.items.size();
     b->grid = grid;
@@ -164,7 +166,7 @@ hipError_t gcm::batch_enqueue(gcm_batch *b, hipStream_t s)
     if (e == hipSuccess && b->any_combine)
         e = launch_verdict(b->d_descs, b->n, nullptr, partials, counters, s);
     if (e == hipSuccess && b->any_zerofill)
-        e = launch_zerofill(b->d_descs, counters, (uint32_t)std::max(1, ctx->cu_count * 4), s);
+        e = launch_zerofill(b->d_descs, counters, (uint32_t)ctx->cu_count * 4, b->longest_zerofill, s);
     return e;
 }
 

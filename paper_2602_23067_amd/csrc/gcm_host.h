@@ -207,8 +207,9 @@ hipError_t launch_fold(const void *vals, uint32_t k, const void *ekj0, uint8_t *
                        uint32_t tag_len, uint64_t slot, const uint32_t lenblk[4], hipStream_t s);
 // device address of the fixed scratch array on `device` (looked up once per device)
 hipError_t scratch_address(int device, void **out);
-// clears the outputs of a batch's rejected messages
-hipError_t launch_zerofill(const MsgDesc *descs, const uint32_t *counters, uint32_t grid, hipStream_t s);
+// clears the outputs of a batch's rejected messages, none of them longer than `longest`
+hipError_t launch_zerofill(const MsgDesc *descs, const uint32_t *counters, uint32_t grid, uint64_t longest,
+                           hipStream_t s);
 // AES-GCM-SIV: message keys into the slot at out_slot (and, with tag_in, the
 // counter block from the received tag at ctr_out); the tile passes (0 POLYVAL
 // only, 1 counter mode only, 2 counter mode + POLYVAL of the output); the tag

@@ -396,6 +396,7 @@ struct BatchPlan {
     bool any_decrypt = false;
     // messages that the tile kernel does not finish by itself, and decrypts among them
     bool any_combine = false, any_zerofill = false;
+    uint64_t longest_zerofill = 0;  // payload bytes of the longest of the latter
     bool rows = false;  // all tiles are single rows, run by the row kernel
     uint64_t workspace_bytes() const { return workspace_counter_bytes(descs.size()) + 16 * partial_slots; }
 };
@@ -407,6 +408,7 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
     p->items.clear();
     p->total_tiles = p->partial_slots = p->payload = 0;
     p->any_decrypt = p->any_combine = p->any_zerofill = false;
+    p->longest_zerofill = 0;
     p->rows = cap_log2B <= 6 && group_log2(waves) != 0;
     uint64_t tile_base = 0, n_items = 0;
     for (uint32_t i = 0; i < n; ++i) {
@@ -418,7 +420,10 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
         if (p->rows)
             p->descs[i].flags |= kRows;
         p->any_combine |= !(p->descs[i].flags & kFinish);
-        p->any_zerofill |= !(p->descs[i].flags & kFinish) && j.op == 1;
+        if (!(p->descs[i].flags & kFinish) && j.op == 1) {
+            p->any_zerofill = true;
+            p->longest_zerofill = std::max(p->longest_zerofill, j.len);
+        }
         tile_base += p->descs[i].n_tiles + 2;  // partials, then the E_K(J0) and J0 slots
         p->total_tiles += p->descs[i].n_tiles;
         p->any_decrypt |= j.op == 1;

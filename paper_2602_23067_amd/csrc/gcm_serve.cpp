@@ -215,7 +215,7 @@ static int launch_batch(gcm_serve *s, Slot &sl, const std::vector<PolicyReq> &ba
     if (e == hipSuccess && plan.any_combine)
         e = launch_verdict(d_desc, n, nullptr, partials, counters, sl.stream);
     if (e == hipSuccess && plan.any_zerofill)
-        e = launch_zerofill(d_desc, counters, (uint32_t)std::max(1, ctx->cu_count * 2), sl.stream);
+        e = launch_zerofill(d_desc, counters, (uint32_t)ctx->cu_count * 2, plan.longest_zerofill, sl.stream);
     if (e == hipSuccess && plan.any_decrypt)
         e = hipMemcpyAsync(h_flags, d_flags, 4ull * n, hipMemcpyDeviceToHost, sl.stream);
     if (e == hipSuccess)

@@ -110,11 +110,28 @@ static void key_order()
     }
 }
 
+// One wave of the tile kernel clears what it rejects: it finishes a decrypt by
+// itself only up to 1 MiB, and any encrypt of one group.
+static void finish_bound()
+{
+    for (uint32_t waves : {8u, 12u, 16u})
+        for (uint32_t log2B : {6u, 12u, 16u, 20u})
+            for (uint64_t len : {0ull, 1000ull, 1ull << 20, (1ull << 20) + 1, 10ull << 20, 200ull << 20})
+                for (uint32_t op : {0u, 1u}) {
+                    MsgDesc d;
+                    fill_desc(&d, op, iv, 0, 0, 0, 0, len, 0, 0, 0, 14, log2B, waves, 0);
+                    set_groups(&d, waves, true);
+                    const bool one = d.n_tiles <= (waves == 16 ? 16u : waves == 8 ? 8u : 4u);
+                    CHECK(((d.flags & kFinish) != 0) == (one && (op == 0 || len <= 1ull << 20)));
+                }
+}
+
 int main()
 {
     flag_in_tag();
     batch_cap();
     key_order();
+    finish_bound();
     std::printf("plan rules harness: OK\n");
     return 0;
 }

@@ -192,9 +192,9 @@ inline uint32_t batch_msg_log2B(uint64_t m, uint32_t waves, uint32_t cap)
 // 1400 cycles, bound by the vector units, where the tile kernel takes 523; but an
 // item of the tile kernel costs about 15000 cycles besides, most of them for the
 // 80 KiB of key tables, so that messages of less than some 17 rows are better off
-// with rows (1024 messages, median 4 KiB with 2 KiB of AAD: 50 us, 63 with tiles;
-// median 16 KiB: 115 and 93), and so is what gives every wave slot of the chip at
-// most a row (64 messages, median 16 KiB: 22 us, 34 with tiles).
+// with rows (1024 messages, median 8 KiB with 1 KiB of AAD: 55 us, 63 with tiles;
+// median 16 KiB: 89 and 78), and so is what gives every wave slot of the chip at
+// most a row (64 messages, median 16 KiB: 15 us, 27 with tiles).
 inline bool batch_rows(uint64_t n, uint64_t m, uint64_t cus) { return m <= 1024 * n || m <= 64 * 16 * cus; }
 
 // Workspace: a counter and reject list (4 + 4 * n_msgs bytes, rounded up to
@@ -462,10 +462,14 @@ inline void plan_batch(const PlanMsg *msgs, uint32_t n, const SlotView &slots, u
 // matter for tile sizes and for spreading items over workgroups: 523 a row of 64
 // blocks with AES-256 and proportionally fewer with smaller keys (the compute
 // unit is busy), but not less than its longest wave takes alone, and some 12000
-// for getting started and summing up.
+// for getting started and summing up.  In the row kernel every wave goes through
+// nearly all of it, with a row or without: 6.9 us an item of one row, 8.4 of
+// eight with AES-128, 7.7 and 9.4 with AES-256.
 constexpr uint64_t kItemStart = 12000, kRowCost = 38;  // kRowCost: a row and AES round
-inline uint64_t item_cost(uint32_t log2B, uint32_t nr, uint64_t tiles)
+inline uint64_t item_cost(uint32_t log2B, uint32_t nr, uint64_t tiles, bool rows)
 {
+    if (rows)
+        return 9700 + 425 * nr + 460 * tiles;
     return kItemStart + (1ull << (log2B - 6)) * nr * std::max<uint64_t>(tiles * kRowCost, 320);
 }
 
@@ -479,7 +483,7 @@ inline uint32_t item_tiles(const MsgDesc &d, uint32_t first_tile, uint32_t waves
 
 inline uint64_t item_cost(const MsgDesc &d, uint32_t first_tile, uint32_t waves)
 {
-    return item_cost(d.log2B, d.nr, item_tiles(d, first_tile, waves));
+    return item_cost(d.log2B, d.nr, item_tiles(d, first_tile, waves), d.flags & kRows);
 }
 
 // Cap on the tile sizes of a batch run by the tile kernel on `groups` resident
@@ -517,7 +521,7 @@ inline uint32_t batch_cap_log2B(const PlanMsg *msgs, uint32_t n, const SlotView 
             if (most[q]) {
                 const uint32_t l = batch_msg_log2B(most[q], waves, cap);
                 const uint64_t T = (most[q] + (1ull << l) - 1) >> l;
-                big = std::max(big, item_cost(l, 10 + 2 * q, std::min<uint64_t>(T, waves)));
+                big = std::max(big, item_cost(l, 10 + 2 * q, std::min<uint64_t>(T, waves), false));
             }
         const uint64_t it = items[cap - 8], g = std::max<uint64_t>(1, std::min(it, groups));
         const uint64_t starts = kItemStart * it - kItemStart * 3 / 4 * more[cap - 8];
@@ -543,6 +547,7 @@ inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint
     const size_t n = items->size(), g = grid;
     if (n <= g || g < 2)
         return;
+    const bool rows = descs[(*items)[0].msg].flags & kRows;  // as all of them
     // the items by cost: a counting sort over (tile size, key size, tiles)
     constexpr uint32_t kTiles = 16 + 1, kClasses = (20 - 6 + 1) * 3 * kTiles;
     std::vector<uint32_t> cls(n), count(kClasses, 0), by_cost(n);
@@ -555,7 +560,7 @@ inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint
     std::vector<uint64_t> cost(kClasses, 0);
     for (uint32_t c = 0; c < kClasses; ++c)
         if (count[c]) {
-            cost[c] = item_cost(6 + c / (3 * kTiles), 10 + 2 * (c / kTiles % 3), c % kTiles);
+            cost[c] = item_cost(6 + c / (3 * kTiles), 10 + 2 * (c / kTiles % 3), c % kTiles, rows);
             used.push_back({cost[c], c});
         }
     std::sort(used.begin(), used.end(), std::greater<std::pair<uint64_t, uint32_t>>());

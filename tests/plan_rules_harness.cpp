@@ -126,12 +126,37 @@ static void finish_bound()
                 }
 }
 
+// Items of the row kernel: more rows cost more, and so does a larger key, but a
+// full item less than half as much again as one row (8.4 us to 6.9 measured).
+static void row_items()
+{
+    for (uint32_t waves : {8u, 12u, 16u})
+        for (uint32_t nr : {10u, 12u, 14u}) {
+            uint64_t before = 0, one = 0;
+            for (uint32_t rows = 1; rows <= (waves == 12 ? 4 : waves); ++rows) {
+                MsgDesc d;
+                fill_desc(&d, 0, iv, 0, 0, 0, 0, 1024 * rows - 16, 0, 0, 0, nr, 6, waves, 0);
+                set_groups(&d, waves, true);
+                d.flags |= kRows;
+                const uint64_t c = item_cost(d, 0, waves);
+                CHECK(c > before);
+                one = rows == 1 ? c : one;
+                CHECK(2 * c < 3 * one);
+                before = c;
+                MsgDesc e = d;
+                e.nr = nr + 2;
+                CHECK(item_cost(e, 0, waves) > c);
+            }
+        }
+}
+
 int main()
 {
     flag_in_tag();
     batch_cap();
     key_order();
     finish_bound();
+    row_items();
     std::printf("plan rules harness: OK\n");
     return 0;
 }

@@ -403,9 +403,10 @@ typedef struct gcm_batch gcm_batch;
 int gcm_batch_create(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
                      gcm_batch **out);
 
-/* Enqueue one pass over the batch on `stream`: the fused tile kernel over all
- * messages in one persistent launch, the per-message combine (tags / accept
- * flags written to base_d) and the zero-fill of rejected outputs.  Allocates
+/* Enqueue one pass over the batch on `stream`: the fused kernel over all
+ * messages in one persistent launch, for messages of more than one workgroup
+ * the verdict (tags / accept flags written to base_d) and the zero-fill of
+ * rejected outputs.  Allocates
  * nothing; results are identical to running each message alone. */
 int gcm_batch_launch(gcm_batch *b, void *stream);
 
@@ -513,23 +514,24 @@ int gcm_set_launch(gcm_ctx *ctx, uint32_t log2_tile_blocks, uint32_t waves_per_g
  * Results never depend on it. */
 int gcm_set_combine(gcm_ctx *ctx, uint32_t fanin);
 
-/* Result of an autotune search (also the answer of gcm_launch_plan). */
+/* Result of an autotune search: its fastest shape (also the answer of
+ * gcm_launch_plan). */
 typedef struct gcm_tune_result {
     uint32_t log2_tile_blocks; /* chosen blocks per wave tile (log2); for a batch, the cap on its tiles */
     uint32_t waves_per_group;  /* chosen workgroup size in waves */
-    uint32_t candidates;       /* shapes timed */
+    uint32_t candidates;       /* shapes timed, for a batch once in each of four turns */
     float best_ms;             /* mean time of the chosen shape (one encrypt pass / one batch pass) */
     double gbs;                /* payload GB/s of the chosen shape */
     uint32_t groups_per_cu;    /* chosen resident workgroups per compute unit */
-    uint32_t combine_fanin;    /* chosen fan-in of the reduction tree */
+    uint32_t combine_fanin;    /* chosen fan-in of the reduction tree (streams and the host pipeline) */
 } gcm_tune_result;
 
 /* Exhaustive launch-shape search for messages of about `len` bytes under
  * `key_len`-byte keys (the paper's per-GPU parameter sweep): every candidate
- * tile size (blocks per lane), workgroup size, groups per CU (1 up to the
- * occupancy limit) and reduction fan-in is timed `reps` times with HIP events
- * on a scratch message, all candidates must produce the identical tag
- * (GCM_E_INTERNAL otherwise), and the fastest shape is cached for that (key
+ * tile size (2^8..2^16 blocks), workgroup size and groups per CU (1 up to the
+ * occupancy limit) is timed `reps` times with HIP events on a scratch message,
+ * then the reduction tree at every fan-in.  All must produce the identical tag
+ * (GCM_E_INTERNAL otherwise).  The fastest shape is cached for that (key
  * size, floor(log2 len)) and used by every later single-message call
  * (one-shot, asynchronous, counter mode, host pipeline, streamed segments;
  * gcm_workspace_size sizes for it) without an explicit gcm_set_launch.
@@ -538,14 +540,13 @@ int gcm_autotune(gcm_ctx *ctx, uint32_t key_len, uint64_t len, uint32_t reps, gc
 
 /* The same search for a batch, run on the caller's jobs (gcm_batch_create's
  * arguments): workgroup size x groups per CU x cap on the messages' tile
- * sizes (2^8..2^12 blocks) x fan-in, each point a full pass over the batch
- * timed `reps` times, every point's tags and accept flags required equal to
- * the first point's (GCM_E_INTERNAL otherwise).  The winner is cached for
- * (floor(log2 n), floor(log2 payload bytes)) and used by later
- * gcm_batch_create calls and serving batches of that shape.  Every pass
- * rewrites the jobs' outputs, tags and flags, so jobs may not run in place
- * (GCM_E_ARG) and one job's output may not overlap another's input.
- * Blocks until done. */
+ * sizes (2^8..2^12 blocks), each point a full pass over the batch timed `reps`
+ * times in each of four turns, every point's tags and accept flags required
+ * equal to the first point's (GCM_E_INTERNAL otherwise).  The winner is cached
+ * for (floor(log2 n), floor(log2 payload bytes)) and used by later
+ * gcm_batch_create calls and serving batches of that shape.  Every pass rewrites
+ * the jobs' outputs, tags and flags, so jobs may not run in place (GCM_E_ARG)
+ * and one job's output may not overlap another's input.  Blocks until done. */
 int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
                        uint32_t reps, gcm_tune_result *out, void *stream);
 

@@ -3,22 +3,24 @@
 // fastest), with a bit-equality check across every candidate.
 //
 // Single messages: for one (key size, message size) point the search times
-// every shape in {log2 tile blocks} x {waves per workgroup} x {groups per
-// CU} x {reduction-tree fan-in} on a scratch message with HIP events,
-// requires all of them to produce the same tag (the counter map and GHASH
-// exponents derive from block indices only), and records the fastest in the
-// context's cache, keyed by (key bytes, floor(log2 len)).
+// every shape of the tile kernel in {log2 tile blocks} x {waves per workgroup} x
+// {groups per CU} on a scratch message with HIP events, requires all of them to
+// produce the same tag (the counter map and GHASH exponents derive from block
+// indices only), and records the fastest in the context's cache, keyed by (key
+// bytes, floor(log2 len)), with the fan-in at which the reduction tree that
+// streams and the host pipeline end with was fastest for that shape.
 //
 // Batches: the same search over {waves} x {groups per CU} x {cap on the
-// messages' tile sizes} x {fan-in} on the caller's own batch, every point's
-// tags and accept flags compared with the first point's, recorded under
-// (floor(log2 messages), floor(log2 payload bytes)).
+// messages' tile sizes} on the caller's own batch, every point's tags and accept
+// flags compared with the first point's, recorded under (floor(log2 messages),
+// floor(log2 payload bytes)).
 //
 // Every planner (one-shot, asynchronous, batches, the serving loop, host
 // pipeline, streamed segments) consults these caches when no explicit shape
 // is set with gcm_set_launch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -35,7 +37,7 @@ const uint32_t kWaveOpts[3] = {8, 12, 16};
 const uint32_t kFaninOpts[4] = {2, 4, 8, 16};
 
 // Candidate groups per CU for a workgroup size: 1 .. what the occupancy
-// calculator allows (the tile kernel's 144 KiB of LDS holds it to one on
+// calculator allows (the tile kernel's 149 KiB of LDS hold it to one on
 // gfx950, so this dimension has a single point there).
 std::vector<uint32_t> gpc_options(uint32_t waves)
 {
@@ -46,12 +48,36 @@ std::vector<uint32_t> gpc_options(uint32_t waves)
     return v;
 }
 
+constexpr uint32_t kTurns = 4;  // what is compared is timed in turn this often
+
 struct Timer {
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t init()
     {
         hipError_t e = hipEventCreate(&a);
         return e == hipSuccess ? hipEventCreate(&b) : e;
+    }
+    // f's work on `s`, the mean of `reps` passes in ms, added to *ms
+    template <typename F>
+    hipError_t add(hipStream_t s, uint32_t reps, float *ms, F f)
+    {
+        hipError_t e = hipSuccess;
+        float total = 0.f;
+        for (uint32_t r = 0; r < reps && e == hipSuccess; ++r) {
+            e = hipEventRecord(a, s);
+            if (e == hipSuccess)
+                e = f();
+            if (e == hipSuccess)
+                e = hipEventRecord(b, s);
+            if (e == hipSuccess)
+                e = hipEventSynchronize(b);
+            float one = 0.f;
+            if (e == hipSuccess)
+                e = hipEventElapsedTime(&one, a, b);
+            total += one;
+        }
+        *ms += total / (float)reps;
+        return e;
     }
     ~Timer()
     {
@@ -111,61 +137,84 @@ extern "C" int gcm_autotune(gcm_ctx *ctx, uint32_t key_len, uint64_t len, uint32
             e = tm.init();
 
         float best_ms = 1e30f;
-        Shape best;
+        TuneEntry best;
         uint32_t tried = 0;
         bool all_equal = true;
         uint8_t ref_tag[16], cur_tag[16];
         bool have_ref = false;
         const bool save_prof = ctx->prof;
         ctx->prof = false;
-        for (uint32_t l = 8; l <= 16 && e == hipSuccess && rc == GCM_OK; ++l) {
+        auto desc = [&](const Shape &sh) {
+            MsgDesc d;
+            fill_desc(&d, 0, iv, 0, 0, (uint64_t)in, (uint64_t)outp, len, (uint64_t)tag, 0,
+                      (uint64_t)(ctx->d_slots + kSlotBytes * slot), key_len / 4 + 6, sh.log2B, sh.waves, 0);
+            return d;
+        };
+        auto check = [&]() {  // the tag of the last pass
+            const hipError_t r = hipMemcpy(cur_tag, tag, 16, hipMemcpyDeviceToHost);
+            if (r == hipSuccess && !have_ref) {
+                std::memcpy(ref_tag, cur_tag, 16);
+                have_ref = true;
+            } else if (r == hipSuccess && std::memcmp(ref_tag, cur_tag, 16) != 0) {
+                all_equal = false;
+            }
+            return r;
+        };
+        auto pass = [&](const Shape &sh) {
+            const int r = launch_single(ctx, desc(sh), sh, ws, s);
+            rc = rc ? rc : r;
+            return r ? hipErrorUnknown : hipSuccess;
+        };
+        auto time_shape = [&](const Shape &sh, float *ms) {
+            hipError_t r = pass(sh);  // warm-up
+            if (r == hipSuccess)
+                r = tm.add(s, reps, ms, [&] { return pass(sh); });
+            return r == hipSuccess ? check() : r;
+        };
+        for (uint32_t l = 8; l <= 16 && e == hipSuccess; ++l) {
             if ((1ull << l) > 4 * m && l > 8)
                 break;  // tiles larger than the whole message add nothing
             for (uint32_t w : kWaveOpts)
-                for (uint32_t gpc : gpc_options(w))
-                    for (uint32_t f : kFaninOpts) {
-                        if (e != hipSuccess || rc != GCM_OK)
-                            break;
-                        Shape sh;
-                        sh.log2B = l;
-                        sh.waves = w;
-                        sh.gpc = gpc;
-                        sh.fanin = f;
-                        MsgDesc d;
-                        fill_desc(&d, 0, iv, 0, 0, (uint64_t)in, (uint64_t)outp, len, (uint64_t)tag, 0,
-                                  (uint64_t)(ctx->d_slots + kSlotBytes * slot), key_len / 4 + 6, l, w, 0);
-                        rc = launch_single(ctx, d, sh, ws, s);  // warm-up
-                        float total = 0.f;
-                        for (uint32_t r = 0; r < reps && rc == GCM_OK && e == hipSuccess; ++r) {
-                            e = hipEventRecord(tm.a, s);
-                            if (e == hipSuccess)
-                                rc = launch_single(ctx, d, sh, ws, s);
-                            if (e == hipSuccess && rc == GCM_OK)
-                                e = hipEventRecord(tm.b, s);
-                            if (e == hipSuccess)
-                                e = hipEventSynchronize(tm.b);
-                            float ms = 0.f;
-                            if (e == hipSuccess)
-                                e = hipEventElapsedTime(&ms, tm.a, tm.b);
-                            total += ms;
-                        }
-                        if (e == hipSuccess && rc == GCM_OK)
-                            e = hipMemcpy(cur_tag, tag, 16, hipMemcpyDeviceToHost);
-                        if (e != hipSuccess || rc != GCM_OK)
-                            break;
-                        if (!have_ref) {
-                            std::memcpy(ref_tag, cur_tag, 16);
-                            have_ref = true;
-                        } else if (std::memcmp(ref_tag, cur_tag, 16) != 0) {
-                            all_equal = false;
-                        }
-                        ++tried;
-                        const float ms = total / (float)reps;
-                        if (ms < best_ms) {
-                            best_ms = ms;
-                            best = sh;
-                        }
+                for (uint32_t gpc : gpc_options(w)) {
+                    if (e != hipSuccess)
+                        break;
+                    Shape sh;
+                    sh.log2B = l;
+                    sh.waves = w;
+                    sh.gpc = gpc;
+                    float ms = 0.f;
+                    e = time_shape(sh, &ms);
+                    ++tried;
+                    if (e == hipSuccess && ms < best_ms) {
+                        best_ms = ms;
+                        best = sh;
                     }
+                }
+        }
+        // The tree over single partials, which whole-message launches do without
+        // but streams and the host pipeline end with, at every fan-in.
+        if (e == hipSuccess) {
+            const MsgDesc d = desc(best);
+            rc = launch_tile_range(ctx, d, best, ws, s);
+            e = rc ? hipErrorUnknown : hipSuccess;
+            float least = 1e30f, sum[4] = {0.f, 0.f, 0.f, 0.f};
+            for (uint32_t k = 0; k <= kTurns && e == hipSuccess; ++k)
+                for (uint32_t f = 0; f < 4 && e == hipSuccess; ++f) {
+                    float ms = 0.f;
+                    e = tm.add(s, reps, &ms, [&] {
+                        return launch_combine(nullptr, 1, &d, ws + workspace_counter_bytes(1),
+                                              reinterpret_cast<uint32_t *>(ws), kFaninOpts[f], s);
+                    });
+                    if (k)
+                        sum[f] += ms;  // the first round is the warm-up
+                    else if (e == hipSuccess)
+                        e = check();
+                }
+            for (uint32_t f = 0; f < 4; ++f)
+                if (sum[f] < least) {
+                    least = sum[f];
+                    best.fanin = kFaninOpts[f];
+                }
         }
         ctx->prof = save_prof;
         (void)hipStreamSynchronize(s);
@@ -233,59 +282,50 @@ extern "C" int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n,
         e = tm.init();
         if (e != hipSuccess)
             return fail_hip(e, "hipEventCreate");
-        float best_ms = 1e30f;
-        Shape best;
         uint32_t tried = 0;
         bool have_ref = false, all_equal = true;
         int rc = GCM_OK;
         const bool save_prof = ctx->prof;
         ctx->prof = false;
+        auto time_shape = [&](const Shape &sh, float *ms) {
+            gcm_batch *b = nullptr;
+            rc = batch_create_locked(ctx, jobs, n, base_d, base_bytes, &sh, &b);
+            if (rc)
+                return hipErrorUnknown;
+            hipError_t r = batch_enqueue(b, s);  // warm-up
+            if (r == hipSuccess)
+                r = tm.add(s, reps, ms, [&] { return batch_enqueue(b, s); });
+            if (r == hipSuccess)
+                r = fetch(have_ref ? cur : ref);
+            batch_free_locked(b);
+            if (r != hipSuccess)
+                return r;
+            if (!have_ref)
+                have_ref = true;
+            else if (cur != ref)
+                all_equal = false;
+            ++tried;
+            return r;
+        };
+        // every shape in every turn, so that a shape is not
+        // chosen for a moment in which the clock was high
+        std::vector<TuneEntry> shapes;
         for (uint32_t w : kWaveOpts)
             for (uint32_t gpc : gpc_options(w))
-                for (uint32_t cap = 8; cap <= 12; ++cap)
-                    for (uint32_t f : kFaninOpts) {
-                        if (rc || e != hipSuccess)
-                            break;
-                        Shape sh;
-                        sh.log2B = cap;
-                        sh.waves = w;
-                        sh.gpc = gpc;
-                        sh.fanin = f;
-                        gcm_batch *b = nullptr;
-                        rc = batch_create_locked(ctx, jobs, n, base_d, base_bytes, &sh, &b);
-                        if (rc)
-                            break;
-                        e = batch_enqueue(b, s);  // warm-up
-                        float total = 0.f;
-                        for (uint32_t r = 0; r < reps && e == hipSuccess; ++r) {
-                            e = hipEventRecord(tm.a, s);
-                            if (e == hipSuccess)
-                                e = batch_enqueue(b, s);
-                            if (e == hipSuccess)
-                                e = hipEventRecord(tm.b, s);
-                            if (e == hipSuccess)
-                                e = hipEventSynchronize(tm.b);
-                            float ms = 0.f;
-                            if (e == hipSuccess)
-                                e = hipEventElapsedTime(&ms, tm.a, tm.b);
-                            total += ms;
-                        }
-                        if (e == hipSuccess)
-                            e = fetch(have_ref ? cur : ref);
-                        batch_free_locked(b);
-                        if (e != hipSuccess)
-                            break;
-                        if (!have_ref)
-                            have_ref = true;
-                        else if (cur != ref)
-                            all_equal = false;
-                        ++tried;
-                        const float ms = total / (float)reps;
-                        if (ms < best_ms) {
-                            best_ms = ms;
-                            best = sh;
-                        }
-                    }
+                for (uint32_t cap = 8; cap <= 12; ++cap) {
+                    TuneEntry t;
+                    t.log2B = cap;
+                    t.waves = w;
+                    t.gpc = gpc;
+                    shapes.push_back(t);
+                }
+        std::vector<float> sum(shapes.size(), 0.f);
+        for (uint32_t k = 0; k < kTurns && e == hipSuccess; ++k)
+            for (size_t q = 0; q < shapes.size() && e == hipSuccess; ++q)
+                e = time_shape(shapes[q], &sum[q]);
+        const size_t at = std::min_element(sum.begin(), sum.end()) - sum.begin();
+        TuneEntry best = shapes[at];
+        const float best_ms = sum[at] / (float)kTurns;
         ctx->prof = save_prof;
         if (rc)
             return rc;

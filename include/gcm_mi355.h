@@ -530,23 +530,26 @@ typedef struct gcm_tune_result {
  * `key_len`-byte keys (the paper's per-GPU parameter sweep): every candidate
  * tile size (2^8..2^16 blocks), workgroup size and groups per CU (1 up to the
  * occupancy limit) is timed `reps` times with HIP events on a scratch message,
- * then the reduction tree at every fan-in.  All must produce the identical tag
+ * then the fastest in turn with the shape that the planner takes by itself, and
+ * the reduction tree at every fan-in.  All must produce the identical tag
  * (GCM_E_INTERNAL otherwise).  The fastest shape is cached for that (key
  * size, floor(log2 len)) and used by every later single-message call
  * (one-shot, asynchronous, counter mode, host pipeline, streamed segments;
- * gcm_workspace_size sizes for it) without an explicit gcm_set_launch.
+ * gcm_workspace_size sizes for it) without an explicit gcm_set_launch, unless
+ * the planner's own was as fast, which is then kept (gcm_launch_plan tells).
  * Allocates scratch for the duration of the call; blocks until done. */
 int gcm_autotune(gcm_ctx *ctx, uint32_t key_len, uint64_t len, uint32_t reps, gcm_tune_result *out, void *stream);
 
 /* The same search for a batch, run on the caller's jobs (gcm_batch_create's
  * arguments): workgroup size x groups per CU x cap on the messages' tile
- * sizes (2^8..2^12 blocks), each point a full pass over the batch timed `reps`
- * times in each of four turns, every point's tags and accept flags required
- * equal to the first point's (GCM_E_INTERNAL otherwise).  The winner is cached
- * for (floor(log2 n), floor(log2 payload bytes)) and used by later
- * gcm_batch_create calls and serving batches of that shape.  Every pass rewrites
- * the jobs' outputs, tags and flags, so jobs may not run in place (GCM_E_ARG)
- * and one job's output may not overlap another's input.  Blocks until done. */
+ * sizes (2^8..2^12 blocks) and the planner's own shape, each point a full pass
+ * over the batch timed `reps` times in each of four turns, every point's tags
+ * and accept flags required equal to the first point's (GCM_E_INTERNAL
+ * otherwise).  The winner is cached for (floor(log2 n), floor(log2 payload
+ * bytes)) and used by later gcm_batch_create calls and serving batches of that
+ * shape, unless the planner's own was as fast.  Every pass rewrites the jobs'
+ * outputs, tags and flags, so jobs may not run in place (GCM_E_ARG) and one
+ * job's output may not overlap another's input.  Blocks until done. */
 int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n, uint8_t *base_d, uint64_t base_bytes,
                        uint32_t reps, gcm_tune_result *out, void *stream);
 

@@ -389,16 +389,38 @@ uint64_t gcm::resident_bound(const gcm_ctx *ctx)
     return r;
 }
 
+// Cap on a batch's tile sizes for the waves and groups of `sh`: the rule; where
+// memory is short, the single-launch tile size of the whole batch's m blocks,
+// within 2^8..2^12
+static uint32_t batch_tile_cap(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, uint64_t m, const Shape &sh, bool small)
+{
+    const uint64_t groups = (uint64_t)ctx->cu_count * sh.gpc;
+    if (small)
+        return batch_cap_log2B(msgs, n, slot_view(ctx), sh.waves, groups);
+    return std::min<uint32_t>(12, std::max<uint32_t>(8, heuristic_log2B(std::max<uint64_t>(1, m), groups * sh.waves)));
+}
+
+Shape gcm::heuristic_shape(const gcm_ctx *ctx, uint64_t m)
+{
+    Shape sh;
+    sh.waves = heuristic_waves(m, (uint64_t)ctx->cu_count, groups_per_cu);
+    sh.gpc = groups_per_cu(sh.waves);
+    sh.log2B = heuristic_log2B(m, (uint64_t)ctx->cu_count * sh.gpc * sh.waves);
+    return sh;
+}
+
 Shape gcm::message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, uint64_t aad_len)
 {
     Shape sh;
     TuneEntry t;
     bool tuned = false;
+    uint32_t fanin = 2;
     if (!ctx->cfg_log2B && !ctx->cfg_waves) {
         auto it = ctx->tuned.find((uint64_t)key_bytes << 32 | size_bucket(len));
         if (it != ctx->tuned.end()) {
             t = it->second;
-            tuned = true;
+            tuned = t.faster;
+            fanin = t.fanin;  // timed with the shape that is used
         }
     }
     const uint64_t m = ghash_blocks(aad_len, len);
@@ -409,50 +431,54 @@ Shape gcm::message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, u
     else if (ctx->cfg_log2B || ctx->cfg_gpc)
         sh.waves = 16;
     else
-        sh.waves = heuristic_waves(m, (uint64_t)ctx->cu_count, groups_per_cu);
-    sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : (tuned && t.gpc) ? t.gpc : groups_per_cu(sh.waves);
+        sh = heuristic_shape(ctx, m);
+    sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : tuned ? t.gpc : groups_per_cu(sh.waves);
     sh.log2B = ctx->cfg_log2B ? ctx->cfg_log2B
                : tuned        ? t.log2B
                               : heuristic_log2B(m, (uint64_t)ctx->cu_count * sh.gpc * sh.waves);
-    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : (tuned && t.fanin) ? t.fanin : 2;
+    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : fanin;
     return sh;
 }
 
-Shape gcm::batch_shape(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small)
+Shape gcm::batch_rule(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small)
 {
-    uint64_t m = 0, payload = 0;
-    for (uint32_t i = 0; i < n; ++i) {
+    uint64_t m = 0;
+    for (uint32_t i = 0; i < n; ++i)
         m += ghash_blocks(msgs[i].aad_len, msgs[i].len);
-        payload += msgs[i].len;
-    }
     Shape sh;
-    TuneEntry t;
-    bool tuned = false;
-    if (!ctx->cfg_log2B && !ctx->cfg_waves) {
-        auto it = ctx->tuned_batch.find((uint64_t)size_bucket(n) << 32 | size_bucket(payload));
-        if (it != ctx->tuned_batch.end()) {
-            t = it->second;
-            tuned = true;
-        }
-    }
-    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : (tuned && t.fanin) ? t.fanin : 2;
-    if (small && !tuned && !ctx->cfg_log2B && !ctx->cfg_waves && !ctx->cfg_gpc && batch_rows(n, m, (uint64_t)ctx->cu_count)) {
+    if (small && batch_rows(n, m, (uint64_t)ctx->cu_count)) {
         sh.log2B = 6;
         sh.waves = 8;
         sh.gpc = 2;
         return sh;
     }
-    sh.waves = ctx->cfg_waves ? ctx->cfg_waves : tuned ? t.waves : 16;
-    sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : (tuned && t.gpc) ? t.gpc : (uint32_t)max_groups_per_cu((int)sh.waves);
-    const uint64_t groups = (uint64_t)ctx->cu_count * sh.gpc;
-    if (ctx->cfg_log2B)
-        sh.log2B = ctx->cfg_log2B;
-    else if (tuned)
-        sh.log2B = t.log2B;
-    else if (small)
-        sh.log2B = batch_cap_log2B(msgs, n, slot_view(ctx), sh.waves, groups);
-    else  // the single-launch tile size of the whole batch's blocks, within 2^8..2^12
-        sh.log2B = std::min<uint32_t>(12, std::max<uint32_t>(8, heuristic_log2B(std::max<uint64_t>(1, m), groups * sh.waves)));
+    sh.waves = 16;
+    sh.gpc = groups_per_cu(sh.waves);
+    sh.log2B = batch_tile_cap(ctx, msgs, n, m, sh, small);
+    return sh;
+}
+
+Shape gcm::batch_shape(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small)
+{
+    uint64_t payload = 0, m = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        m += ghash_blocks(msgs[i].aad_len, msgs[i].len);
+        payload += msgs[i].len;
+    }
+    Shape sh;
+    if (!ctx->cfg_log2B && !ctx->cfg_waves) {
+        auto it = ctx->tuned_batch.find((uint64_t)size_bucket(n) << 32 | size_bucket(payload));
+        if (it != ctx->tuned_batch.end() && it->second.faster) {
+            sh = it->second;
+            sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : sh.gpc;
+            return sh;
+        }
+        if (!ctx->cfg_gpc)
+            return batch_rule(ctx, msgs, n, small);
+    }
+    sh.waves = ctx->cfg_waves ? ctx->cfg_waves : 16;
+    sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : groups_per_cu(sh.waves);
+    sh.log2B = ctx->cfg_log2B ? ctx->cfg_log2B : batch_tile_cap(ctx, msgs, n, m, sh, small);
     return sh;
 }
 

@@ -4,16 +4,21 @@
 //
 // Single messages: for one (key size, message size) point the search times
 // every shape of the tile kernel in {log2 tile blocks} x {waves per workgroup} x
-// {groups per CU} on a scratch message with HIP events, requires all of them to
-// produce the same tag (the counter map and GHASH exponents derive from block
-// indices only), and records the fastest in the context's cache, keyed by (key
-// bytes, floor(log2 len)), with the fan-in at which the reduction tree that
-// streams and the host pipeline end with was fastest for that shape.
+// {groups per CU} on a scratch message with HIP events, and the planner's own
+// shape, which may be the row kernel's, requires all of them to produce the same
+// tag (the counter map and GHASH exponents derive from block indices only), and
+// records the fastest in the context's cache, keyed by (key bytes,
+// floor(log2 len)), with the fan-in at which the reduction tree that streams and
+// the host pipeline end with was fastest for the shape that is used.
 //
 // Batches: the same search over {waves} x {groups per CU} x {cap on the
-// messages' tile sizes} on the caller's own batch, every point's tags and accept
-// flags compared with the first point's, recorded under (floor(log2 messages),
-// floor(log2 payload bytes)).
+// messages' tile sizes} and the planner's own shape on the caller's own batch,
+// every point's tags and accept flags compared with the first point's, recorded
+// under (floor(log2 messages), floor(log2 payload bytes)).
+//
+// Calls use a recorded shape if it was faster than the planner's own
+// (TuneEntry::faster): 1 MiB with AES-128 takes 12 us in rows, 19 in the best
+// tiles of the search.
 //
 // Every planner (one-shot, asynchronous, batches, the serving loop, host
 // pipeline, streamed segments) consults these caches when no explicit shape
@@ -48,7 +53,12 @@ std::vector<uint32_t> gpc_options(uint32_t waves)
     return v;
 }
 
-constexpr uint32_t kTurns = 4;  // what is compared is timed in turn this often
+// A shape replaces the planner's own if it takes less than 99% of its time; the
+// two are timed in turn this often.
+constexpr uint32_t kTurns = 4;
+bool is_faster(float shape_ms, float own_ms) { return shape_ms < 0.99f * own_ms; }
+
+bool same(const Shape &x, const Shape &y) { return x.log2B == y.log2B && x.waves == y.waves && x.gpc == y.gpc; }
 
 struct Timer {
     hipEvent_t a = nullptr, b = nullptr;
@@ -187,15 +197,27 @@ extern "C" int gcm_autotune(gcm_ctx *ctx, uint32_t key_len, uint64_t len, uint32
                     ++tried;
                     if (e == hipSuccess && ms < best_ms) {
                         best_ms = ms;
-                        best = sh;
+                        static_cast<Shape &>(best) = sh;
                     }
                 }
+        }
+        const Shape own = heuristic_shape(ctx, m);
+        if (!same(best, own)) {
+            ++tried;
+            float best_sum = 0.f, own_sum = 0.f;
+            for (uint32_t k = 0; k < kTurns && e == hipSuccess; ++k) {
+                e = time_shape(own, &own_sum);
+                if (e == hipSuccess)
+                    e = time_shape(best, &best_sum);
+            }
+            best.faster = is_faster(best_sum, own_sum);
         }
         // The tree over single partials, which whole-message launches do without
         // but streams and the host pipeline end with, at every fan-in.
         if (e == hipSuccess) {
-            const MsgDesc d = desc(best);
-            rc = launch_tile_range(ctx, d, best, ws, s);
+            const Shape &used = best.faster ? static_cast<const Shape &>(best) : own;
+            const MsgDesc d = desc(used);
+            rc = launch_tile_range(ctx, d, used, ws, s);
             e = rc ? hipErrorUnknown : hipSuccess;
             float least = 1e30f, sum[4] = {0.f, 0.f, 0.f, 0.f};
             for (uint32_t k = 0; k <= kTurns && e == hipSuccess; ++k)
@@ -282,6 +304,16 @@ extern "C" int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n,
         e = tm.init();
         if (e != hipSuccess)
             return fail_hip(e, "hipEventCreate");
+        std::vector<PlanMsg> msgs(n);
+        {
+            const SlotView sv = slot_view(ctx);
+            PlanError err;
+            for (uint32_t i = 0; i < n; ++i) {
+                if (check_job(jobs[i], i, base_bytes, sv, &err))
+                    return plan_error(err);
+                msgs[i] = plan_msg_from_job(jobs[i], (uint64_t)base_d);
+            }
+        }
         uint32_t tried = 0;
         bool have_ref = false, all_equal = true;
         int rc = GCM_OK;
@@ -307,7 +339,7 @@ extern "C" int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n,
             ++tried;
             return r;
         };
-        // every shape in every turn, so that a shape is not
+        // every shape and the planner's own in every turn, so that a shape is not
         // chosen for a moment in which the clock was high
         std::vector<TuneEntry> shapes;
         for (uint32_t w : kWaveOpts)
@@ -319,13 +351,23 @@ extern "C" int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n,
                     t.gpc = gpc;
                     shapes.push_back(t);
                 }
+        Shape own = batch_rule(ctx, msgs.data(), n, true);
         std::vector<float> sum(shapes.size(), 0.f);
-        for (uint32_t k = 0; k < kTurns && e == hipSuccess; ++k)
+        float own_sum = 0.f;
+        for (uint32_t k = 0; k < kTurns && e == hipSuccess; ++k) {
+            e = time_shape(own, &own_sum);
+            if (rc == GCM_E_NOMEM && k == 0) {  // as gcm_batch_create does
+                rc = GCM_OK;
+                own = batch_rule(ctx, msgs.data(), n, false);
+                e = time_shape(own, &own_sum);
+            }
             for (size_t q = 0; q < shapes.size() && e == hipSuccess; ++q)
                 e = time_shape(shapes[q], &sum[q]);
+        }
         const size_t at = std::min_element(sum.begin(), sum.end()) - sum.begin();
         TuneEntry best = shapes[at];
         const float best_ms = sum[at] / (float)kTurns;
+        best.faster = is_faster(sum[at], own_sum);
         ctx->prof = save_prof;
         if (rc)
             return rc;
@@ -349,7 +391,8 @@ extern "C" int gcm_batch_autotune(gcm_ctx *ctx, const gcm_job *jobs, uint32_t n,
 }
 
 // Cache file: {"arch": ..., "entries": [...], "batch_entries": [...]}, each
-// entry four size/shape integers and the groups per CU and fan-in.
+// entry four size/shape integers, the groups per CU, the fan-in, and whether the
+// shape was faster than the planner's own (which a file may lack: it was).
 extern "C" int gcm_autotune_save(gcm_ctx *ctx, const char *path)
 {
     GCM_ABI_TRY
@@ -367,9 +410,9 @@ extern "C" int gcm_autotune_save(gcm_ctx *ctx, const char *path)
         for (auto &kv : ctx->tuned) {
             std::fprintf(f,
                          "%s{\"key_bytes\": %u, \"len_log2\": %u, \"log2_tile_blocks\": %u, \"waves\": %u, "
-                         "\"groups_per_cu\": %u, \"fanin\": %u}",
+                         "\"groups_per_cu\": %u, \"fanin\": %u, \"faster\": %u}",
                          first ? "" : ", ", (uint32_t)(kv.first >> 32), (uint32_t)(kv.first & 0xffffffffu),
-                         kv.second.log2B, kv.second.waves, kv.second.gpc, kv.second.fanin);
+                         kv.second.log2B, kv.second.waves, kv.second.gpc, kv.second.fanin, kv.second.faster ? 1u : 0u);
             first = false;
         }
         std::fprintf(f, "], \"batch_entries\": [");
@@ -377,9 +420,9 @@ extern "C" int gcm_autotune_save(gcm_ctx *ctx, const char *path)
         for (auto &kv : ctx->tuned_batch) {
             std::fprintf(f,
                          "%s{\"msgs_log2\": %u, \"payload_log2\": %u, \"tile_cap_log2\": %u, \"waves\": %u, "
-                         "\"groups_per_cu\": %u, \"fanin\": %u}",
+                         "\"groups_per_cu\": %u, \"fanin\": %u, \"faster\": %u}",
                          first ? "" : ", ", (uint32_t)(kv.first >> 32), (uint32_t)(kv.first & 0xffffffffu),
-                         kv.second.log2B, kv.second.waves, kv.second.gpc, kv.second.fanin);
+                         kv.second.log2B, kv.second.waves, kv.second.gpc, kv.second.fanin, kv.second.faster ? 1u : 0u);
             first = false;
         }
         std::fprintf(f, "]}\n");
@@ -391,6 +434,13 @@ extern "C" int gcm_autotune_save(gcm_ctx *ctx, const char *path)
 static bool valid_entry(unsigned lt, unsigned wv, unsigned gp, unsigned fi)
 {
     return lt >= 6 && lt <= 20 && (wv == 8 || wv == 12 || wv == 16) && gp >= 1 && gp <= 64 && valid_fanin(fi);
+}
+
+static TuneEntry tune_entry(uint32_t log2B, uint32_t waves, uint32_t gpc, uint32_t fanin, uint32_t faster)
+{
+    TuneEntry t;
+    t.log2B = log2B, t.waves = waves, t.gpc = gpc, t.fanin = fanin, t.faster = faster != 0;
+    return t;
 }
 
 // Minimal reader for the format gcm_autotune_save writes; a cache for another
@@ -418,26 +468,26 @@ extern "C" int gcm_autotune_load(gcm_ctx *ctx, const char *path)
         size_t pos = 0;
         uint32_t loaded = 0;
         while ((pos = text.find("{\"key_bytes\":", pos)) != std::string::npos) {
-            unsigned kb, ll, lt, wv, gp, fi;
+            unsigned kb, ll, lt, wv, gp, fi, fa = 1;
             if (std::sscanf(text.c_str() + pos,
                             "{\"key_bytes\": %u, \"len_log2\": %u, \"log2_tile_blocks\": %u, \"waves\": %u, "
-                            "\"groups_per_cu\": %u, \"fanin\": %u}",
-                            &kb, &ll, &lt, &wv, &gp, &fi) == 6 &&
+                            "\"groups_per_cu\": %u, \"fanin\": %u, \"faster\": %u}",
+                            &kb, &ll, &lt, &wv, &gp, &fi, &fa) >= 6 &&
                 (kb == 16 || kb == 24 || kb == 32) && ll < 64 && valid_entry(lt, wv, gp, fi)) {
-                ctx->tuned[(uint64_t)kb << 32 | ll] = Shape{lt, wv, gp, fi};
+                ctx->tuned[(uint64_t)kb << 32 | ll] = tune_entry(lt, wv, gp, fi, fa);
                 ++loaded;
             }
             ++pos;
         }
         pos = 0;
         while ((pos = text.find("{\"msgs_log2\":", pos)) != std::string::npos) {
-            unsigned nl, pl, lt, wv, gp, fi;
+            unsigned nl, pl, lt, wv, gp, fi, fa = 1;
             if (std::sscanf(text.c_str() + pos,
                             "{\"msgs_log2\": %u, \"payload_log2\": %u, \"tile_cap_log2\": %u, \"waves\": %u, "
-                            "\"groups_per_cu\": %u, \"fanin\": %u}",
-                            &nl, &pl, &lt, &wv, &gp, &fi) == 6 &&
+                            "\"groups_per_cu\": %u, \"fanin\": %u, \"faster\": %u}",
+                            &nl, &pl, &lt, &wv, &gp, &fi, &fa) >= 6 &&
                 nl < 64 && pl < 64 && valid_entry(lt, wv, gp, fi)) {
-                ctx->tuned_batch[(uint64_t)nl << 32 | pl] = Shape{lt, wv, gp, fi};
+                ctx->tuned_batch[(uint64_t)nl << 32 | pl] = tune_entry(lt, wv, gp, fi, fa);
                 ++loaded;
             }
             ++pos;

@@ -127,6 +127,8 @@ int register_keys_locked(gcm_ctx *ctx, const uint8_t *const *keys, const uint32_
 // Every single-message path (one-shot, asynchronous, counter mode, host
 // pipeline, streamed segments, GCM-SIV) and gcm_workspace_size use it.
 Shape message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, uint64_t aad_len);
+// The heuristic alone, for m GHASH blocks.
+Shape heuristic_shape(const gcm_ctx *ctx, uint64_t m);
 // groups of the tile kernel (`waves` waves each) a compute unit holds
 uint32_t groups_per_cu(uint32_t waves);
 // the most waves the planners may count as resident (any wave count)
@@ -138,6 +140,8 @@ void stream_pool_release(gcm_ctx *ctx);
 // autotune cache, else the rules of gcm_plan.h (rows, or tiles and their cap).
 // small: tiles as small as is fastest; else, where memory is short, larger ones
 Shape batch_shape(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small = true);
+// The rules alone.
+Shape batch_rule(const gcm_ctx *ctx, const PlanMsg *msgs, uint32_t n, bool small);
 // the key table as the planner sees it
 SlotView slot_view(const gcm_ctx *ctx);
 // lengths and device buffers of one message (see check_buffers)

@@ -36,7 +36,11 @@ constexpr uint64_t kMaxAad = (1ull << 61) - 1;   // < 2^64 bits
 struct Shape {
     uint32_t log2B = 16, waves = 16, gpc = 1, fanin = 2;
 };
-using TuneEntry = Shape;
+// An autotune cache entry: the fastest shape of its search, and whether calls use
+// it, or were at least as fast with the shape they have without an entry.
+struct TuneEntry : Shape {
+    bool faster = true;
+};
 
 // size bucket of the autotune caches: floor(log2 x) (0 for x <= 1)
 inline uint32_t size_bucket(uint64_t x)

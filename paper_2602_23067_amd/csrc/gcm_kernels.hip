@@ -452,10 +452,6 @@ __global__ __launch_bounds__(64) void k_key_setup(KeyChunk chunk, const uint32_t
     write_hpow(hd, h_sh, frob, (int)threadIdx.x);
 }
 
-// Fixed-multiplier tables.  Block b < kTab4Levels builds the nibble-position
-// table of H^(2^b); the next sixteen build the byte-position table of
-// H^(2^kStrideLevel) = H^64, the per-lane Horner multiplier of the tile
-// kernel, one byte position each.
 // a * b for one operand pair, all 64 lanes of the wave cooperating: lane i
 // contributes the terms of bits i and i + 64 of a (b * x^i, b * x^(i + 64)),
 // folded once, then an XOR across the wave sums them.  Every lane returns the
@@ -504,11 +500,13 @@ __device__ __forceinline__ u32x4 gf_mul2_wave(u32x4 a, u32x4 b, u32x4 c, u32x4 d
 //                   that this table is not the launch's longest block)
 //   blocks 56..71:  H^e, e = 0..63, and its 4-bit window table for the lane
 //                   l = 63 - e that multiplies by it in the tile fix-up, one a wave
-//   blocks 72..105: the group lifts H^(2^s * j) and H^(64 e + 32), one a wave
-// 1024 keys at once: 671 us with a block for each window and no lifts, 745 us
-// with the lifts, 721 us with the windows four a block.
+//   blocks 72..86:  the group lifts H^(2^s * j) and H^(64 e + 32), a wave those that
+//                   share factors
+// Bound by the vector units.  1024 keys: 459 us without lifts, 514 us with a wave
+// and one to four products for each lift, 458 us this way (and without products
+// by the field's one).
 constexpr int kTab8Blocks = 16, kWinBlocks = kLanePows / 4;
-constexpr int kLiftBlocks = (7 * kLiftLevels + 16 + 3) / 4;
+constexpr int kLiftBlocks = (3 * kLiftLevels + 8 + 3) / 4;
 constexpr int kKeyTableBlocks = kTab4Levels + kTab8Blocks + kWinBlocks + kLiftBlocks;
 __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
 {
@@ -524,34 +522,62 @@ __global__ __launch_bounds__(256) void k_key_tables(SlotChunk chunk)
             m_sh = u32x4{hd->hpow[lvl][0], hd->hpow[lvl][1], hd->hpow[lvl][2], hd->hpow[lvl][3]};
         }
     } else if (b >= kTab4Levels + kTab8Blocks + kWinBlocks) {
+        // a wave forms powers that share factors, one product each
         const int q = 4 * (b - kTab4Levels - kTab8Blocks - kWinBlocks) + (int)uniform(tid >> 6);
-        const bool half = q < 16;  // H^(64 q + 32)
-        const int row = (q - 16) / kLiftLevels, lvl = half ? 6 : kLiftLo + (q - 16) % kLiftLevels;
-        const int j = half ? q : 2 * row + 3;
-        if (!half && (row > 6 || (row > 2 && lvl > kLiftHi - 2)))
+        const auto pow2 = [&](int k) { return u32x4{hd->hpow[k][0], hd->hpow[k][1], hd->hpow[k][2], hd->hpow[k][3]}; };
+        u32x4 *halves = reinterpret_cast<u32x4 *>(slot + kSlotTab8Off);
+        u32x4 *high = reinterpret_cast<u32x4 *>(slot + kSlotLaneWinOff);
+        const bool write = (tid & 63) == 0;
+        if (q < 8) {  // H^(64 e + 32) for e = q, q + 8
+            u32x4 m = pow2(5);
+            for (int k = 0; k < 3; ++k)
+                if ((q >> k) & 1)
+                    m = gf_mul_wave(m, pow2(6 + k));
+            const u32x4 m8 = gf_mul_wave(m, pow2(9));
+            if (write)
+                halves[q] = m, halves[q + 8] = m8;
             return;
-        u32x4 m = {0x80u, 0u, 0u, 0u};  // the field's one
-        if (half)
-            m = u32x4{hd->hpow[5][0], hd->hpow[5][1], hd->hpow[5][2], hd->hpow[5][3]};
-        for (int k = 0; k < 4; ++k)
-            if ((j >> k) & 1) {
-                const uint32_t *h = hd->hpow[lvl + k];
-                m = gf_mul_wave(m, u32x4{h[0], h[1], h[2], h[3]});
-            }
-        u32x4 *dst = half ? reinterpret_cast<u32x4 *>(slot + kSlotTab8Off) + q
-                     : row < 3 ? reinterpret_cast<u32x4 *>(reinterpret_cast<KeySlotHdr *>(slot)->lift[row][lvl - kLiftLo])
-                             : reinterpret_cast<u32x4 *>(slot + kSlotLaneWinOff) + 16 * (row - 3) + (lvl - kLiftLo);
-        if ((tid & 63) == 0)
-            *dst = m;
+        }
+        const int chain = (q - 8) / kLiftLevels, lvl = kLiftLo + (q - 8) % kLiftLevels, at = lvl - kLiftLo;
+        if (chain > 2)
+            return;
+        KeySlotHdr *out = reinterpret_cast<KeySlotHdr *>(slot);
+        const auto lift = [&](int j, u32x4 m) {  // H^(2^lvl * j)
+            u32x4 *dst = j < 9 ? reinterpret_cast<u32x4 *>(out->lift[(j - 3) >> 1][at]) : high + 8 * (j - 9) + at;
+            if (write)
+                *dst = m;
+        };
+        const bool upper = lvl <= kLiftHi - 2;  // j = 9, 11, 13, 15 too
+        const u32x4 m1 = pow2(lvl);
+        if (chain == 0) {
+            const u32x4 m3 = gf_mul_wave(m1, pow2(lvl + 1)), m7 = gf_mul_wave(m3, pow2(lvl + 2));
+            lift(3, m3);
+            lift(7, m7);
+            if (upper)
+                lift(15, gf_mul_wave(m7, pow2(lvl + 3)));
+        } else if (chain == 1) {
+            const u32x4 m5 = gf_mul_wave(m1, pow2(lvl + 2));
+            lift(5, m5);
+            if (upper)
+                lift(13, gf_mul_wave(m5, pow2(lvl + 3)));
+        } else if (upper) {
+            const u32x4 m9 = gf_mul_wave(m1, pow2(lvl + 3));
+            lift(9, m9);
+            lift(11, gf_mul_wave(m9, pow2(lvl + 1)));
+        }
         return;
     } else {
         // H^e as the product of H^(2^k) over the set bits of e,
         // then lane v = 1..15 writes (v * H^e) mod P for lane 63 - e
         const int e = 4 * (b - kTab4Levels - kTab8Blocks) + (int)uniform(tid >> 6), lane = tid & 63;
         u32x4 m = {0x80u, 0u, 0u, 0u};  // the field's one
+        bool one = true;
         for (int k = 0; k < 6; ++k)
-            if ((e >> k) & 1)
-                m = gf_mul_wave(m, u32x4{hd->hpow[k][0], hd->hpow[k][1], hd->hpow[k][2], hd->hpow[k][3]});
+            if ((e >> k) & 1) {
+                const u32x4 h = {hd->hpow[k][0], hd->hpow[k][1], hd->hpow[k][2], hd->hpow[k][3]};
+                m = one ? h : gf_mul_wave(m, h);
+                one = false;
+            }
         if (lane > 0 && lane < 16) {
             const uint32_t mm[4] = {m.x, m.y, m.z, m.w};
             const P128 pm = mem_to_poly(mm);

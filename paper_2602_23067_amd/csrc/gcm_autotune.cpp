@@ -224,8 +224,7 @@ extern "C" int gcm_autotune(gcm_ctx *ctx, uint32_t key_len, uint64_t len, uint32
                 for (uint32_t f = 0; f < 4 && e == hipSuccess; ++f) {
                     float ms = 0.f;
                     e = tm.add(s, reps, &ms, [&] {
-                        return launch_combine(nullptr, 1, &d, ws + workspace_counter_bytes(1),
-                                              reinterpret_cast<uint32_t *>(ws), kFaninOpts[f], s);
+                        return launch_combine(nullptr, 1, &d, ws + workspace_counter_bytes(1), kFaninOpts[f], s);
                     });
                     if (k)
                         sum[f] += ms;  // the first round is the warm-up

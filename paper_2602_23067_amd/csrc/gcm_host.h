@@ -194,9 +194,11 @@ hipError_t launch_tiles(int waves, const MsgDesc *descs, const WorkItem *items, 
                         const MsgDesc *single, const uint32_t *te0, void *partials, uint32_t *counters, uint32_t grid,
                         bool rows, hipStream_t s);  // rows: a batch of one-row tiles
 int max_groups_per_cu(int waves);
-// fanin: children per node of the reduction tree over tile partials (2, 4, 8, 16)
+// The tree over single tile partials, fanin (2, 4, 8, 16) children a node: the
+// lifted GHASH values (MsgDesc.yout) of a streamed message's segments, or a
+// message's tag or accept flag
 hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
-                          uint32_t *counters, uint32_t fanin, hipStream_t s);
+                          uint32_t fanin, hipStream_t s);
 // grouped messages (MsgDesc.log2G > 0): tag or verdict from the lifted partials;
 // a single message's rejected output is cleared, a batch's rejected messages
 // are listed in `counters` for launch_zerofill

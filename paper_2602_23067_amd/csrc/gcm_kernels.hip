@@ -2049,7 +2049,7 @@ __global__ __launch_bounds__(256) void k_gcm_verdict(MsgDesc single, const MsgDe
     const u32x4 ek = part[P];
     const int tl = (int)dp->tag_len;  // T = MSB_t of the full tag
     GLOBAL_AS uint8_t *dst = gptr<uint8_t>(dp->tag);
-    const uint32_t want = dp->op == 1 && !dp->yout && lane < tl ? dst[lane] : 0u;  // asked for with the partials
+    const uint32_t want = dp->op == 1 && lane < tl ? dst[lane] : 0u;  // asked for with the partials
     u32x4 s = {0, 0, 0, 0};
     for (uint64_t i = threadIdx.x; i < P; i += 256)
         s ^= part[i];
@@ -2064,11 +2064,6 @@ __global__ __launch_bounds__(256) void k_gcm_verdict(MsgDesc single, const MsgDe
         s = gf_mul_wave(s, u32x4{hd->hpow[0][0], hd->hpow[0][1], hd->hpow[0][2], hd->hpow[0][3]});
     }
     const bool lead = (BATCH || blockIdx.x == 0) && threadIdx.x == 0;
-    if (dp->yout) {
-        if (lead)
-            *gptr<u32x4>(dp->yout) = s;
-        return;
-    }
     const u32x4 tag = s ^ ek;
     const uint32_t mine = byte_of(tag, lane & 15);
     if (dp->op == 0) {
@@ -2112,8 +2107,7 @@ constexpr int kCombineLog2 = 10;
 // partials.
 template <bool BATCH, int LOGF>
 __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *__restrict__ descs, MsgDesc single,
-                                                                 const u32x4 *__restrict__ partials,
-                                                                 uint32_t *counters)
+                                                                 const u32x4 *__restrict__ partials)
 {
     __shared__ u32x4 tabs[kCombineLog2 + 2][512];  // [0]: H; [1+k]: H^(B*2^k), k = 0..10
     __shared__ u32x4 leaf[kCombineThreads];
@@ -2218,11 +2212,10 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
     }
     // * H, by the first half-wave
     const u32x4 s = mul_tab4_half(i < 32 ? leaf[0] : u32x4{0, 0, 0, 0}, tabs[0], i & 31u, i < 32);
-    if (d.yout) {
-        // a streamed segment (or a POLYVAL pass): hand on its GHASH value,
-        // first multiplied by H^lift (the blocks of the message that follow
-        // the segment) with the key slot's nibble tables of H^(2^k), one
-        // half-wave product per set bit
+    if (BATCH) {
+        // streamed segments: hand on each one's GHASH value, first multiplied by
+        // H^lift (the blocks of the message that follow the segment) with the key
+        // slot's nibble tables of H^(2^k), one half-wave product per set bit
         if (i >= 64)
             return;
         u32x4 y = s;
@@ -2247,12 +2240,7 @@ __global__ __launch_bounds__(kCombineThreads) void k_gcm_combine(const MsgDesc *
             uint32_t diff = 0;
             for (int k = 0; k < tl; ++k)
                 diff |= ((tw[k >> 2] >> (8 * (k & 3))) & 0xffu) ^ exp[k];
-            const int32_t ok = diff == 0 ? 1 : 0;
-            *reinterpret_cast<int32_t *>(d.ok) = ok;
-            if (!ok) {
-                const uint32_t pos = atomicAdd(&counters[0], 1u);
-                counters[1 + pos] = BATCH ? blockIdx.x : 0u;
-            }
+            *reinterpret_cast<int32_t *>(d.ok) = diff == 0 ? 1 : 0;
         }
     }
 }
@@ -2727,33 +2715,30 @@ int max_groups_per_cu(int waves)
 }
 
 template <int LOGF>
-static void launch_combine_f(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const u32x4 *p,
-                             uint32_t *counters, hipStream_t s)
+static void launch_combine_f(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const u32x4 *p, hipStream_t s)
 {
     if (descs)
-        hipLaunchKernelGGL((k_gcm_combine<true, LOGF>), dim3(n_msgs), dim3(kCombineThreads), 0, s, descs, MsgDesc{},
-                           p, counters);
+        hipLaunchKernelGGL((k_gcm_combine<true, LOGF>), dim3(n_msgs), dim3(kCombineThreads), 0, s, descs, MsgDesc{}, p);
     else
-        hipLaunchKernelGGL((k_gcm_combine<false, LOGF>), dim3(1), dim3(kCombineThreads), 0, s, nullptr, *single, p,
-                           counters);
+        hipLaunchKernelGGL((k_gcm_combine<false, LOGF>), dim3(1), dim3(kCombineThreads), 0, s, nullptr, *single, p);
 }
 
 hipError_t launch_combine(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *single, const void *partials,
-                          uint32_t *counters, uint32_t fanin, hipStream_t s)
+                          uint32_t fanin, hipStream_t s)
 {
     const u32x4 *p = reinterpret_cast<const u32x4 *>(partials);
     switch (fanin) {
     case 2:
-        launch_combine_f<1>(descs, n_msgs, single, p, counters, s);
+        launch_combine_f<1>(descs, n_msgs, single, p, s);
         break;
     case 4:
-        launch_combine_f<2>(descs, n_msgs, single, p, counters, s);
+        launch_combine_f<2>(descs, n_msgs, single, p, s);
         break;
     case 8:
-        launch_combine_f<3>(descs, n_msgs, single, p, counters, s);
+        launch_combine_f<3>(descs, n_msgs, single, p, s);
         break;
     case 16:
-        launch_combine_f<4>(descs, n_msgs, single, p, counters, s);
+        launch_combine_f<4>(descs, n_msgs, single, p, s);
         break;
     default:
         return hipErrorInvalidValue;
@@ -2768,8 +2753,7 @@ hipError_t launch_verdict(const MsgDesc *descs, uint32_t n_msgs, const MsgDesc *
     if (descs) {
         hipLaunchKernelGGL(k_gcm_verdict<true>, dim3(n_msgs), dim3(256), 0, s, MsgDesc{}, descs, p, counters);
     } else {
-        const uint32_t grid = single->yout ? 1 : verdict_groups(*single);
-        hipLaunchKernelGGL(k_gcm_verdict<false>, dim3(grid), dim3(256), 0, s, *single, nullptr, p, counters);
+        hipLaunchKernelGGL(k_gcm_verdict<false>, dim3(verdict_groups(*single)), dim3(256), 0, s, *single, nullptr, p, counters);
     }
     return hipGetLastError();
 }

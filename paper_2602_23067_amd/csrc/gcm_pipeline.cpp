@@ -224,9 +224,7 @@ static int run_pipeline(gcm_ctx *ctx, uint32_t op, const uint8_t *key, size_t ke
         }
     }
     if (rc == GCM_OK && e == hipSuccess) {
-        uint32_t *counters = reinterpret_cast<uint32_t *>(ctx->d_ws);
-        const uint8_t *partials = ctx->d_ws + workspace_counter_bytes(1);
-        e = launch_combine(nullptr, 1, &d, partials, counters, shape.fanin, sc);
+        e = launch_combine(nullptr, 1, &d, ctx->d_ws + workspace_counter_bytes(1), shape.fanin, sc);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ctx->h_io, ctx->d_io, 32, hipMemcpyDeviceToHost, sc);
     }

@@ -41,7 +41,6 @@ Shape siv_shape(const gcm_ctx *ctx, uint64_t m)
                                                   : heuristic_waves(m, (uint64_t)ctx->cu_count, groups_per_cu);
     sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : groups_per_cu(sh.waves);
     sh.log2B = ctx->cfg_log2B ? ctx->cfg_log2B : heuristic_log2B(m, (uint64_t)ctx->cu_count * sh.gpc * sh.waves);
-    sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : 2;
     return sh;
 }
 

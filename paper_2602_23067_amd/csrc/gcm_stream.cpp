@@ -352,8 +352,7 @@ extern "C" int gcm_stream_final(gcm_stream *st, uint8_t *tag_d, int32_t *accept_
         std::memcpy(st->h_desc, st->segs.data(), desc_bytes);
         e = hipMemcpyAsync(d_descs, st->h_desc, desc_bytes, hipMemcpyHostToDevice, s);
         if (e == hipSuccess)
-            e = launch_combine(d_descs, k, nullptr, st->d_part + kHeader, reinterpret_cast<uint32_t *>(st->d_part),
-                               st->fanin, s);
+            e = launch_combine(d_descs, k, nullptr, st->d_part + kHeader, st->fanin, s);
         const MsgDesc &first = st->segs.front();
         if (e == hipSuccess)
             e = launch_fold(vals, k, st->d_part + kHeader + 16 * (first.tile_base + first.n_tiles), tag_d, accept_d,

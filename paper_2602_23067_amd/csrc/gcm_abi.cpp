@@ -424,18 +424,15 @@ Shape gcm::message_shape(const gcm_ctx *ctx, uint32_t key_bytes, uint64_t len, u
         }
     }
     const uint64_t m = ghash_blocks(aad_len, len);
-    if (ctx->cfg_waves)
-        sh.waves = ctx->cfg_waves;
-    else if (tuned)
-        sh.waves = t.waves;
-    else if (ctx->cfg_log2B || ctx->cfg_gpc)
-        sh.waves = 16;
-    else
+    if (!tuned && !ctx->cfg_log2B && !ctx->cfg_waves && !ctx->cfg_gpc) {
         sh = heuristic_shape(ctx, m);
-    sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : tuned ? t.gpc : groups_per_cu(sh.waves);
-    sh.log2B = ctx->cfg_log2B ? ctx->cfg_log2B
-               : tuned        ? t.log2B
-                              : heuristic_log2B(m, (uint64_t)ctx->cu_count * sh.gpc * sh.waves);
+    } else {
+        sh.waves = ctx->cfg_waves ? ctx->cfg_waves : tuned ? t.waves : 16;
+        sh.gpc = ctx->cfg_gpc ? ctx->cfg_gpc : tuned ? t.gpc : groups_per_cu(sh.waves);
+        sh.log2B = ctx->cfg_log2B ? ctx->cfg_log2B
+                   : tuned        ? t.log2B
+                                  : heuristic_log2B(m, (uint64_t)ctx->cu_count * sh.gpc * sh.waves);
+    }
     sh.fanin = ctx->cfg_fanin ? ctx->cfg_fanin : fanin;
     return sh;
 }

@@ -906,13 +906,14 @@ def main():
     payload_gbs = n / (ms_enc * 1e-3) / 1e9
     traffic = 2 * n + aad_len + 16
     blocks = (n + 15) // 16 + (aad_len + 15) // 16 + 1
-    # the tile count of the launch the library plans for this message (its partials are written)
+    # the tile count of the launch the library plans for this message (a 16-byte partial for those of
+    # a workgroup, or of a third of one of twelve waves, is written)
     plan = ctx.launch_plan(len(msg.key), n, aad_len)
     tiles = plan["tiles"]
     assert tiles == -(-blocks // (1 << plan["log2_tile_blocks"]))
-    tile_bytes = 2 * n + aad_len + 16 * tiles
+    tile_bytes = 2 * n + aad_len + 16 * -(-tiles // {16: 16, 12: 4, 8: 8}[plan["waves_per_group"]])
     nr = len(msg.key) // 4 + 6
-    lds_bytes_per_block = 4 * (1 + 4 + 16 * (nr - 3) + 16) + 16 * 16
+    lds_bytes_per_block = 4 * (16 * (nr - 3) + 16) + 16 + 16 * 16
     tile_gbs = tile_bytes / (tile_ms * 1e-3) / 1e9
 
     cpu = None
@@ -993,8 +994,8 @@ def main():
             "algorithmic_bytes_per_launch": tile_bytes,
         },
         # the resource that binds the tile kernel: LDS reads of the AES T-tables
-        # (4 bytes per lane per lookup; 197 lookups per AES-256 block with
-        # counter-mode caching through round 2) and of the GHASH byte table
+        # (4 bytes per lane per lookup; 192 lookups per AES-256 block with
+        # counter-mode caching, and one of 16 bytes for round 2) and of the GHASH byte table
         # (16 lookups of 16 bytes), against 128 B/clk/CU x 256 CUs at the
         # nominal 2.4 GHz (the chip runs slower under this load: see
         # issue_at_measured_clock)

@@ -5,8 +5,8 @@
 // tiles), the prefix sum of tiles over messages (each message's first
 // partial-hash slot), and a work list of workgroup items -- `waves`
 // consecutive wave tiles of one message -- handed out so that the persistent
-// workgroups end together (spread_items), items of equal cost by key slot, so
-// that a workgroup reloads its key's tables only when the key changes.
+// workgroups end together (spread_items), each running its own by key slot, so
+// that it reloads the tables only when the key changes.
 // Launching a plan enqueues up to three kernels (tiles; for messages of more
 // than one workgroup item a verdict and the zero-fill of rejected ones) and
 // allocates nothing, so it can be captured into a hipGraph and replayed.

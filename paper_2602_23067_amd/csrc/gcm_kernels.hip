@@ -1489,9 +1489,11 @@ struct StageKeys {
 // message (single) or a batch with a list of items.
 //
 // What bounds it is the LDS.  Per row of 64 blocks and CU, AES-256: 192 b32
-// lookups, which take 2.27 cycles each with 16 waves in a loop of nothing
-// else, one b128 for round 2 and 16 b128 of GHASH: 453 LDS cycles of 523 in
-// all, 425 vector instructions.  1 GiB with AES-256 / AES-128:
+// lookups of two cycles, one b128 of four for round 2 and 16 b128 of GHASH, 453
+// cycles (by the counter of its active cycles) of 528 over the whole launch, with
+// 427 vector instructions.  (16 waves that do nothing else get a b32 lookup every
+// 2.05 cycles, every 2.27 where each address depends on the lookup before, as it
+// does in AES.)  1 GiB with AES-256 / AES-128:
 //   GCM           1058 -> 1039 us, 823 -> 805 us
 //   counter mode  1006 ->  824 us, 746 -> 627 us (32 table copies: no key
 //                 rotations, 449 cycles a row where it took 566)
@@ -1802,8 +1804,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_gcm_tiles(MsgDesc single, const 
 // another, so that a message costs 8 KiB of windows and not 80 KiB of tables; two
 // workgroups of eight waves share a compute unit and hide each other's waits
 // (72.3 KiB of LDS each; the launch bound asks for no more registers than that).
-// The vector units bound it, some 1400 instructions a row: 1024 messages with a
-// median of 4 KiB and 2 KiB of AAD, 79 us by tiles, 50 us.
+// A wave issues some 990 vector instructions for an item, with a row or without,
+// which keep the vector units busy 69% of the time, the LDS 30%; the rest is the
+// start of an item.  1024 messages with a median of 4 KiB and 2 KiB of AAD, 12022
+// rows: 79 us by tiles, 39 us.
 constexpr uint32_t kRowWin = 0x10000u, kRowSums = 0x12000u;
 
 template <int WAVES, bool BATCH, int KIND>

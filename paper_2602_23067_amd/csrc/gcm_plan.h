@@ -9,7 +9,9 @@
 // X = A || 0-pad || C || 0-pad || L has m = n_A + n + 1 blocks (SP 800-38D
 // GCM-AE step 5), left-padded with z zero blocks so that m + z = T * 2^log2B
 // (GHASH(0^z || X) = GHASH(X)); wave tile t covers padded positions
-// [t * 2^log2B, (t + 1) * 2^log2B) and leaves one 16-byte partial.
+// [t * 2^log2B, (t + 1) * 2^log2B).  The tiles of a workgroup leave one 16-byte
+// partial together (set_groups), but for streams and the host pipeline, whose
+// tiles leave one each.
 #pragma once
 #include <stdarg.h>
 #include <stdint.h>
@@ -193,10 +195,10 @@ inline uint32_t batch_msg_log2B(uint64_t m, uint32_t waves, uint32_t cap)
 
 // Whether a batch of n messages, m GHASH blocks in all, goes to the row kernel
 // (one-row tiles, two workgroups of eight waves a compute unit).  A row takes it
-// 1400 cycles, bound by the vector units, where the tile kernel takes 523; but an
-// item of the tile kernel costs about 15000 cycles besides, most of them for the
-// 80 KiB of key tables, so that messages of less than some 17 rows are better off
-// with rows (1024 messages, median 8 KiB with 1 KiB of AAD: 55 us, 63 with tiles;
+// 1100 cycles with AES-128, 1230 with AES-256, where the tile kernel takes 388 and
+// 523; but an item of the tile kernel costs some 12000 cycles besides, most of them
+// for the 80 KiB of key tables, so that messages of up to some 17 rows are better
+// off with rows (1024 messages, median 8 KiB with 1 KiB of AAD: 55 us, 63 with tiles;
 // median 16 KiB: 89 and 78), and so is what gives every wave slot of the chip at
 // most a row (64 messages, median 16 KiB: 15 us, 27 with tiles).
 inline bool batch_rows(uint64_t n, uint64_t m, uint64_t cus) { return m <= 1024 * n || m <= 64 * 16 * cus; }
@@ -393,9 +395,8 @@ inline PlanMsg plan_msg_from_job(const gcm_job &j, uint64_t base)
 
 // The persistent launch of a batch: descriptors (message i's partials start
 // at tile_base, after the n_tiles + 2 slots of the messages before it), and
-// the work list -- items of `waves` consecutive wave tiles of one message --
-// ordered by key slot so that a persistent workgroup restages its GHASH table
-// only when the key changes.
+// the work list -- items of `waves` consecutive wave tiles of one message -- by
+// key slot, which spread_items shares out among the workgroups.
 struct BatchPlan {
     std::vector<MsgDesc> descs;
     std::vector<WorkItem> items;

@@ -546,7 +546,10 @@ inline uint32_t batch_cap_log2B(const PlanMsg *msgs, uint32_t n, const SlotView 
 // lognormal; 1204 us), and half as much again as the mean with 1024 of 16 KiB
 // (124 us).  What a workgroup has been given it runs in the list's order, by key
 // slot and message, so that it stages each key's tables once, however few keys
-// the messages share.
+// the messages share; items of up to six on average the largest first, but
+// together by message and key (1024 messages, median 16 KiB: 86.8 us, 87.3 in the
+// list's order; 2000 of 1 MiB: 3298 us, 3191 in the list's, where workgroups run
+// parts of a message at the same time).
 inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint32_t grid, std::vector<WorkItem> *items)
 {
     const size_t n = items->size(), g = grid;
@@ -593,15 +596,45 @@ inline void spread_items(const std::vector<MsgDesc> &descs, uint32_t waves, uint
         moved = cost[cls[by_cost[at]]] != cost[cls[by_cost[at + m - 1]]];
     }
     // the workgroups with an item in the last round, the first of `load`, come first
-    std::vector<uint32_t> next(g);
+    std::vector<uint32_t> next(g), run(n);
     for (size_t k = 0; k < g; ++k)
         next[load[k].second] = (uint32_t)k;
-    std::vector<WorkItem> out(n);
-    for (size_t i = 0; i < n; ++i) {
+    const bool few = n <= 6 * g;
+    for (size_t k = 0; k < n; ++k) {
+        const uint32_t i = few ? by_cost[k] : (uint32_t)k;
         uint32_t &to = next[taker[i]];
-        out[to] = (*items)[i];
+        run[to] = i;
         to += (uint32_t)g;
     }
+    if (few) {
+        std::vector<uint32_t> msg(n, 0), slot(n, 0);  // numbered in the list's order
+        for (size_t i = 1; i < n; ++i) {
+            const uint32_t m = (*items)[i].msg, before = (*items)[i - 1].msg;
+            msg[i] = msg[i - 1] + (m != before);
+            slot[i] = slot[i - 1] + (descs[m].slot != descs[before].slot);
+        }
+        // an item goes behind the last one of its message, or else of its key
+        for (size_t p = g; p < n && slot[n - 1] + 1 < n; ++p) {
+            const uint32_t i = run[p];
+            size_t to = 0;  // none yet
+            for (size_t q = p; q >= g; q -= g) {
+                const uint32_t j = run[q - g];
+                if (msg[j] == msg[i]) {
+                    to = q;
+                    break;
+                }
+                if (slot[j] == slot[i] && !to)
+                    to = q;
+            }
+            to = to ? to : p;
+            for (size_t q = p; q > to; q -= g)
+                run[q] = run[q - g];
+            run[to] = i;
+        }
+    }
+    std::vector<WorkItem> out(n);
+    for (size_t k = 0; k < n; ++k)
+        out[k] = (*items)[run[k]];
     items->swap(out);
 }
 
